@@ -41,6 +41,23 @@ __device__ __forceinline__ void scatter_atomic(const WaveLds<KS>& W, int count, 
 //   dL/da_i = dL/ds s^2 a_i / r_i^3 - dL/dq_i c_i b_i / r_i^2,
 //   dL/db_i = dL/ds s^2 b_i / r_i^3 + dL/dq_i c_i a_i / r_i^2,
 // written to gq[l][16] (zero where s = 0); zin is z.
+//
+// <G, v_j> and the sums over j are formed in fp64 (fp32 x fp32 products are
+// exact there).  Next to a lattice point one term carries all of dq (and
+// behind the activation layer dL/ds is sum_j w_j <G, v_j>), so a cancelling
+// fp32 dot product would become the relative error of the whole gradient.
+//
+// What bounds it is VALU issue: with up to 16 lanes to a row, every row's dot
+// product crossed four fp64 shuffle steps and every lane repeated its row's
+// coefficient (about 330 VALU instructions per lookup at m = 64 fp32).  Four
+// lanes to a row instead (each reads its 16 bytes of every 64): the two
+// passes' dot products are reduced together by one exchange of halves and
+// one sum, after which two lanes hold each row's coefficient and take four
+// coordinates each; the sum over the 32 rows halves the number of coordinates
+// per lane at its first two steps.  Measured at 262,144 lookups (m = 64 fp32,
+// 2^20 rows): merged backward behind the activation layer 1,606 -> 1,368 us;
+// untruncated backward of 29,997 lookups (m = 32 fp32) 322 -> 247 us; 4,096
+// lookups at K = 4 21.3 -> 19.6 us.
 template <int DT, int M, bool TH, int KS>
 __device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS>& W, const Tables& T, int count,
                                            const char* __restrict__ tb, const float* __restrict__ gout, int64_t l,
@@ -48,104 +65,120 @@ __device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS>& W,
                                            const Params& P) {
   constexpr int R = chunk_rows<KS>();  // rows per chunk of the row loop
   using G = RowGeom<DT, M, R>;
-  constexpr int ICOORD = G::LPR >= 8 ? 1 : 8 / G::LPR;  // query coordinates per lane
+  constexpr int LE = G::LPR / G::NP;   // lanes that share a row's dot product in the end (2, or 4 for chunks of 16)
+  constexpr int IC = 8 / LE;           // query coordinates per lane
   const int rsub = lane / G::LPR, ch = lane % G::LPR;
-  double dq[ICOORD];
+  const int e = lane % LE;
+  const int pass = ch / LE;            // the pass whose row this lane ends up with
+  double dq[IC];
   double dls = 0.0;  // dL/ds (TH)
 #pragma unroll
-  for (int k = 0; k < ICOORD; ++k) dq[k] = 0.0;
+  for (int k = 0; k < IC; ++k) dq[k] = 0.0;
   if (count > 0) {
-    float g[G::EPC];
-    const float* gp = gout + (size_t)l * M + ch * G::EPC;
+    double g[G::NC * G::EPC];
 #pragma unroll
-    for (int e = 0; e < G::EPC; e += 4) {
-      const float4 gv = *reinterpret_cast<const float4*>(gp + e);
-      g[e] = gv.x; g[e + 1] = gv.y; g[e + 2] = gv.z; g[e + 3] = gv.w;
-    }
-    // per-lane selectors of the query coordinates this lane accumulates
-    uint32_t lsel[ICOORD];
+    for (int c = 0; c < G::NC; ++c) {
+      const float* gp = gout + (size_t)l * M + (c * G::LPR + ch) * G::EPC;
 #pragma unroll
-    for (int k = 0; k < ICOORD; ++k) {
-      lsel[k] = F.sel[(ch + k * G::LPR) & 7];
+      for (int k = 0; k < G::EPC; k += 4) {
+        const float4 gv = *reinterpret_cast<const float4*>(gp + k);
+        g[c * G::EPC + k] = gv.x; g[c * G::EPC + k + 1] = gv.y;
+        g[c * G::EPC + k + 2] = gv.z; g[c * G::EPC + k + 3] = gv.w;
+      }
     }
+    // selectors of the query coordinates e*IC .. this lane accumulates
+    uint32_t lsel[IC];
+#pragma unroll
+    for (int k = 0; k < IC; ++k) lsel[k] = F.sel[e * IC + k];
     for (int r0 = 0; r0 < (KS == NB ? 1 : count); r0 += R) {
-      uint4 v[G::NP];
-      int32_t sl[G::NP];
+      // rows of padding entries read row 0; their coefficient is zeroed below
+      uint4 v[G::NP][G::NC];
 #pragma unroll
       for (int p = 0; p < G::NP; ++p) {
-        sl[p] = W.nbr[0][r0 + p * G::RPP + rsub].slot;
-        v[p] = sl[p] >= 0 ? *reinterpret_cast<const uint4*>(tb + (size_t)sl[p] * G::RB + ch * 16)
-                          : make_uint4(0, 0, 0, 0);
+        const int32_t s = max(W.nbr[0][r0 + p * G::RPP + rsub].slot, 0);
+        const char* src = tb + (size_t)s * G::RB + ch * 16;
+#pragma unroll
+        for (int c = 0; c < G::NC; ++c) v[p][c] = *reinterpret_cast<const uint4*>(src + c * (G::LPR * 16));
+      }
+      double pd[G::NP];
+#pragma unroll
+      for (int p = 0; p < G::NP; ++p) {
+        pd[p] = 0.0;
+#pragma unroll
+        for (int c = 0; c < G::NC; ++c) {
+          float f[G::EPC];
+          unpack16<DT, G::EPC>(v[p][c], f);
+#pragma unroll
+          for (int k = 0; k < G::EPC; ++k) pd[p] = fma(g[c * G::EPC + k], (double)f[k], pd[p]);
+        }
+      }
+      // over the row's four lanes: two passes exchange halves (lane bit 1),
+      // then one sum (bit 0); a single pass is summed over both bits
+      double dot;
+      if constexpr (G::NP == 2) {
+        const bool up = (ch & 2) != 0;
+        dot = up ? pd[1] : pd[0];
+        dot += dpp_f64<DPP_XOR2>(up ? pd[0] : pd[1]);
+      } else {
+        static_assert(G::NP == 1, "one or two passes");
+        dot = pd[0] + dpp_f64<DPP_XOR2>(pd[0]);
+      }
+      dot += dpp_f64<DPP_XOR1>(dot);
+      const Nbr n = W.nbr[0][r0 + pass * G::RPP + rsub];
+      const bool real = n.slot >= 0;
+      const float u = 1.0f - __uint_as_float(n.dbits) * 0.125f;
+      const double a = real ? -2.0 * (double)(u * u * u) * dot : 0.0;
+      if constexpr (TH) {
+        const float u2 = u * u;
+        dls += real ? (double)(u2 * u2) * dot : 0.0;
       }
 #pragma unroll
-      for (int p = 0; p < G::NP; ++p) {
-        const int j = r0 + p * G::RPP + rsub;
-        float f[G::EPC];
-        unpack16<DT, G::EPC>(v[p], f);
-        // <G, v_j>: this lane's chunk, then a sum over the LPR lanes of the row,
-        // in fp64 (fp32 x fp32 products are exact there).  Next to a lattice
-        // point one term carries all of dq (and behind the activation layer
-        // dL/ds is sum_j w_j <G, v_j>), so a cancelling fp32 dot product would
-        // become the relative error of the whole gradient.
-        double pd64 = 0.0;
-#pragma unroll
-        for (int e = 0; e < G::EPC; ++e) pd64 = fma((double)g[e], (double)f[e], pd64);
-#pragma unroll
-        for (int mask = 1; mask < G::LPR; mask <<= 1) pd64 += __shfl_xor(pd64, mask);
-        if (sl[p] >= 0) {
-          const Nbr n = W.nbr[0][j];
-          const float u = 1.0f - __uint_as_float(n.dbits) * 0.125f;
-          const double a = -2.0 * (double)(u * u * u) * pd64;
-          if constexpr (TH) {
-            const float u2 = u * u;
-            dls = fma((double)(u2 * u2), pd64, dls);
-          }
-#pragma unroll
-          for (int k = 0; k < ICOORD; ++k) {
-            const int i = ch + k * G::LPR;
-            if (i < 8) {
-              const uint32_t ab = __builtin_amdgcn_perm(n.hi, n.lo, lsel[k]);
-              dq[k] = fma(a, (double)lds_f32(T.et, ab + 256u * i), dq[k]);
-            }
-          }
-        }
+      for (int k = 0; k < IC; ++k) {
+        const uint32_t ab = __builtin_amdgcn_perm(n.hi, n.lo, lsel[k]);
+        // (padding entries carry no candidate: any table entry, times zero)
+        dq[k] = fma(a, (double)lds_f32(T.et, (real ? ab : 0u) + 256u * (e * IC + k)), dq[k]);
       }
     }  // chunks of R rows
   }
+  // over the rows (lane bits 5 .. log2(LE)); bits 5 and 4 halve the
+  // coordinates per lane as long as there are two
+  int i = e * IC;
 #pragma unroll
-  for (int mask = G::LPR; mask < WAVE; mask <<= 1) {
-#pragma unroll
-    for (int k = 0; k < ICOORD; ++k) dq[k] += __shfl_xor(dq[k], mask);
-    if constexpr (TH) dls += __shfl_xor(dls, mask);
+  for (int k = 0; k < IC / 2; ++k) dq[k] = add_halves_f64<32>(dq[k], dq[k + IC / 2]);
+  i += (lane & 32) ? IC / 2 : 0;
+  if constexpr (IC == 4) {
+    dq[0] = add_halves_f64<16>(dq[0], dq[1]);
+    i += (lane & 16) ? 1 : 0;
+  } else {
+    dq[0] = add_halves_f64<16>(dq[0], dq[0]);
   }
-  // every lane of column ch now holds the sums; lane (rsub, ch) with rsub <
-  // ICOORD writes coordinate ch + rsub*LPR, so the coordinates' epilogues run
-  // side by side rather than one after another
-  if (rsub < ICOORD) {
-    double dqk = dq[0];
+  dq[0] = sum_row_f64<LE>(dq[0]);
+  if constexpr (TH) {
+    dls = add_halves_f64<32>(dls, dls);
+    dls = add_halves_f64<16>(dls, dls);
+    dls = sum_row_f64<LE>(dls);
+  }
+  // one lane per coordinate writes it
+  if ((lane & (IC == 4 ? 14 : 28)) == 0) {
+    const double dqk = dq[0];
+    if constexpr (!TH) {
+      gq[l * 8 + i] = (float)dqk;
+    } else {
+      double ci = P.cK[0];
 #pragma unroll
-    for (int k = 1; k < ICOORD; ++k) dqk = rsub == k ? dq[k] : dqk;
-    const int i = ch + rsub * G::LPR;
-    if (i < 8) {
-      if constexpr (!TH) {
-        gq[l * 8 + i] = (float)dqk;
-      } else {
-        double ci = P.cK[0];
-#pragma unroll
-        for (int e = 1; e < 8; ++e) ci = i == e ? P.cK[e] : ci;
-        const double sc = F.s;
-        double ga = 0.0, gb = 0.0;
-        if (sc > 0.0) {
-          const float2 ab = *reinterpret_cast<const float2*>(zin + l * 16 + 2 * i);
-          const double a = ab.x, b = ab.y;
-          const double r2 = a * a + b * b;
-          const double ir2 = 1.0 / r2, ir3 = ir2 / sqrt(r2);  // 1/r^2, 1/r^3
-          const double ds = dls * sc * sc, dqs = dqk * sc * ci;
-          ga = ds * a * ir3 - dqs * b * ir2;
-          gb = ds * b * ir3 + dqs * a * ir2;
-        }
-        *reinterpret_cast<float2*>(gq + l * 16 + 2 * i) = make_float2((float)ga, (float)gb);
+      for (int k = 1; k < 8; ++k) ci = i == k ? P.cK[k] : ci;
+      const double sc = F.s;
+      double ga = 0.0, gb = 0.0;
+      if (sc > 0.0) {
+        const float2 ab = *reinterpret_cast<const float2*>(zin + l * 16 + 2 * i);
+        const double a = ab.x, b = ab.y;
+        const double r2 = a * a + b * b;
+        const double ir2 = 1.0 / r2, ir3 = ir2 / sqrt(r2);  // 1/r^2, 1/r^3
+        const double ds = dls * sc * sc, dqs = dqk * sc * ci;
+        ga = ds * a * ir3 - dqs * b * ir2;
+        gb = ds * b * ir3 + dqs * a * ir2;
       }
+      *reinterpret_cast<float2*>(gq + l * 16 + 2 * i) = make_float2((float)ga, (float)gb);
     }
   }
 }

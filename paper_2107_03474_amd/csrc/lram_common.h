@@ -160,6 +160,52 @@ __device__ __forceinline__ void sink_prefetch(const uint32_t (&v)[NP], bool neve
   if (never && x == 0x7FC00001u) dst[0] = 0.0f;
 }
 
+// Lane exchanges without LDS.  DPP controls: the lane with the last (last but
+// one) index bit flipped, and rotations inside each row of 16 lanes.
+constexpr int DPP_XOR1 = 0xB1;   // quad_perm [1,0,3,2]
+constexpr int DPP_XOR2 = 0x4E;   // quad_perm [2,3,0,1]
+constexpr int DPP_ROR4 = 0x124;  // row_ror:4
+constexpr int DPP_ROR8 = 0x128;  // row_ror:8
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+// MASK = 32 or 16: lanes whose index has that bit clear get a summed over the
+// pair of lanes that differ in it, the others b.
+template <int MASK>
+__device__ __forceinline__ double add_halves_f64(double a, double b) {
+  static_assert(MASK == 32 || MASK == 16, "permlane swaps exchange halves or rows");
+  const uint64_t ab = __builtin_bit_cast(uint64_t, a), bb = __builtin_bit_cast(uint64_t, b);
+  uint64_t x, y;
+  if constexpr (MASK == 32) {
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)ab, (uint32_t)bb, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(ab >> 32), (uint32_t)(bb >> 32), false, false);
+    x = (uint64_t)lo[0] | ((uint64_t)hi[0] << 32);
+    y = (uint64_t)lo[1] | ((uint64_t)hi[1] << 32);
+  } else {
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)ab, (uint32_t)bb, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(ab >> 32), (uint32_t)(bb >> 32), false, false);
+    x = (uint64_t)lo[0] | ((uint64_t)hi[0] << 32);
+    y = (uint64_t)lo[1] | ((uint64_t)hi[1] << 32);
+  }
+  return __builtin_bit_cast(double, x) + __builtin_bit_cast(double, y);
+}
+
+// Sum over the lanes of a row of 16 whose index agrees modulo STRIDE (2 or 4).
+template <int STRIDE>
+__device__ __forceinline__ double sum_row_f64(double x) {
+  static_assert(STRIDE == 2 || STRIDE == 4, "lanes per group");
+  x += dpp_f64<DPP_ROR8>(x);
+  x += dpp_f64<DPP_ROR4>(x);
+  if constexpr (STRIDE == 2) x += dpp_f64<DPP_XOR2>(x);
+  return x;
+}
+
 // Orders LDS traffic between lanes of one wave: the wave's LDS operations
 // execute in issue order, so a compiler barrier is enough.
 __device__ __forceinline__ void wave_lds_sync() {

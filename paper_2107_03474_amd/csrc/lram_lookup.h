@@ -67,16 +67,18 @@ __global__ void __launch_bounds__(THREADS) k_neighbors(const float* __restrict__
   }
 }
 
-// Row geometry of the backward's table reads for chunks of R rows.
+// Row geometry of the backward's table reads for chunks of R rows: four lanes
+// to a row, 16 bytes each, NC loads per row (the four lanes cover 64 bytes).
 template <int DT, int M, int R = NB>
 struct RowGeom {
   static constexpr int ES = DT == LRAM_F32 ? 4 : 2;      // table element bytes
   static constexpr int RB = M * ES;                       // row bytes
-  static constexpr int LPR = RB / 16;                     // lanes per row (16 B each)
+  static constexpr int LPR = 4;                           // lanes per row
+  static constexpr int NC = RB / (16 * LPR);              // 16-byte chunks per lane and row
   static constexpr int RPP = WAVE / LPR;                  // rows per pass
   static constexpr int NP = R / RPP;                      // passes
   static constexpr int EPC = 16 / ES;                     // elements per 16-byte chunk
-  static_assert(RB % 16 == 0 && LPR <= WAVE && R % RPP == 0, "row geometry");
+  static_assert(RB % (16 * LPR) == 0 && R % RPP == 0 && LPR % NP == 0, "row geometry");
 };
 
 // Rows handled together by the gathers of a list of KS neighbours.
