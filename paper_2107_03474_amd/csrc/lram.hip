@@ -753,10 +753,9 @@ int lram_access_stats(const float* hist, int64_t N, double* out, void* stream) {
   if (N <= 0 || !hist || !out || misaligned4(hist) || (reinterpret_cast<uintptr_t>(out) & 7)) return LRAM_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(WAVE), 0, s, out, 4, 0.0);
-  const int64_t blocks = (N + THREADS - 1) / THREADS;
-  hipLaunchKernelGGL(k_access_reduce, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(THREADS), 0, s, hist,
-                     N, out);
-  hipLaunchKernelGGL(k_access_finalize, dim3(1), dim3(WAVE), 0, s, out, N);
+  const int64_t blocks = (N + STATS_THREADS - 1) / STATS_THREADS;
+  hipLaunchKernelGGL(k_access_reduce, dim3((unsigned)(blocks < STATS_BLOCKS ? blocks : STATS_BLOCKS)),
+                     dim3(STATS_THREADS), 0, s, hist, N, out);
   return launched();
 }
 

@@ -52,6 +52,25 @@ def test_access_stats(K):
     np.testing.assert_allclose(st["kl"], kl, rtol=1e-6)
 
 
+@pytest.mark.parametrize("N,offset", [(1, 0), (3, 1), (1023, 0), (1025, 1), (262145, 0), (1048579, 3), (2097152, 0)])
+def test_access_stats_sizes(N, offset):
+    """One value, remainders of the 16-byte loads, unaligned arrays, one to many workgroups: fp64 sums of at most
+    2^21 terms, so 1e-12 relative (2^21 * 2^-53 = 2.3e-10 is the worst case of one serial sum; the partial sums of
+    a workgroup are at most 2^13 long)."""
+    rng = np.random.default_rng(N)
+    h = np.where(rng.random(N) < 0.3, 0.0, rng.exponential(1.0, N)).astype(np.float32)
+    h[0] = 0.5
+    buf = torch.zeros(N + offset, device=DEV)
+    buf[offset:] = torch.from_numpy(h)
+    st = lram.access_stats(buf[offset:])
+    x = h.astype(np.float64)
+    H, pos = x.sum(), x[x > 0]
+    kl = np.log(N) + (pos * np.log(pos)).sum() / H - np.log(H)
+    assert st["count"] == pos.size and st["used"] == pos.size / N
+    np.testing.assert_allclose(st["total"], H, rtol=1e-12)
+    np.testing.assert_allclose(st["kl"], kl, rtol=1e-12, atol=1e-11)
+
+
 def test_access_stats_lattice_points_uniform():
     K = (2, 2, 2, 4, 2, 2, 2, 2)
     pts = []
