@@ -15,7 +15,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(BUILD, "liblram.so")
 SOURCES = [os.path.join(CSRC, "lram.hip")]
 DEPS = SOURCES + sorted(glob.glob(os.path.join(CSRC, "*.h"))) + [
-    os.path.join(CSRC, "e8_candidates.inc"), os.path.join(ROOT, "include", "lram.h")]
+    os.path.join(CSRC, "e8_candidates.inc"), os.path.join(CSRC, "e8_tile.inc"), os.path.join(ROOT, "include", "lram.h")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

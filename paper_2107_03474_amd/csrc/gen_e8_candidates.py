@@ -26,6 +26,15 @@ Output (``e8_candidates.inc``):
     error outside F, or whose fp32 distance rounds below 8, can see them; the
     kernel scans them only on that rare path.
 The gap to the next distance level is checked to be large.
+
+Output (``e8_tile.inc``): the strict points in the order of the tile search,
+15 blocks of 16 rows (a row of a matrix product each; indices into the strict
+list).  How often each point is among the 32 closest is sampled over uniform
+queries: ten points always are, 67 others ever.  Blocks 0-3 hold the 64 points
+that are next most often, block 4 the ten in its rows 0-9 and six of the
+rest, blocks 5-14 the rest (rows repeated to fill the last of either norm).
+The search checks its result against every row, so the sample decides only how
+often a query takes the general path.
 """
 from __future__ import annotations
 
@@ -37,6 +46,7 @@ import numpy as np
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 OUT = os.path.join(HERE, "e8_candidates.inc")
+OUT_TILE = os.path.join(HERE, "e8_tile.inc")
 
 
 FAST = 192  # three candidates per lane of a 64-lane wave
@@ -127,6 +137,64 @@ def exact_dist2(p, S) -> Fraction:
     return sum((p[k] - z[k]) ** 2 for k in range(8))
 
 
+def sample_region(n: int, seed: int = 0) -> np.ndarray:
+    """n points of F: uniform queries, reduced by their closest point and the signed permutation."""
+    x = np.random.default_rng(seed).random((n, 8)) * 16.0
+
+    def d8(y):
+        r = np.rint(y)
+        d = y - r
+        odd = np.nonzero(r.sum(1).astype(np.int64) & 1)[0]
+        j = np.abs(d).argmax(1)[odd]
+        r[odd, j] += np.where(d[odd, j] > 0, 1, -1)
+        return r
+
+    a, b = 2 * d8(x / 2), 2 * d8((x - 1) / 2) + 1
+    y = x - np.where((((x - a) ** 2).sum(1) <= ((x - b) ** 2).sum(1))[:, None], a, b)
+    z = -np.sort(-np.abs(y), axis=1)
+    z[:, 7] *= np.where((y < 0).sum(1) & 1, -1.0, 1.0)
+    return z
+
+
+def tile_order(strict: np.ndarray, n: int = 200000) -> np.ndarray:
+    """Strict-list indices of the tile search's 15 x 16 rows."""
+    z = sample_region(n)
+    n2 = (strict ** 2).sum(1)
+    d = (z ** 2).sum(1)[:, None] + n2[None] - 2.0 * z @ strict.T
+    freq = np.bincount(np.argsort(d, axis=1, kind="stable")[:, :32].ravel(), minlength=len(strict))
+    order = np.argsort(-freq, kind="stable")
+    always, var, rest = order[:10], order[10:74], order[74:]
+    assert n2[always].max() <= 8 and always[0] == 0
+    small = [i for i in var if n2[i] == 8]
+    large = [i for i in var if n2[i] == 16]
+    assert len(small) >= 48
+    rows = np.zeros((15, 16), np.int64)
+    # blocks 0-2 of norm 8 throughout; block 3 the others of norm 8, then norm 16;
+    # inside a block neighbours in frequency go to different groups of four
+    # rows (a lane of the search holds four rows of a block)
+    def deal(block):
+        out = np.zeros(16, np.int64)
+        for k, i in enumerate(block):
+            turn, g = divmod(k, 4)
+            out[4 * (g if turn % 2 == 0 else 3 - g) + turn] = i
+        return out
+
+    for b in range(3):
+        rows[b] = deal(small[b::3][:16])
+    used = set(rows[:3].ravel())
+    rows[3] = deal([i for i in small if i not in used] + large)
+    r8 = [i for i in rest if n2[i] == 8]
+    r16 = [i for i in rest if n2[i] == 16]
+    rows[4] = np.concatenate([always, r8[:6]])
+    r8 = r8[6:]
+    r8 += [r8[-1]] * (80 - len(r8))
+    r16 += [r16[-1]] * (80 - len(r16))
+    rows[5:10] = np.reshape(r8, (5, 16))
+    rows[10:15] = np.reshape(r16, (5, 16))
+    assert set(rows.ravel()) == set(range(len(strict)))
+    return rows
+
+
 def main(write: bool = True) -> dict:
     # |z| <= 2 on F (covering radius), so a point within sqrt 8 of F has |p|^2 < (2 + sqrt 8)^2 < 24;
     # norm 24 is included to measure the gap above the boundary level.
@@ -176,6 +244,14 @@ def main(write: bool = True) -> dict:
                 for v in lst:
                     f.write("  {%s}, \\\n" % ", ".join("%2d" % int(c) for c in v))
                 f.write("}\n")
+        rows = tile_order(np.array(strict))
+        with open(OUT_TILE, "w") as f:
+            f.write("// Generated by gen_e8_candidates.py -- do not edit.\n")
+            f.write("// Rows of the tile search: 15 blocks of 16 indices into E8_STRICT_INIT.\n")
+            f.write("#pragma once\n#define E8_TILE_BLOCKS 15\n#define E8_TILE_INIT { \\\n")
+            for r in rows:
+                f.write("  {%s}, \\\n" % ", ".join("%3d" % i for i in r))
+            f.write("}\n")
     return info
 
 

@@ -26,6 +26,7 @@
 // by HBM and by memory-side atomics, not a contraction.
 
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cmath>
 #include <stdint.h>
 
@@ -34,6 +35,7 @@
 
 #include "../../include/lram.h"
 #include "e8_candidates.inc"
+#include "e8_tile.inc"
 
 #include "lram_common.h"
 #include "lram_search.h"
@@ -54,6 +56,22 @@ thread_local int g_last_hip_error = 0;
 // vectors, the element size for the per-element arrays.
 bool misaligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
 bool misaligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3) != 0; }
+
+// Lookups per wave.  A wave that searches tiles spends a tile's cost whatever
+// the tile holds (about 900 instructions; 120 more for each pair of lookups), so
+// small batches put two lookups on a wave, more once every SIMD has two
+// waves, up to a whole tile from 32,768 lookups on.  Forward, lookups per
+// wave 1 / 2 / 4 / 8 / 16 / 32 / 64: 4,096 lookups 16.2 / 12.1 / 12.0 / 13.8 / 17 / - / - us;
+// 16,384 lookups 48 / 28 / 21 / 19.9 / 22 / 37 / -; 65,536 - / 95 / 67 / 55 / 51 / 57 / 87;
+// 262,144 (2^20 rows, m = 64 fp32) - / - / 352 / 309 / 304 / 305 / 320.  The general search
+// (tile = false) costs the same for every lookup: one each until every SIMD
+// has four waves, then up to 64.
+int32_t lookups_per_wave(int64_t L, bool tile) {
+  const int64_t simds = 256 * 4;
+  if (!tile) return (int32_t)std::min<int64_t>(std::max<int64_t>((L + 4 * simds - 1) / (4 * simds), 1), WAVE);
+  const int64_t lpw = (L + 2 * simds - 1) / (2 * simds);
+  return (int32_t)std::min<int64_t>(std::max<int64_t>((lpw + 1) / 2 * 2, 2), L < (int64_t(1) << 19) ? TILE : 2 * TILE);
+}
 
 int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t* L, Params* P) {
   if (B < 0 || H < 0 || !K) return LRAM_EINVAL;
@@ -79,11 +97,7 @@ int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t
   }
   P->N = (uint32_t)N;
   P->L = *L;
-  // lookups per wave: up to 64, fewer for small batches so that every CU gets
-  // work (about 16 waves per CU for 256 CUs)
-  const int64_t target_waves = 256 * 16;
-  int64_t lpw = (*L + target_waves - 1) / target_waves;
-  P->lpw = (int32_t)(lpw < 1 ? 1 : (lpw > WAVE ? WAVE : lpw));
+  P->lpw = lookups_per_wave(*L, true);
   return LRAM_OK;
 }
 
@@ -347,8 +361,10 @@ int build_order(const float* q, const Params& P, const OrderWs& o, hipStream_t s
 // device-side choice (null: always scatter); perm an order to visit the
 // lookups in (null: index order); saved the forward's lists (or off).
 template <int DT, int M, bool TH, int KS>
-void launch_atomic(const float* q, const Params& P, const void* table, const float* g, float* gt, float* gq,
+void launch_atomic(const float* q, const Params& Pq, const void* table, const float* g, float* gt, float* gq,
                    const uint32_t* gate, const uint32_t* perm, NbrList saved, hipStream_t s) {
+  Params P = Pq;
+  P.lpw = lookups_per_wave(P.L, KS == NB);
   const dim3 grid(grid_for(P)), b(THREADS);
   uint32_t* const nk = nullptr;
   uint2* const nv = nullptr;
@@ -477,7 +493,9 @@ int list_width(int32_t k) {
 
 template <int DT, int M>
 struct FwdKLaunch {
-  static int go(const float* q, const Params& P, const void* table, void* out, int width, hipStream_t s) {
+  static int go(const float* q, const Params& Pq, const void* table, void* out, int width, hipStream_t s) {
+    Params P = Pq;
+    P.lpw = lookups_per_wave(P.L, width == NB);
     const dim3 g(grid_for(P)), b(THREADS);
     switch (width) {
       case 16: hipLaunchKernelGGL((k_forward_k<DT, M, 16>), g, b, 0, s, q, P, table, out); break;
@@ -839,6 +857,7 @@ int lram_neighbors_k(const float* q, int64_t B, int64_t H, const int32_t K[8], i
   if (rc) return rc;
   if (L == 0) return LRAM_OK;
   if (!slot || !w || misaligned4(slot) || misaligned4(w) || misaligned4(d2)) return LRAM_EINVAL;
+  P.lpw = lookups_per_wave(L, width == NB);
   const dim3 g(grid_for(P)), b(THREADS);
   hipStream_t s = (hipStream_t)stream;
   switch (width) {

@@ -18,9 +18,10 @@ __device__ __forceinline__ bool merge_chosen(uint32_t shared, int64_t L) { retur
 
 // Value-gradient scatter of one lookup: M consecutive lanes own one gradient
 // row, so each atomic instruction covers 64/M whole rows.
-template <int M, int KS>
-__device__ __forceinline__ void scatter_atomic(const WaveLds<KS>& W, int count, const float* __restrict__ gout,
-                                               int64_t l, float* __restrict__ gtab, int lane) {
+template <int M, int KS, int NBUF, int WBUF>
+__device__ __forceinline__ void scatter_atomic(const WaveLds<KS, NBUF, WBUF>& W, int buf, int count,
+                                               const float* __restrict__ gout, int64_t l, float* __restrict__ gtab,
+                                               int lane) {
   constexpr int RA = WAVE / M;
   const int col = lane % M;
   const float gc = gout[(size_t)l * M + col];
@@ -28,8 +29,8 @@ __device__ __forceinline__ void scatter_atomic(const WaveLds<KS>& W, int count, 
 #pragma unroll 4
   for (int k = 0; k < kend; ++k) {
     const int j = k * RA + lane / M;
-    const int32_t s = W.nbr[0][j].slot;
-    if (s >= 0) unsafeAtomicAdd(gtab + (size_t)s * M + col, W.wgt[0][j] * gc);
+    const int32_t s = W.nbr[buf][j].slot;
+    if (s >= 0) unsafeAtomicAdd(gtab + (size_t)s * M + col, W.wgt[buf][j] * gc);
   }
 }
 
@@ -58,9 +59,9 @@ __device__ __forceinline__ void scatter_atomic(const WaveLds<KS>& W, int count, 
 // 2^20 rows): merged backward behind the activation layer 1,606 -> 1,368 us;
 // untruncated backward of 29,997 lookups (m = 32 fp32) 322 -> 247 us; 4,096
 // lookups at K = 4 21.3 -> 19.6 us.
-template <int DT, int M, bool TH, int KS>
-__device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS>& W, const Tables& T, int count,
-                                           const char* __restrict__ tb, const float* __restrict__ gout, int64_t l,
+template <int DT, int M, bool TH, int KS, int NBUF, int WBUF>
+__device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS, NBUF, WBUF>& W, int buf, const Tables& T,
+                                           int count, const char* __restrict__ tb, const float* __restrict__ gout, int64_t l,
                                            int lane, float* __restrict__ gq, const float* __restrict__ zin,
                                            const Params& P) {
   constexpr int R = chunk_rows<KS>();  // rows per chunk of the row loop
@@ -95,7 +96,7 @@ __device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS>& W,
       uint4 v[G::NP][G::NC];
 #pragma unroll
       for (int p = 0; p < G::NP; ++p) {
-        const int32_t s = max(W.nbr[0][r0 + p * G::RPP + rsub].slot, 0);
+        const int32_t s = max(W.nbr[buf][r0 + p * G::RPP + rsub].slot, 0);
         const char* src = tb + (size_t)s * G::RB + ch * 16;
 #pragma unroll
         for (int c = 0; c < G::NC; ++c) v[p][c] = *reinterpret_cast<const uint4*>(src + c * (G::LPR * 16));
@@ -124,7 +125,7 @@ __device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS>& W,
         dot = pd[0] + dpp_f64<DPP_XOR2>(pd[0]);
       }
       dot += dpp_f64<DPP_XOR1>(dot);
-      const Nbr n = W.nbr[0][r0 + pass * G::RPP + rsub];
+      const Nbr n = W.nbr[buf][r0 + pass * G::RPP + rsub];
       const bool real = n.slot >= 0;
       const float u = 1.0f - __uint_as_float(n.dbits) * 0.125f;
       const double a = real ? -2.0 * (double)(u * u * u) * dot : 0.0;
@@ -192,7 +193,7 @@ __device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS>& W,
 // ORD: visit the lookups in the order perm (as k_forward).
 // SAVED: the forward's lists (NbrList saved) replace the search.
 template <int DT, int M, bool EMIT, bool TH, int KS = NB, bool ORD = false, bool SAVED = false>
-__global__ void __launch_bounds__(THREADS) k_backward(const float* __restrict__ q, Params P,
+__global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH ? 3 : 4) k_backward(const float* __restrict__ q, Params P,
                                                       const void* __restrict__ table,
                                                       const float* __restrict__ gout, float* __restrict__ gtab,
                                                       float* __restrict__ gq, uint32_t* __restrict__ pair_key,
@@ -200,37 +201,64 @@ __global__ void __launch_bounds__(THREADS) k_backward(const float* __restrict__ 
                                                       const uint32_t* __restrict__ perm, NbrList saved) {
   static_assert(!EMIT || KS == NB, "the sorted scatter takes lists of 32");
   static_assert(!(SAVED || ORD) || (KS == NB && !TH), "orders and saved lists serve the k = 32 lookup");
-  __shared__ SearchLds<WAVE, KS> S;
+  __shared__ SearchLds<KS> S;
   if (gate && merge_chosen(*gate, P.L)) return;
   WaveCtx c;
-  if (!wave_ctx(P, c, ORD)) return;
+  wave_ctx(P, c, ORD);
   const int lane = c.lane;
-  Search<KS> srch(P, S.tab, S.wave[c.wave], c.wave, lane);
-  WaveLds<KS>& W = S.wave[c.wave];
-  Frame* FR = S.frames[c.wave];
-  uint32_t my_l = 0;
-  if constexpr (ORD)
-    my_l = phase_a_perm<TH>(q, perm, c.base, c.nl, P, FR, lane);
-  else
-    phase_a<TH>(q, c.base, c.nl, P, FR, lane);
   const char* tb = reinterpret_cast<const char*>(table);
-  for (int t = 0; t < c.nl; ++t) {
-    const Frame& F = FR[t];
-    const Sel sel = read_sel(F);
-    const int64_t l = ORD ? (int64_t)(uint32_t)__builtin_amdgcn_readlane(my_l, t) : c.base + t;
-    int count;
-    if constexpr (SAVED)
-      count = srch.load(F, sel, 0, saved, l, P.N);
-    else
-      count = srch.run(F, sel, 0);
-    if (!EMIT && gtab && count > 0) scatter_atomic<M, KS>(W, count, gout, l, gtab, lane);
-    if (gq && (!ORD || l < P.L)) grad_query<DT, M, TH, KS>(F, W, S.tab, count, tb, gout, l, lane, gq, q, P);
-    if (EMIT && gtab && lane < NB && (!ORD || l < P.L)) {
-      const int32_t s = W.nbr[0][lane].slot;
+  WaveLds<KS, (KS == NB ? 2 : 1)>& W = S.wave[c.wave];
+  // scatter and query gradient of list buf, which is lookup l's (ok: inside the batch)
+  auto finish = [&](const Frame& F, int buf, int count, int64_t l, bool ok) {
+    if (!EMIT && gtab && count > 0) scatter_atomic<M, KS>(W, buf, count, gout, l, gtab, lane);
+    if (gq && ok) grad_query<DT, M, TH, KS>(F, W, buf, S.tab, count, tb, gout, l, lane, gq, q, P);
+    if (EMIT && gtab && lane < NB && ok) {
+      const int32_t s = W.nbr[buf][lane].slot;
       pair_key[l * NB + lane] = s >= 0 ? (uint32_t)s : P.N;
-      pair_val[l * NB + lane] = make_uint2((uint32_t)l, __float_as_uint(W.wgt[0][lane]));
+      pair_val[l * NB + lane] = make_uint2((uint32_t)l, __float_as_uint(W.wgt[buf][lane]));
     }
-    wave_lds_sync();
+  };
+  if constexpr (KS == NB) {
+    TileInput<TH, ORD> in(q, perm, c.base, c.nl, P, lane);
+    TileSearch<TH, 2> ts(P, S, c.wave, lane);
+    for (int t0 = 0; t0 < c.nl; t0 += TILE) {
+      const int nt = min(TILE, c.nl - t0);
+      ts.template frames<!SAVED>(in.v, in.have, nt);
+      in.advance(t0, P);
+      if constexpr (SAVED) {
+        for (int t = 0; t < nt; ++t) {
+          bool ok;
+          const int64_t l = in.lookup(t0, t, P, ok);
+          const int count = ts.one.load(ts.FR[t], read_sel(ts.FR[t]), 0, saved, l, P.N);
+          finish(ts.FR[t], 0, count, l, ok);
+          wave_lds_sync();
+        }
+      } else {
+        for (int p = 0; 2 * p < nt; ++p) {
+          ts.pair(p, 0);
+          bool ok;
+          const int64_t l0 = in.lookup(t0, 2 * p, P, ok);
+          finish(ts.FR[2 * p], 0, ts.count0, l0, ok);
+          const int64_t l1 = in.lookup(t0, 2 * p + 1, P, ok);
+          if (2 * p + 1 < nt) finish(ts.FR[2 * p + 1], 1, ts.count1, l1, ok);
+          wave_lds_sync();
+        }
+      }
+    }
+  } else {
+    static_assert(KS == NB || (!TH && !ORD && !SAVED && !EMIT), "other lists serve the plain lookup");
+    Search<KS> srch(P, S.tab, W, S.tile, c.wave, lane);
+    const QuadCtx<false> Q(P, lane);
+    Frame* FR = S.frames[c.wave];
+    for (int t0 = 0; t0 < c.nl; t0 += TILE) {
+      const int nt = min(TILE, c.nl - t0);
+      tile_frames(q, c.base + t0, nt, P, FR, Q, lane);
+      for (int t = 0; t < nt; ++t) {
+        const int count = srch.run(FR[t], read_sel(FR[t]), 0);
+        finish(FR[t], 0, count, c.base + t0 + t, true);
+        wave_lds_sync();
+      }
+    }
   }
 }
 

@@ -14,14 +14,14 @@ constexpr int THREADS = WAVE * WAVES;
 constexpr int NS_STRICT = (E8_NSTRICT + WAVE - 1) / WAVE;      // 4 candidate slots per lane
 constexpr int NS_BOUND = (E8_NBOUNDARY + WAVE - 1) / WAVE;     // 3
 constexpr int NS_ALL = NS_STRICT + NS_BOUND;
-constexpr int NS_FAST = E8_FAST / WAVE;                          // 3: the fast set's slots per lane
+constexpr int NS_FAST = E8_FAST / WAVE;                          // 3: the fast set's slots per lane (lists of 16)
 constexpr int NS_FAST2 = E8_FAST2 / WAVE;                        // 2: its first tier
 static_assert(E8_FAST % WAVE == 0 && NS_FAST < NS_STRICT, "the fast candidate set fills whole slots");
 static_assert(E8_FAST2 % WAVE == 0 && NS_FAST2 < NS_FAST, "the first tier fills whole slots");
 constexpr int CMIN = E8_CAND_MIN;
 constexpr int NV = E8_CAND_MAX - E8_CAND_MIN + 1;
 static_assert(NV == 8, "each per-query table row holds the 8 possible candidate coordinate values");
-static_assert(WAVES <= 4, "the wave index is folded into byte-sized LDS offsets");
+static_assert(WAVES <= 4, "the wave index and the list of a pair are folded into byte-sized LDS offsets");
 constexpr int KMAX = 8192;  // per-coordinate torus side bound: lattice coordinates fit in int16
 constexpr int XCDS = 8;  // accelerator complex dies of an MI355X
 constexpr int64_t LMAX = (int64_t(1) << 31) - 1;  // lookups per call
@@ -52,9 +52,6 @@ constexpr uint32_t KEY_SUSPECT = 0x40FFF7CFu;  // 7.999f
 constexpr uint32_t KEY_FAST = __builtin_bit_cast(uint32_t, E8_FAST_BOUND - 0.0078125f);
 constexpr uint32_t KEY_FAST2 = __builtin_bit_cast(uint32_t, E8_FAST2_BOUND - 0.0078125f);
 
-__constant__ signed char c_strict[E8_NSTRICT][8] = E8_STRICT_INIT;
-__constant__ signed char c_boundary[E8_NBOUNDARY][8] = E8_BOUNDARY_INIT;
-
 struct Params {
   int32_t K[8];
   uint32_t S[8];     // mixed-radix strides of the location map, S_7 = 1
@@ -65,14 +62,20 @@ struct Params {
   double cK[8];      // K_i / (2 pi): torus coordinate per radian of arg z_i (activation layer)
 };
 
-// Per-lookup frame written by phase A (96 bytes).
+// Lookups that a wave searches together: phase A spreads each over four lanes,
+// the tile selection over four lanes of a matrix product's result.
+constexpr int TILE = 16;
+
+// Per-lookup frame written by phase A (112 bytes).
 struct alignas(16) Frame {
-  float x[8];         // Lambda-scale query, wrapped
+  uint2 rec[8];       // original coordinate i: bits of the wrapped Lambda-scale query x_i; 2 c_i + (s'_i = -1)
+                      // with c the closest lattice point and s' the sign flips
   uint32_t sel[8];    // v_perm selector of original coordinate i: byte r_i (its F position) into byte 0
-  int16_t c[8];       // closest lattice point
-  uint32_t misc;      // bits 0-7: sign flips s'_i = -1; bit 8: query finite
+                      // (during the tile selection: bits of -z_r / 2, z the query in F)
+  uint32_t valid;     // query finite
   float s;            // output scale: 1, or (sum 1/|z_i|)^-1 behind the activation layer
-  uint32_t pad[2];
+  float r2;           // |z|^2
+  uint32_t pad;
 };
 
 // A selected neighbour as handed from the search to the gather / scatter.
@@ -82,14 +85,18 @@ struct alignas(16) Nbr {
   int32_t slot;       // location, -1 for padding
 };
 
-// Per-wave search state for lists of KS neighbours, NBUF lists deep (the k =
-// 32 forward double-buffers them: lookup t+1 is searched while t is consumed).
-template <int KS, int NBUF = 1>
+// Per-wave search state for lists of KS neighbours: NBUF lists (two lookups are
+// finished at a time for k = 32), WBUF weight lists (the k = 32 forward keeps
+// the weights of the pair whose rows are in flight).
+template <int KS, int NBUF = 1, int WBUF = NBUF>
 struct alignas(16) WaveLds {
+  static constexpr int LISTS = NBUF;
   Nbr nbr[NBUF][KS];
-  float wgt[NBUF][KS];
-  uint32_t tie[tie_max<KS>()][2];
-  uint32_t hist[64];  // distance histogram of the selection, 64 buckets on [4, 8)
+  float wgt[WBUF][KS];
+  union {
+    uint32_t tie[tie_max<KS>()][2];
+    uint32_t hist[64];  // distance histogram of the selection, 64 buckets on [4, 8) (read before ties are listed)
+  };
 };
 
 // Neighbour lists saved by the forward for the backward (any pointer null: no
@@ -121,19 +128,35 @@ __device__ __forceinline__ void bytes_of(uint32_t code, uint32_t wbyte, uint32_t
   hi = (spread((code >> 12) & 0xFFFu) << 2) + wb;
 }
 
-// per-query tables, [coordinate i][wave w][value v] -> byte i*256 + w*64 + 4v
+// per-query tables, [coordinate i][wave w][list h of a pair][value v] -> byte
+// i*256 + w*64 + h*32 + 4v
 struct alignas(16) Tables {
   float qt[8 * 64];
   uint32_t st[8 * 64];
   float et[8 * 64];
 };
 
-// LDS of the search for FR lookups per wave and lists of KS neighbours.
-template <int FR, int KS = NB, int NBUF = 1>
+// Candidates of the closest 32 in the order of the tile search: 64 that are
+// often among them, the ten that always are, the other strict ones, the
+// boundary list; and each lookup of a tile's selected ones (CAND_NONE: padding).
+constexpr int TILE_VAR = 64;
+constexpr int TILE_ALWAYS = 10;
+constexpr int CANDS = E8_NSTRICT + E8_NBOUNDARY;
+constexpr uint32_t CAND_NONE = 0xFFFFu;
+template <int KS>
+struct alignas(16) TileLds {
+  uint32_t a[KS == NB ? E8_TILE_BLOCKS : 1][KS == NB ? WAVE : 4];  // operands of the distance product (two bf16)
+  uint2 cand[KS == NB ? CANDS + 1 : 2];                            // packed bytes
+  uint16_t idx[WAVES][KS == NB ? TILE : 1][KS == NB ? NB : 2];
+};
+
+// LDS of the search for lists of KS neighbours.
+template <int KS = NB, int NBUF = (KS == NB ? 2 : 1), int WBUF = NBUF>
 struct alignas(16) SearchLds {
   Tables tab;
-  WaveLds<KS, NBUF> wave[WAVES];
-  Frame frames[WAVES][FR];
+  WaveLds<KS, NBUF, WBUF> wave[WAVES];
+  Frame frames[WAVES][TILE];
+  TileLds<KS> tile;
 };
 
 __device__ __forceinline__ float lds_f32(const float* base, uint32_t byte_off) {
@@ -145,6 +168,15 @@ __device__ __forceinline__ uint32_t lds_u32(const uint32_t* base, uint32_t byte_
 
 __device__ __forceinline__ int prefix_count(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+}
+
+// The value itself, opaque to the optimiser: loads addressed through it stay
+// where they are written instead of being hoisted out of the lookup loop into
+// registers held throughout.
+template <typename T>
+__device__ __forceinline__ T opaque(T v) {
+  asm volatile("" : "+v"(v));
+  return v;
 }
 
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -167,6 +199,16 @@ constexpr int DPP_XOR2 = 0x4E;   // quad_perm [2,3,0,1]
 constexpr int DPP_ROR4 = 0x124;  // row_ror:4
 constexpr int DPP_ROR8 = 0x128;  // row_ror:8
 
+constexpr int DPP_XOR3 = 0x1B;   // quad_perm [3,2,1,0]
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float x) {
+  return __uint_as_float(dpp_u32<CTRL>(__float_as_uint(x)));
+}
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double x) {
   const uint64_t b = __builtin_bit_cast(uint64_t, x);
@@ -194,6 +236,18 @@ __device__ __forceinline__ double add_halves_f64(double a, double b) {
     y = (uint64_t)lo[1] | ((uint64_t)hi[1] << 32);
   }
   return __builtin_bit_cast(double, x) + __builtin_bit_cast(double, y);
+}
+
+template <int MASK>
+__device__ __forceinline__ float add_halves_f32(float a, float b) {
+  static_assert(MASK == 32 || MASK == 16, "permlane swaps exchange halves or rows");
+  const auto r = [&] {
+    if constexpr (MASK == 32)
+      return __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    else
+      return __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  }();
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // Sum over the lanes of a row of 16 whose index agrees modulo STRIDE (2 or 4).

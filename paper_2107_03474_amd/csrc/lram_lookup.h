@@ -19,51 +19,96 @@ struct WaveCtx {
 // xcd: take the workgroups' ranges XCD-contiguously (for lookups visited in a
 // locality order, so that neighbouring ranges share an L2).
 __device__ __forceinline__ bool wave_ctx(const Params P, WaveCtx& c, bool xcd = false) {
-  c.wave = threadIdx.x / WAVE;
+  c.wave = (int)uniform(threadIdx.x / WAVE);  // scalar: loop bounds and LDS bases stay out of vector registers
   c.lane = threadIdx.x % WAVE;
   const int64_t blk = xcd ? xcd_block() : (int64_t)blockIdx.x;
   c.base = (blk * WAVES + c.wave) * P.lpw;
-  if (c.base >= P.L) return false;
-  c.nl = (int)min<int64_t>(P.lpw, P.L - c.base);
-  return true;
+  c.nl = (int)max<int64_t>(0, min<int64_t>(P.lpw, P.L - c.base));
+  return c.nl > 0;
+}
+
+// Writes one list of a lookup (entries in LDS, count real ones) ordered by
+// (distance bits, location, lattice point); half: the lanes of one half wave
+// (32 entries), otherwise all lanes.
+template <int KS, int NBUF, int WBUF>
+__device__ __forceinline__ void store_list(const WaveLds<KS, NBUF, WBUF>& W, int buf, int wb, int first, int step,
+                                           int count, const Frame& F, const Sel& sel, int64_t l, int32_t* slot_out,
+                                           float* w_out, float* d2_out) {
+  for (int me_i = first; me_i < KS; me_i += step) {
+    const Nbr me = W.nbr[buf][me_i];
+    int rank = me_i;
+    if (me_i < count) {
+      // (distance bits, location) as one key; equal keys (the same location
+      // twice, which takes a torus side of 2) are ordered by the point itself
+      const uint64_t mk = (uint64_t)me.dbits << 32 | (uint32_t)me.slot;
+      rank = 0;
+      int same = 0;
+      for (int e = 0; e < count; ++e) {
+        const uint2 o = *reinterpret_cast<const uint2*>(&W.nbr[buf][e].dbits);
+        const uint64_t ok = (uint64_t)o.x << 32 | o.y;
+        rank += ok < mk ? 1 : 0;
+        same += ok == mk ? 1 : 0;
+      }
+      if (same > 1) {
+        const uint32_t lk = cand_liftkey(me.lo, me.hi, sel, F);
+        for (int e = 0; e < count; ++e) {
+          const Nbr o = W.nbr[buf][e];
+          if (o.dbits == me.dbits && o.slot == me.slot && e != me_i)
+            rank += cand_liftkey(o.lo, o.hi, sel, F) < lk ? 1 : 0;
+        }
+      }
+    }
+    slot_out[l * KS + rank] = me.slot;
+    w_out[l * KS + rank] = W.wgt[wb][me_i];
+    if (d2_out) d2_out[l * KS + rank] = __uint_as_float(me.dbits);
+  }
 }
 
 // Neighbour lists of width KS (NB = 32: Sec. 2.6; KALL: the whole support).
 template <int KS>
-__global__ void __launch_bounds__(THREADS) k_neighbors(const float* __restrict__ q, Params P,
+__global__ void __launch_bounds__(THREADS, 4) k_neighbors(const float* __restrict__ q, Params P,
                                                        int32_t* __restrict__ slot_out, float* __restrict__ w_out,
                                                        float* __restrict__ d2_out) {
-  __shared__ SearchLds<WAVE, KS> S;
+  __shared__ SearchLds<KS> S;
   WaveCtx c;
-  if (!wave_ctx(P, c)) return;
-  Search<KS> srch(P, S.tab, S.wave[c.wave], c.wave, c.lane);
-  WaveLds<KS>& W = S.wave[c.wave];
-  Frame* FR = S.frames[c.wave];
-  phase_a<false>(q, c.base, c.nl, P, FR, c.lane);
-  for (int t = 0; t < c.nl; ++t) {
-    const Frame& F = FR[t];
-    const Sel sel = read_sel(F);
-    const int count = srch.run(F, sel, 0);
-    const int64_t l = c.base + t;
-    for (int me_i = c.lane; me_i < KS; me_i += WAVE) {
-      // order the list by (distance bits, location, lattice point)
-      const Nbr me = W.nbr[0][me_i];
-      int rank = me_i;
-      if (me_i < count) {
-        const uint32_t mk = cand_liftkey(me.lo, me.hi, sel, F);
-        rank = 0;
-        for (int e = 0; e < count; ++e) {
-          const Nbr o = W.nbr[0][e];
-          bool less = o.dbits < me.dbits || (o.dbits == me.dbits && o.slot < me.slot);
-          if (o.dbits == me.dbits && o.slot == me.slot && e != me_i) less = cand_liftkey(o.lo, o.hi, sel, F) < mk;
-          rank += less ? 1 : 0;
-        }
+  if constexpr (KS == NB) {
+    wave_ctx(P, c);
+    TileInput<false, false> in(q, nullptr, c.base, c.nl, P, c.lane);
+    TileSearch<false, 2> ts(P, S, c.wave, c.lane);
+    for (int t0 = 0; t0 < c.nl; t0 += TILE) {
+      const int nt = min(TILE, c.nl - t0);
+      ts.frames(in.v, in.have, nt);
+      in.advance(t0, P);
+      for (int p = 0; 2 * p < nt; ++p) {
+        ts.pair(p, 0);
+        // a half wave orders each list of the pair
+        const int h = c.lane >> 5, t = 2 * p + h;
+        const Frame& F = ts.FR[t];
+        Sel sel;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sel.s[i] = F.sel[i];
+        if (t < nt)
+          store_list<NB, 2, 2>(ts.W, h, h, c.lane & 31, NB, h ? ts.count1 : ts.count0, F, sel, c.base + t0 + t, slot_out,
+                               w_out, d2_out);
+        wave_lds_sync();
       }
-      slot_out[l * KS + rank] = me.slot;
-      w_out[l * KS + rank] = W.wgt[0][me_i];
-      if (d2_out) d2_out[l * KS + rank] = __uint_as_float(me.dbits);
     }
-    wave_lds_sync();
+  } else {
+    if (!wave_ctx(P, c)) return;
+    Search<KS> srch(P, S.tab, S.wave[c.wave], S.tile, c.wave, c.lane);
+    const QuadCtx<false> Q(P, c.lane);
+    Frame* FR = S.frames[c.wave];
+    for (int t0 = 0; t0 < c.nl; t0 += TILE) {
+      const int nt = min(TILE, c.nl - t0);
+      tile_frames(q, c.base + t0, nt, P, FR, Q, c.lane);
+      for (int t = 0; t < nt; ++t) {
+        const Sel sel = read_sel(FR[t]);
+        const int count = srch.run(FR[t], sel, 0);
+        store_list<KS, 1, 1>(S.wave[c.wave], 0, 0, c.lane, WAVE, count, FR[t], sel, c.base + t0 + t, slot_out, w_out,
+                             d2_out);
+        wave_lds_sync();
+      }
+    }
   }
 }
 
@@ -100,100 +145,98 @@ __device__ __forceinline__ void unpack16(const uint4 v, float (&f)[EPC]) {
   }
 }
 
-// Gather geometry of the forward: each lane reads BPL contiguous bytes of a row,
+// Gather geometry of the forward: each lane reads 16 contiguous bytes of a row,
 // LPR lanes cover a row, one load instruction covers RPI rows, NI instructions
-// cover the 32 rows; a lane accumulates EPL output elements over its NI rows and
-// the RPI row groups are summed with xor shuffles.
+// cover R rows; a lane accumulates EPL output elements over its NI rows, and
+// the RPI row groups are summed across lanes.
 template <int DT, int M, int R = NB>
 struct FwdGeom {
   static constexpr int ES = DT == LRAM_F32 ? 4 : 2;
   static constexpr int RB = M * ES;
-  static constexpr int BPL = (DT == LRAM_F32 && M == 64) ? 8 : 4;
-  static constexpr int LPR = RB / BPL;
+  static constexpr int LPR = RB / 16;
   static constexpr int RPI = WAVE / LPR;
   static constexpr int NI = R / RPI;
-  static constexpr int EPL = BPL / ES;
-  static constexpr int DW = BPL / 4;  // dwords per lane per row
-  static_assert(LPR <= WAVE && WAVE % LPR == 0 && R % RPI == 0, "forward gather geometry");
+  static constexpr int EPL = 16 / ES;
+  static_assert(LPR >= 4 && LPR <= 16 && R % RPI == 0, "forward gather geometry");
 };
 
 // Loads the rows r0 .. r0 + R of list `buf` (R = the geometry's chunk).
-template <int DT, int M, int KS, int R = NB, int NBUF = 1>
-__device__ __forceinline__ void fwd_issue(const char* __restrict__ tb, const WaveLds<KS, NBUF>& W, int buf, int lane,
-                                          uint32_t (&v)[FwdGeom<DT, M, R>::NI][FwdGeom<DT, M, R>::DW], int r0 = 0) {
+// full: every entry is real, so the loads need no condition; padding entries
+// (location -1) are not read and give zeros.
+template <int DT, int M, int KS, int R = NB, int NBUF, int WBUF>
+__device__ __forceinline__ void fwd_issue(const char* __restrict__ tb, const WaveLds<KS, NBUF, WBUF>& W, int buf, int lane,
+                                          bool full, uint4 (&v)[FwdGeom<DT, M, R>::NI], int r0 = 0) {
   using G = FwdGeom<DT, M, R>;
   const int rsub = lane / G::LPR, col = lane % G::LPR;
+  if (full) {
 #pragma unroll
-  for (int p = 0; p < G::NI; ++p) {
-    const int32_t s = W.nbr[buf][r0 + p * G::RPI + rsub].slot;
-    const char* src = tb + (size_t)(s >= 0 ? s : 0) * G::RB + col * G::BPL;
-    if constexpr (G::DW == 1) {
-      v[p][0] = s >= 0 ? *reinterpret_cast<const uint32_t*>(src) : 0u;
-    } else {
-      const uint2 t = s >= 0 ? *reinterpret_cast<const uint2*>(src) : make_uint2(0, 0);
-      v[p][0] = t.x;
-      v[p][1] = t.y;
+    for (int p = 0; p < G::NI; ++p) {
+      const uint32_t s = (uint32_t)W.nbr[buf][r0 + p * G::RPI + rsub].slot;
+      v[p] = *reinterpret_cast<const uint4*>(tb + (size_t)s * G::RB + col * 16);
+    }
+  } else {
+#pragma unroll
+    for (int p = 0; p < G::NI; ++p) {
+      const int32_t s = W.nbr[buf][r0 + p * G::RPI + rsub].slot;
+      v[p] = make_uint4(0, 0, 0, 0);
+      if (s >= 0) v[p] = *reinterpret_cast<const uint4*>(tb + (size_t)s * G::RB + col * 16);
     }
   }
 }
 
-// acc += sum over the rows r0 .. r0 + R of w_j * v_j (this lane's columns).
-template <int DT, int M, int KS, int R = NB, int NBUF = 1>
-__device__ __forceinline__ void fwd_accumulate(const WaveLds<KS, NBUF>& W, int buf, int lane,
-                                               const uint32_t (&v)[FwdGeom<DT, M, R>::NI][FwdGeom<DT, M, R>::DW],
+// acc += sum over the rows r0 .. r0 + R of w_j * v_j (this lane's columns),
+// weight list wb.
+template <int DT, int M, int KS, int R = NB, int NBUF, int WBUF>
+__device__ __forceinline__ void fwd_accumulate(const WaveLds<KS, NBUF, WBUF>& W, int wb, int lane,
+                                               const uint4 (&v)[FwdGeom<DT, M, R>::NI],
                                                float (&acc)[FwdGeom<DT, M, R>::EPL], int r0 = 0) {
   using G = FwdGeom<DT, M, R>;
   const int rsub = lane / G::LPR;
 #pragma unroll
   for (int p = 0; p < G::NI; ++p) {
-    const float w = W.wgt[buf][r0 + p * G::RPI + rsub];
-    if constexpr (DT == LRAM_F32) {
+    const float w = W.wgt[wb][r0 + p * G::RPI + rsub];
+    float f[G::EPL];
+    unpack16<DT, G::EPL>(v[p], f);
 #pragma unroll
-      for (int e = 0; e < G::EPL; ++e) acc[e] = fmaf(w, __uint_as_float(v[p][e]), acc[e]);
-    } else {
-#pragma unroll
-      for (int d = 0; d < G::DW; ++d) {
-        acc[2 * d] = fmaf(w, bf16_lo(v[p][d]), acc[2 * d]);
-        acc[2 * d + 1] = fmaf(w, bf16_hi(v[p][d]), acc[2 * d + 1]);
-      }
-    }
+    for (int e = 0; e < G::EPL; ++e) acc[e] = fmaf(w, f[e], acc[e]);
   }
 }
 
-// Sums the row groups of the wave (xor shuffles) and writes out[l] once
-// (nothing when !ok: only the store is skipped, so that the row loads are
-// waited for on every path and the next lookup's loads need not wait for
-// this store).
+// Sums the row groups of the wave and writes out[l] once (nothing when !ok).
+// Lane bits 5 and 4 always tell row groups apart: there the lanes exchange
+// halves of their columns while they add, so a lane ends with a quarter of
+// its columns (one fp32, two bf16); the bits below are plain sums.
 template <int DT, int M>
 __device__ __forceinline__ void fwd_store(int lane, int64_t l, float (&acc)[FwdGeom<DT, M>::EPL],
                                           void* __restrict__ out, bool ok = true) {
   using G = FwdGeom<DT, M>;
-  const int rsub = lane / G::LPR, col = lane % G::LPR;
+  constexpr int Q = G::EPL / 4;
 #pragma unroll
-  for (int mask = G::LPR; mask < WAVE; mask <<= 1)
+  for (int e = 0; e < 2 * Q; ++e) acc[e] = add_halves_f32<32>(acc[e], acc[e + 2 * Q]);
 #pragma unroll
-    for (int e = 0; e < G::EPL; ++e) acc[e] += __shfl_xor(acc[e], mask);
-  if (rsub == 0 && ok) {
-    char* ob = reinterpret_cast<char*>(out) + (size_t)l * G::RB + col * G::BPL;
-    if constexpr (DT == LRAM_F32) {
-      if constexpr (G::EPL == 1)
-        *reinterpret_cast<float*>(ob) = acc[0];
-      else
-        *reinterpret_cast<float2*>(ob) = make_float2(acc[0], acc[1]);
-    } else {
+  for (int e = 0; e < Q; ++e) {
+    acc[e] = add_halves_f32<16>(acc[e], acc[e + Q]);
+    if constexpr (G::LPR <= 8) acc[e] += dpp_f32<DPP_ROR8>(acc[e]);
+    if constexpr (G::LPR <= 4) acc[e] += dpp_f32<DPP_ROR4>(acc[e]);
+  }
+  if ((lane & 15) < G::LPR && ok) {
+    const int piece = (lane & 15) * 4 + ((lane & 32) ? 2 : 0) + ((lane & 16) ? 1 : 0);
+    char* ob = reinterpret_cast<char*>(out) + (size_t)l * G::RB + piece * 4;
+    if constexpr (DT == LRAM_F32)
+      *reinterpret_cast<float*>(ob) = acc[0];
+    else
       *reinterpret_cast<uint32_t*>(ob) = pack_bf16x2(acc[0], acc[1]);
-    }
   }
 }
 
 template <int DT, int M>
-__device__ __forceinline__ void fwd_consume(const WaveLds<NB, 2>& W, int buf, int lane, int64_t l,
-                                            const uint32_t (&v)[FwdGeom<DT, M>::NI][FwdGeom<DT, M>::DW],
-                                            void* __restrict__ out, bool ok = true) {
+__device__ __forceinline__ void fwd_consume(const WaveLds<NB, 2, 4>& W, int wb, int lane, int64_t l,
+                                            const uint4 (&v)[FwdGeom<DT, M>::NI], void* __restrict__ out,
+                                            bool ok = true) {
   float acc[FwdGeom<DT, M>::EPL];
 #pragma unroll
   for (int e = 0; e < FwdGeom<DT, M>::EPL; ++e) acc[e] = 0.0f;
-  fwd_accumulate<DT, M, NB>(W, buf, lane, v, acc);
+  fwd_accumulate<DT, M, NB>(W, wb, lane, v, acc);
   fwd_store<DT, M>(lane, l, acc, out, ok);
 }
 
@@ -204,34 +247,47 @@ __device__ __forceinline__ void fwd_consume(const WaveLds<NB, 2>& W, int buf, in
 // in time and on the same XCD); outputs still go to the lookup's row.
 // SAVE: write every lookup's list for the backward (NbrList).
 template <int DT, int M, bool TH, bool ORD = false, bool SAVE = false>
-__global__ void __launch_bounds__(THREADS) k_forward(const float* __restrict__ q, Params P,
+__global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH ? 3 : 4) k_forward(const float* __restrict__ q, Params P,
                                                      const void* __restrict__ table, void* __restrict__ out,
                                                      const uint32_t* __restrict__ perm, NbrList save) {
   using G = FwdGeom<DT, M>;
-  __shared__ SearchLds<WAVE, NB, 2> S;
+  __shared__ SearchLds<NB, 2, 4> S;
   WaveCtx c;
-  if (!wave_ctx(P, c, ORD)) return;
-  Search<NB, 2> srch(P, S.tab, S.wave[c.wave], c.wave, c.lane);
-  WaveLds<NB, 2>& W = S.wave[c.wave];
-  Frame* FR = S.frames[c.wave];
-  uint32_t my_l = 0;
-  if constexpr (ORD)
-    my_l = phase_a_perm<TH>(q, perm, c.base, c.nl, P, FR, c.lane);
-  else
-    phase_a<TH>(q, c.base, c.nl, P, FR, c.lane);
+  wave_ctx(P, c, ORD);
+  TileInput<TH, ORD> in(q, perm, c.base, c.nl, P, c.lane);
+  TileSearch<TH, 4> ts(P, S, c.wave, c.lane);
   const char* tb = reinterpret_cast<const char*>(table);
-  uint32_t v[G::NI][G::DW];
-  srch.run(FR[0], read_sel(FR[0]), 0);
-  fwd_issue<DT, M, NB>(tb, W, 0, c.lane, v);
-  for (int t = 0; t < c.nl; ++t) {
-    const int buf = t & 1;
-    const int64_t l = ORD ? (int64_t)(uint32_t)__builtin_amdgcn_readlane(my_l, t) : c.base + t;
-    // search lookup t+1 while the rows of lookup t are in flight
-    if (t + 1 < c.nl) srch.run(FR[t + 1], read_sel(FR[t + 1]), buf ^ 1);
-    const bool ok = !ORD || l < P.L;
-    fwd_consume<DT, M>(W, buf, c.lane, ok ? l : 0, v, out, ok);
-    if constexpr (SAVE) srch.save(buf, save, l, ok);
-    if (t + 1 < c.nl) fwd_issue<DT, M, NB>(tb, W, buf ^ 1, c.lane, v);
+  for (int t0 = 0; t0 < c.nl; t0 += TILE) {
+    const int nt = min(TILE, c.nl - t0), np = (nt + 1) / 2;
+    ts.frames(in.v, in.have, nt);
+    in.advance(t0, P);
+    uint4 v0[G::NI], v1[G::NI];
+    // pair p is searched while the rows of pair p - 1 are in flight
+#pragma unroll 1
+    for (int p = 0; p <= np; ++p) {
+      bool ok;
+      if (p < np) {
+        ts.pair(p, 2 * (p & 1));
+        if constexpr (SAVE) {
+          const int64_t l0 = in.lookup(t0, 2 * p, P, ok);
+          ts.one.save(0, 2 * (p & 1), save, l0, ok);
+          const int64_t l1 = in.lookup(t0, 2 * p + 1, P, ok);
+          ts.one.save(1, 2 * (p & 1) + 1, save, l1, ok);
+        }
+      }
+      if (p > 0) {
+        const int wb = 2 * ((p - 1) & 1);
+        const int64_t l0 = in.lookup(t0, 2 * p - 2, P, ok);
+        fwd_consume<DT, M>(ts.W, wb, c.lane, l0, v0, out, ok);
+        const int64_t l1 = in.lookup(t0, 2 * p - 1, P, ok);
+        fwd_consume<DT, M>(ts.W, wb + 1, c.lane, l1, v1, out, ok);
+      }
+      if (p < np) {
+        fwd_issue<DT, M, NB>(tb, ts.W, 0, c.lane, ts.count0 == NB, v0);
+        fwd_issue<DT, M, NB>(tb, ts.W, 1, c.lane, ts.count1 == NB, v1);
+      }
+    }
+    wave_lds_sync();
   }
 }
 
@@ -243,26 +299,30 @@ __global__ void __launch_bounds__(THREADS) k_forward_k(const float* __restrict__
                                                        const void* __restrict__ table, void* __restrict__ out) {
   constexpr int R = chunk_rows<KS>();
   using G = FwdGeom<DT, M, R>;
-  __shared__ SearchLds<WAVE, KS> S;
+  __shared__ SearchLds<KS> S;
   WaveCtx c;
   if (!wave_ctx(P, c)) return;
-  Search<KS> srch(P, S.tab, S.wave[c.wave], c.wave, c.lane);
+  Search<KS> srch(P, S.tab, S.wave[c.wave], S.tile, c.wave, c.lane);
   WaveLds<KS>& W = S.wave[c.wave];
+  const QuadCtx<false> Q(P, c.lane);
   Frame* FR = S.frames[c.wave];
-  phase_a<false>(q, c.base, c.nl, P, FR, c.lane);
   const char* tb = reinterpret_cast<const char*>(table);
-  for (int t = 0; t < c.nl; ++t) {
-    const int count = srch.run(FR[t], read_sel(FR[t]), 0);
-    float acc[G::EPL];
+  for (int t0 = 0; t0 < c.nl; t0 += TILE) {
+    const int nt = min(TILE, c.nl - t0);
+    tile_frames(q, c.base + t0, nt, P, FR, Q, c.lane);
+    for (int t = 0; t < nt; ++t) {
+      const int count = srch.run(FR[t], read_sel(FR[t]), 0);
+      float acc[G::EPL];
 #pragma unroll
-    for (int e = 0; e < G::EPL; ++e) acc[e] = 0.0f;
-    for (int r0 = 0; r0 < count; r0 += R) {
-      uint32_t v[G::NI][G::DW];
-      fwd_issue<DT, M, KS, R>(tb, W, 0, c.lane, v, r0);
-      fwd_accumulate<DT, M, KS, R>(W, 0, c.lane, v, acc, r0);
+      for (int e = 0; e < G::EPL; ++e) acc[e] = 0.0f;
+      for (int r0 = 0; r0 < count; r0 += R) {
+        uint4 v[G::NI];
+        fwd_issue<DT, M, KS, R>(tb, W, 0, c.lane, r0 + R <= count, v, r0);
+        fwd_accumulate<DT, M, KS, R>(W, 0, c.lane, v, acc, r0);
+      }
+      fwd_store<DT, M>(c.lane, c.base + t0 + t, acc, out);
+      wave_lds_sync();
     }
-    fwd_store<DT, M>(c.lane, c.base + t, acc, out);
-    wave_lds_sync();
   }
 }
 

@@ -197,7 +197,7 @@ struct alignas(16) FusedLds {
     int32_t tag[MERGE_H];       // hash tags; then group locations [0, ngroups) and pair weights [MERGE_P, 2 MERGE_P)
   } a;
   union {
-    SearchLds<merge_lpw<KS>(), KS> search;
+    SearchLds<KS> search;
     MergeWork<M, merge_t<KS>()> merge;
   } b;
 };
@@ -234,7 +234,7 @@ __global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS>())) 
                                                              const uint32_t* __restrict__ gate, NbrList saved) {
   __shared__ FusedLds<M, KS> S;
   if (!merge_chosen(*gate, P.L)) return;  // the batch is scattered by k_backward instead
-  const int t = threadIdx.x, wave = t / WAVE, lane = t % WAVE;
+  const int t = threadIdx.x, wave = (int)uniform(t / WAVE), lane = t % WAVE;
   const int64_t bbase = xcd_block() * (WAVES * P.lpw);  // consecutive batches share an L2
   const int nt = (int)min<int64_t>(WAVES * P.lpw, P.L - bbase);
   bool shared = false;
@@ -248,44 +248,71 @@ __global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS>())) 
   {
     const int64_t base = bbase + (int64_t)wave * P.lpw;
     const int nl = (int)max<int64_t>(0, min<int64_t>(P.lpw, P.L - base));
-    if (nl > 0) {
-      Search<KS> srch(P, S.b.search.tab, S.b.search.wave[wave], wave, lane);
-      WaveLds<KS>& W = S.b.search.wave[wave];
-      Frame* FR = S.b.search.frames[wave];
-      const uint32_t my_l = phase_a_perm<TH>(q, perm, base, nl, P, FR, lane);
-      const char* tb = reinterpret_cast<const char*>(table);
-      for (int i = 0; i < nl; ++i) {
-        const Frame& F = FR[i];
-        const Sel sel = read_sel(F);
-        const int64_t l = (int64_t)(uint32_t)__builtin_amdgcn_readlane(my_l, i);
-        int count;
-        if constexpr (SAVED)
-          count = srch.load(F, sel, 0, saved, l, P.N);
-        else
-          count = srch.run(F, sel, 0);
-        if (!merge && count > 0) scatter_atomic<M, KS>(W, count, gout, l, gtab, lane);
-        if (gq && l < P.L) grad_query<DT, M, TH, KS>(F, W, S.b.search.tab, count, tb, gout, l, lane, gq, q, P);
-        if (merge && !COMPACT) {
+    auto& W = S.b.search.wave[wave];
+    const char* tb = reinterpret_cast<const char*>(table);
+    // scatter or keep the pairs of list buf (the wave's i-th lookup, l), and its query gradient
+    auto finish = [&](const Frame& F, int buf, int count, int i, int64_t l) {
+      if (!merge && count > 0) scatter_atomic<M, KS>(W, buf, count, gout, l, gtab, lane);
+      if (gq && l < P.L) grad_query<DT, M, TH, KS>(F, W, buf, S.b.search.tab, count, tb, gout, l, lane, gq, q, P);
+      if (merge && !COMPACT) {
 #pragma unroll
-          for (int j = lane; j < KS; j += WAVE) {
-            const int pidx = (wave * P.lpw + i) * KS + j;
-            S.a.pairs.loc[pidx] = W.nbr[0][j].slot;
-            S.a.pairs.w[pidx] = W.wgt[0][j];
+        for (int j = lane; j < KS; j += WAVE) {
+          const int pidx = (wave * P.lpw + i) * KS + j;
+          S.a.pairs.loc[pidx] = W.nbr[buf][j].slot;
+          S.a.pairs.w[pidx] = W.wgt[buf][j];
+        }
+      }
+      if constexpr (COMPACT) {
+        if (merge && used + count <= MERGE_SEG) {
+          for (int j = lane; j < count; j += WAVE) {
+            const int pidx = wave * MERGE_SEG + used + j;
+            S.a.pairs.loc[pidx] = W.nbr[buf][j].slot;
+            S.a.pairs.w[pidx] = W.wgt[buf][j];
+            S.a.pairs.lk[pidx] = (uint8_t)(wave * P.lpw + i);
+          }
+          used += count;
+        } else if (merge && count > 0) {
+          scatter_atomic<M, KS>(W, buf, count, gout, l, gtab, lane);  // the segment is full
+        }
+      }
+    };
+    static_assert(merge_lpw<KS>() <= TILE, "a wave's lookups are one tile");
+    QuadIn<TH> in;
+    uint32_t my_l;
+    auto lookup_of = [&](int i) { return (int64_t)(uint32_t)__builtin_amdgcn_readlane(my_l, 4 * i); };
+    if constexpr (KS == NB) {
+      TileSearch<TH, 2> ts(P, S.b.search, wave, lane);
+      if (nl > 0) {
+        const bool have = load_tile<TH, true>(q, perm, base, nl, P, lane, in, my_l);
+        ts.template frames<!SAVED>(in, have, nl);
+        if constexpr (SAVED) {
+          for (int i = 0; i < nl; ++i) {
+            const int64_t l = lookup_of(i);
+            const int count = ts.one.load(ts.FR[i], read_sel(ts.FR[i]), 0, saved, l, P.N);
+            finish(ts.FR[i], 0, count, i, l);
+            wave_lds_sync();
+          }
+        } else {
+          for (int p = 0; 2 * p < nl; ++p) {
+            ts.pair(p, 0);
+            finish(ts.FR[2 * p], 0, ts.count0, 2 * p, lookup_of(2 * p));
+            if (2 * p + 1 < nl) finish(ts.FR[2 * p + 1], 1, ts.count1, 2 * p + 1, lookup_of(2 * p + 1));
+            wave_lds_sync();
           }
         }
-        if constexpr (COMPACT) {
-          if (merge && used + count <= MERGE_SEG) {
-            for (int j = lane; j < count; j += WAVE) {
-              const int pidx = wave * MERGE_SEG + used + j;
-              S.a.pairs.loc[pidx] = W.nbr[0][j].slot;
-              S.a.pairs.w[pidx] = W.wgt[0][j];
-              S.a.pairs.lk[pidx] = (uint8_t)(wave * P.lpw + i);
-            }
-            used += count;
-          } else if (merge && count > 0) {
-            scatter_atomic<M, KS>(W, count, gout, l, gtab, lane);  // the segment is full
-          }
-        }
+      }
+    } else if (nl > 0) {
+      Search<KS> srch(P, S.b.search.tab, W, S.b.search.tile, wave, lane);
+      const QuadCtx<TH> Q(P, lane);
+      Frame* FR = S.b.search.frames[wave];
+      const bool have = load_tile<TH, true>(q, perm, base, nl, P, lane, in, my_l);
+      const uint2 sel = make_frames<TH>(in, have, Q, FR);
+      wave_lds_sync();
+      finish_frames(sel, lane, FR);
+      wave_lds_sync();
+      for (int i = 0; i < nl; ++i) {
+        const int count = srch.run(FR[i], read_sel(FR[i]), 0);
+        finish(FR[i], 0, count, i, lookup_of(i));
         wave_lds_sync();
       }
     }

@@ -12,38 +12,48 @@ namespace {
 // of the pairs that read location s; then the fraction of locations read and
 // the KL divergence of the weighted access distribution from uniform.
 
-__global__ void __launch_bounds__(THREADS) k_access_hist(const float* __restrict__ q, Params P,
+__global__ void __launch_bounds__(THREADS, 4) k_access_hist(const float* __restrict__ q, Params P,
                                                          float* __restrict__ hist) {
-  __shared__ SearchLds<WAVE> S;
+  __shared__ SearchLds<> S;
   WaveCtx c;
-  if (!wave_ctx(P, c)) return;
-  Search<NB> srch(P, S.tab, S.wave[c.wave], c.wave, c.lane);
-  WaveLds<NB>& W = S.wave[c.wave];
-  Frame* FR = S.frames[c.wave];
-  phase_a<false>(q, c.base, c.nl, P, FR, c.lane);
-  for (int t = 0; t < c.nl; ++t) {
-    const int count = srch.run(FR[t], read_sel(FR[t]), 0);
-    if (c.lane < count) unsafeAtomicAdd(hist + W.nbr[0][c.lane].slot, W.wgt[0][c.lane]);
-    wave_lds_sync();
+  wave_ctx(P, c);
+  TileInput<false, false> in(q, nullptr, c.base, c.nl, P, c.lane);
+  TileSearch<false, 2> ts(P, S, c.wave, c.lane);
+  for (int t0 = 0; t0 < c.nl; t0 += TILE) {
+    const int nt = min(TILE, c.nl - t0);
+    ts.frames(in.v, in.have, nt);
+    in.advance(t0, P);
+    for (int p = 0; 2 * p < nt; ++p) {
+      ts.pair(p, 0);
+      const int h = c.lane >> 5, j = c.lane & 31;
+      const int32_t s = ts.W.nbr[h][j].slot;
+      if (s >= 0) unsafeAtomicAdd(hist + s, ts.W.wgt[h][j]);
+      wave_lds_sync();
+    }
   }
 }
 
 // touched[s] = 1 for every location s in a lookup's list of its closest 32
 // (the rows a backward of these lookups writes): plain byte stores, every
 // writer stores the same value.
-__global__ void __launch_bounds__(THREADS) k_mark_touched(const float* __restrict__ q, Params P,
+__global__ void __launch_bounds__(THREADS, 4) k_mark_touched(const float* __restrict__ q, Params P,
                                                           uint8_t* __restrict__ touched) {
-  __shared__ SearchLds<WAVE> S;
+  __shared__ SearchLds<> S;
   WaveCtx c;
-  if (!wave_ctx(P, c)) return;
-  Search<NB> srch(P, S.tab, S.wave[c.wave], c.wave, c.lane);
-  WaveLds<NB>& W = S.wave[c.wave];
-  Frame* FR = S.frames[c.wave];
-  phase_a<false>(q, c.base, c.nl, P, FR, c.lane);
-  for (int t = 0; t < c.nl; ++t) {
-    const int count = srch.run(FR[t], read_sel(FR[t]), 0);
-    if (c.lane < count) touched[W.nbr[0][c.lane].slot] = 1;
-    wave_lds_sync();
+  wave_ctx(P, c);
+  TileInput<false, false> in(q, nullptr, c.base, c.nl, P, c.lane);
+  TileSearch<false, 2> ts(P, S, c.wave, c.lane);
+  for (int t0 = 0; t0 < c.nl; t0 += TILE) {
+    const int nt = min(TILE, c.nl - t0);
+    ts.frames(in.v, in.have, nt);
+    in.advance(t0, P);
+    for (int p = 0; 2 * p < nt; ++p) {
+      ts.pair(p, 0);
+      const int h = c.lane >> 5, j = c.lane & 31;
+      const int32_t s = ts.W.nbr[h][j].slot;
+      if (s >= 0) touched[s] = 1;
+      wave_lds_sync();
+    }
   }
 }
 

@@ -1,0 +1,74 @@
+"""The tile search at its edges: tiles of every size up to two, and tiles that mix lookups which the tile search
+decides with ones that take the general search (lattice points, holes, near ties) or have no list (non-finite
+queries), in either place of a pair.
+
+Bars as in the parity tests: lists, distances and weights bit-exact against the oracle; forward, dq and the value
+gradient per row relative 1e-5 (fp32) / 2e-2 (a bf16 result), zero rows for non-finite queries.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2107_03474_amd as lram
+from test_gpu_parity import _rel_rows, _say, check_neighbors, special_queries
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def mixed_queries(L, K, seed):
+    rng = np.random.default_rng(seed)
+    q = (rng.random((L, 8)) * np.asarray(K)).astype(np.float32)
+    sp = special_queries(K)
+    for l in range(L):
+        kind = rng.integers(0, 4)
+        if kind == 0:
+            q[l] = sp[rng.integers(0, len(sp))]
+        elif kind == 1:
+            q[l] = (rng.integers(0, 16, 8) / 4.0).astype(np.float32)
+    return q
+
+
+@pytest.mark.parametrize("L", [1, 2, 3, 15, 16, 17, 31, 33, 129])
+@pytest.mark.parametrize("K", [(4,) * 8, (2, 4, 6, 8, 10, 2, 4, 6)])
+def test_lists(L, K):
+    _say("tile lists L=%d K=%s" % (L, K))
+    check_neighbors(mixed_queries(L, K, L), K)
+
+
+@pytest.mark.parametrize("m,dtype", [(32, "f32"), (64, "f32"), (32, "bf16"), (64, "bf16")])
+@pytest.mark.parametrize("L", [1, 3, 17, 40000])
+def test_step(L, m, dtype):
+    _say("tile step L=%d m=%d %s" % (L, m, dtype))
+    K = (4, 4, 6, 4, 4, 8, 4, 4)
+    N = int(np.prod(K))
+    q_np = mixed_queries(min(L, 500), K, 7 * L + m)
+    q_np = np.resize(q_np, (L, 8))
+    if L > 2:
+        q_np[L // 2, 3] = np.nan
+        q_np[L - 1, 0] = np.inf
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    table = (torch.randn((N, m), generator=g, device=DEV) * 0.02).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    G = torch.randn((L, m), generator=g, device=DEV)
+    q = torch.from_numpy(q_np).to(DEV)
+    out = lram.forward(q, table, K)
+    gt, gq = lram.backward(q, table, K, G, mode="atomic")
+    fin = np.isfinite(q_np).all(1)
+    assert not out.cpu().float().numpy()[~fin].any() and not gq.cpu().numpy()[~fin].any()
+    nb = oracle.neighbors(np.where(fin[:, None], q_np, 0), K)
+    rows = oracle.gather_rows(table.float().cpu().numpy(), nb["slot"])
+    G_np = np.where(fin[:, None], G.cpu().numpy(), 0)
+    assert _rel_rows(out.float().cpu().numpy()[fin], oracle.forward(nb, rows)[fin]).max() <= (1e-5 if dtype == "f32" else 2e-2)
+    ref = oracle.grad_query(nb, rows, G_np)
+    # at a lattice point dq is the sum of exactly cancelling terms' rounding: absolute bar, 1e-6 of the largest row
+    err = np.linalg.norm(gq.cpu().numpy()[fin] - ref[fin], axis=1)
+    size = np.linalg.norm(ref[fin], axis=1)
+    assert (err <= np.maximum(1e-5 * size, 1e-6 * size.max())).all()
+    uniq, acc = oracle.grad_table_rows(nb, G_np)
+    got = gt.cpu().numpy()
+    assert _rel_rows(got[uniq], acc).max() <= 2e-5
+    rest = np.ones(N, bool)
+    rest[uniq] = False
+    assert not got[rest].any()
