@@ -31,6 +31,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 #include <utility>
 
 #include "../../include/lram.h"
@@ -56,6 +57,11 @@ thread_local int g_last_hip_error = 0;
 // vectors, the element size for the per-element arrays.
 bool misaligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
 bool misaligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3) != 0; }
+
+// The activation layer's coordinates are staged from this many lookups on (see
+// IN_STAGED): below, the second launch costs what it saves (forward, m = 64 bf16,
+// inline / staged: 16,383 and 16,384 lookups 25.3 / 24.8 us).
+constexpr int64_t STAGE_MIN = 16384;
 
 // Lookups per wave.  A wave that searches tiles spends a tile's cost whatever
 // the tile holds (about 900 instructions; 120 more for each pair of lookups), so
@@ -97,6 +103,7 @@ int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t
   }
   P->N = (uint32_t)N;
   P->L = *L;
+  P->stage = 0;
   P->lpw = lookups_per_wave(*L, true);
   return LRAM_OK;
 }
@@ -132,21 +139,45 @@ int dispatch(int dtype, int32_t m, Args... args) {
   return LRAM_EDTYPE;
 }
 
+// The activation layer's coordinates and scales staged for the lookups: records
+// of `stage` floats, q in the first 8, s in the 9th.
+int stage_coords(const float* z, Params& P, float* at, int stage, hipStream_t s) {
+  P.stage = stage;
+  hipLaunchKernelGGL(k_theta_coords, dim3((unsigned)((P.L + THREADS - 1) / THREADS)), dim3(THREADS), 0, s, z, P, at,
+                     stage, at + 8, stage);
+  return launched();
+}
+
+// Whether [a, a + na) and [b, b + nb) floats share memory (a caller that passes
+// the input's own buffer for the result keeps the path that reads z last).
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + 4 * nb && y < x + 4 * na;
+}
+
 template <int DT, int M>
 struct FwdLaunch {
-  static int go(const float* q, const Params& P, const void* table, void* out, bool th, const uint32_t* perm,
+  static int go(const float* q, const Params& Pq, const void* table, void* out, bool th, const uint32_t* perm,
                 NbrList save, hipStream_t s) {
+    Params P = Pq;
     const dim3 g(grid_for(P)), b(THREADS);
-    if (th)
-      hipLaunchKernelGGL((k_forward<DT, M, true>), g, b, 0, s, q, P, table, out, perm, save);
-    else if (perm && save.on())
-      hipLaunchKernelGGL((k_forward<DT, M, false, true, true>), g, b, 0, s, q, P, table, out, perm, save);
-    else if (perm)
-      hipLaunchKernelGGL((k_forward<DT, M, false, true, false>), g, b, 0, s, q, P, table, out, perm, save);
-    else if (save.on())
-      hipLaunchKernelGGL((k_forward<DT, M, false, false, true>), g, b, 0, s, q, P, table, out, perm, save);
-    else
-      hipLaunchKernelGGL((k_forward<DT, M, false>), g, b, 0, s, q, P, table, out, perm, save);
+    constexpr int row = M * (DT == LRAM_F32 ? 4 : 2) / 4;  // floats of an output row
+    if (th && P.L >= STAGE_MIN && !overlap(q, (size_t)P.L * 16, out, (size_t)P.L * row)) {
+      // an output row (64 bytes or more) holds its lookup's record until it is written
+      static_assert(row >= 9 && row % 4 == 0, "an output row holds a staged record");
+      if (int rc = stage_coords(q, P, (float*)out, row, s)) return rc;
+      hipLaunchKernelGGL((k_forward<DT, M, IN_STAGED>), g, b, 0, s, (const float*)out, P, table, out, perm, save);
+    } else if (th) {
+      hipLaunchKernelGGL((k_forward<DT, M, IN_THETA>), g, b, 0, s, q, P, table, out, perm, save);
+    } else if (perm && save.on()) {
+      hipLaunchKernelGGL((k_forward<DT, M, IN_QUERY, true, true>), g, b, 0, s, q, P, table, out, perm, save);
+    } else if (perm) {
+      hipLaunchKernelGGL((k_forward<DT, M, IN_QUERY, true, false>), g, b, 0, s, q, P, table, out, perm, save);
+    } else if (save.on()) {
+      hipLaunchKernelGGL((k_forward<DT, M, IN_QUERY, false, true>), g, b, 0, s, q, P, table, out, perm, save);
+    } else {
+      hipLaunchKernelGGL((k_forward<DT, M, IN_QUERY>), g, b, 0, s, q, P, table, out, perm, save);
+    }
     return launched();
   }
 };
@@ -326,7 +357,7 @@ size_t sorted_layout(int64_t L, int32_t m, SortedWs* ws, char* base) {
 
 // Fills an order: closest-point keys, the stable sort (its result lands in
 // sort.ka / sort.va whatever the number of passes), and the merge gate's count.
-template <bool TH>
+template <int TH>
 int build_order(const float* q, const Params& P, const OrderWs& o, hipStream_t s) {
   Radix<uint32_t> r = o.sort;
   if (radix_passes(P.N) & 1) {  // start from the other buffers so the result lands in ka / va
@@ -360,29 +391,33 @@ int build_order(const float* q, const Params& P, const OrderWs& o, hipStream_t s
 // The atomic backward kernel for lists of KS; gate is the merged scatter's
 // device-side choice (null: always scatter); perm an order to visit the
 // lookups in (null: index order); saved the forward's lists (or off).
-template <int DT, int M, bool TH, int KS>
-void launch_atomic(const float* q, const Params& Pq, const void* table, const float* g, float* gt, float* gq,
+template <int DT, int M, int TH, int KS>
+void launch_atomic(const float* q, const float* z, const Params& Pq, const void* table, const float* g, float* gt, float* gq,
                    const uint32_t* gate, const uint32_t* perm, NbrList saved, hipStream_t s) {
   Params P = Pq;
   P.lpw = lookups_per_wave(P.L, KS == NB);
+  // behind the gate large batches launch half the workgroups: where the gate
+  // sends the batch to the merge, each still costs its dispatch (32,768 of
+  // them 18 us at 4,194,304 lookups)
+  if (gate && P.lpw >= 2 * TILE) P.lpw = WAVE;
   const dim3 grid(grid_for(P)), b(THREADS);
   uint32_t* const nk = nullptr;
   uint2* const nv = nullptr;
-  if constexpr (!TH && KS == NB) {
+  if constexpr (TH == IN_QUERY && KS == NB) {
     if (perm && saved.on())
-      hipLaunchKernelGGL((k_backward<DT, M, false, false, NB, true, true>), grid, b, 0, s, q, P, table, g, gt, gq, nk,
+      hipLaunchKernelGGL((k_backward<DT, M, false, IN_QUERY, NB, true, true>), grid, b, 0, s, q, z, P, table, g, gt, gq, nk,
                          nv, gate, perm, saved);
     else if (perm)
-      hipLaunchKernelGGL((k_backward<DT, M, false, false, NB, true, false>), grid, b, 0, s, q, P, table, g, gt, gq,
+      hipLaunchKernelGGL((k_backward<DT, M, false, IN_QUERY, NB, true, false>), grid, b, 0, s, q, z, P, table, g, gt, gq,
                          nk, nv, gate, perm, saved);
     else if (saved.on())
-      hipLaunchKernelGGL((k_backward<DT, M, false, false, NB, false, true>), grid, b, 0, s, q, P, table, g, gt, gq,
+      hipLaunchKernelGGL((k_backward<DT, M, false, IN_QUERY, NB, false, true>), grid, b, 0, s, q, z, P, table, g, gt, gq,
                          nk, nv, gate, perm, saved);
     else
-      hipLaunchKernelGGL((k_backward<DT, M, false, false, NB>), grid, b, 0, s, q, P, table, g, gt, gq, nk, nv, gate,
+      hipLaunchKernelGGL((k_backward<DT, M, false, IN_QUERY, NB>), grid, b, 0, s, q, z, P, table, g, gt, gq, nk, nv, gate,
                          perm, saved);
   } else {
-    hipLaunchKernelGGL((k_backward<DT, M, false, TH, KS>), grid, b, 0, s, q, P, table, g, gt, gq, nk, nv, gate,
+    hipLaunchKernelGGL((k_backward<DT, M, false, TH, KS>), grid, b, 0, s, q, z, P, table, g, gt, gq, nk, nv, gate,
                        perm, saved);
   }
 }
@@ -391,16 +426,16 @@ void launch_atomic(const float* q, const Params& Pq, const void* table, const fl
 // passed one: have_order), then both the atomic kernel and the merged kernel --
 // the gate's count decides on the device which one works (thinly spread
 // queries have nothing to merge and keep the atomic kernel's occupancy).
-template <int DT, int M, bool TH, int KS>
-int merged_pass(const float* q, const Params& P, const void* table, const float* g, float* gt, float* gq,
+template <int DT, int M, int TH, int KS>
+int merged_pass(const float* q, const float* z, const Params& P, const void* table, const float* g, float* gt, float* gq,
                 const OrderWs& o, bool have_order, NbrList saved, hipStream_t s) {
   if (!gt) {
-    launch_atomic<DT, M, TH, KS>(q, P, table, g, gt, gq, nullptr, nullptr, saved, s);
+    launch_atomic<DT, M, TH, KS>(q, z, P, table, g, gt, gq, nullptr, nullptr, saved, s);
     return launched();
   }
   if (!have_order)
     if (int rc = build_order<TH>(q, P, o, s)) return rc;
-  launch_atomic<DT, M, TH, KS>(q, P, table, g, gt, gq, o.shared, nullptr, saved, s);
+  launch_atomic<DT, M, TH, KS>(q, z, P, table, g, gt, gq, o.shared, nullptr, saved, s);
   if (int rc = launched()) return rc;
   // one batch of at most merge_t<KS>() lookups per workgroup
   Params Pm = P;
@@ -409,16 +444,27 @@ int merged_pass(const float* q, const Params& P, const void* table, const float*
   const dim3 grid((unsigned)((P.L + per_block - 1) / per_block));
   const uint32_t* keys = o.sort.ka;
   const uint32_t* perm = o.sort.va;
-  if constexpr (!TH && KS == NB) {
+  if constexpr (TH == IN_QUERY && KS == NB) {
     if (saved.on()) {
-      hipLaunchKernelGGL((k_backward_merged<DT, M, false, NB, true>), grid, dim3(THREADS), 0, s, q, Pm, table, g, gt,
-                         gq, keys, perm, (const uint32_t*)o.shared, saved);
+      hipLaunchKernelGGL((k_backward_merged<DT, M, IN_QUERY, NB, true>), grid, dim3(THREADS), 0, s, q, z, Pm, table, g,
+                         gt, gq, keys, perm, (const uint32_t*)o.shared, saved);
       return launched();
     }
   }
-  hipLaunchKernelGGL((k_backward_merged<DT, M, TH, KS>), grid, dim3(THREADS), 0, s, q, Pm, table, g, gt, gq, keys,
+  hipLaunchKernelGGL((k_backward_merged<DT, M, TH, KS>), grid, dim3(THREADS), 0, s, q, z, Pm, table, g, gt, gq, keys,
                      perm, (const uint32_t*)o.shared, saved);
   return launched();
+}
+
+// The activation layer's input of a backward pass: staged in grad_in's rows
+// (16 floats, each read before its lookup's gradient is written) for large
+// batches, otherwise z itself.
+template <typename F>
+int with_theta_input(const float* z, Params P, float* gq, hipStream_t s, F go) {
+  if (!gq || P.L < STAGE_MIN || overlap(z, (size_t)P.L * 16, gq, (size_t)P.L * 16))
+    return go(std::integral_constant<int, IN_THETA>(), z, P);
+  if (int rc = stage_coords(z, P, gq, 16, s)) return rc;
+  return go(std::integral_constant<int, IN_STAGED>(), (const float*)gq, P);
 }
 
 // width: list width (16, 32, 64 or KALL); th: the activation layer (width 32 only).
@@ -426,15 +472,16 @@ template <int DT, int M>
 struct BwdAtomicLaunch {
   static int go(const float* q, const Params& P, const void* table, const float* g, float* gt, float* gq, bool th,
                 int width, const uint32_t* perm, NbrList saved, hipStream_t s) {
-    if (th) {
-      launch_atomic<DT, M, true, NB>(q, P, table, g, gt, gq, nullptr, perm, saved, s);
-    } else {
-      switch (width) {
-        case 16: launch_atomic<DT, M, false, 16>(q, P, table, g, gt, gq, nullptr, perm, saved, s); break;
-        case 64: launch_atomic<DT, M, false, 64>(q, P, table, g, gt, gq, nullptr, perm, saved, s); break;
-        case KALL: launch_atomic<DT, M, false, KALL>(q, P, table, g, gt, gq, nullptr, perm, saved, s); break;
-        default: launch_atomic<DT, M, false, NB>(q, P, table, g, gt, gq, nullptr, perm, saved, s); break;
-      }
+    if (th)
+      return with_theta_input(q, P, gq, s, [&](auto in, const float* at, const Params& Pt) {
+        launch_atomic<DT, M, decltype(in)::value, NB>(at, q, Pt, table, g, gt, gq, nullptr, perm, saved, s);
+        return launched();
+      });
+    switch (width) {
+      case 16: launch_atomic<DT, M, IN_QUERY, 16>(q, q, P, table, g, gt, gq, nullptr, perm, saved, s); break;
+      case 64: launch_atomic<DT, M, IN_QUERY, 64>(q, q, P, table, g, gt, gq, nullptr, perm, saved, s); break;
+      case KALL: launch_atomic<DT, M, IN_QUERY, KALL>(q, q, P, table, g, gt, gq, nullptr, perm, saved, s); break;
+      default: launch_atomic<DT, M, IN_QUERY, NB>(q, q, P, table, g, gt, gq, nullptr, perm, saved, s); break;
     }
     return launched();
   }
@@ -444,12 +491,15 @@ template <int DT, int M>
 struct BwdMergedLaunch {
   static int go(const float* q, const Params& P, const void* table, const float* g, float* gt, float* gq,
                 const OrderWs& o, bool have_order, bool th, int width, NbrList saved, hipStream_t s) {
-    if (th) return merged_pass<DT, M, true, NB>(q, P, table, g, gt, gq, o, have_order, saved, s);
+    if (th)
+      return with_theta_input(q, P, gq, s, [&](auto in, const float* at, const Params& Pt) {
+        return merged_pass<DT, M, decltype(in)::value, NB>(at, q, Pt, table, g, gt, gq, o, have_order, saved, s);
+      });
     switch (width) {
-      case 16: return merged_pass<DT, M, false, 16>(q, P, table, g, gt, gq, o, have_order, saved, s);
-      case 64: return merged_pass<DT, M, false, 64>(q, P, table, g, gt, gq, o, have_order, saved, s);
-      case KALL: return merged_pass<DT, M, false, KALL>(q, P, table, g, gt, gq, o, have_order, saved, s);
-      default: return merged_pass<DT, M, false, NB>(q, P, table, g, gt, gq, o, have_order, saved, s);
+      case 16: return merged_pass<DT, M, IN_QUERY, 16>(q, q, P, table, g, gt, gq, o, have_order, saved, s);
+      case 64: return merged_pass<DT, M, IN_QUERY, 64>(q, q, P, table, g, gt, gq, o, have_order, saved, s);
+      case KALL: return merged_pass<DT, M, IN_QUERY, KALL>(q, q, P, table, g, gt, gq, o, have_order, saved, s);
+      default: return merged_pass<DT, M, IN_QUERY, NB>(q, q, P, table, g, gt, gq, o, have_order, saved, s);
     }
   }
 };
@@ -461,13 +511,13 @@ struct BwdSortedLaunch {
     const dim3 grid(grid_for(P)), b(THREADS);
     const uint32_t* const np = nullptr;
     if (th)
-      hipLaunchKernelGGL((k_backward<DT, M, true, true>), grid, b, 0, s, q, P, table, g, gt, gq, ws.sort.ka,
+      hipLaunchKernelGGL((k_backward<DT, M, true, IN_THETA>), grid, b, 0, s, q, q, P, table, g, gt, gq, ws.sort.ka,
                          ws.sort.va, np, np, saved);
     else if (saved.on())
-      hipLaunchKernelGGL((k_backward<DT, M, true, false, NB, false, true>), grid, b, 0, s, q, P, table, g, gt, gq,
+      hipLaunchKernelGGL((k_backward<DT, M, true, IN_QUERY, NB, false, true>), grid, b, 0, s, q, q, P, table, g, gt, gq,
                          ws.sort.ka, ws.sort.va, np, np, saved);
     else
-      hipLaunchKernelGGL((k_backward<DT, M, true, false>), grid, b, 0, s, q, P, table, g, gt, gq, ws.sort.ka,
+      hipLaunchKernelGGL((k_backward<DT, M, true, IN_QUERY>), grid, b, 0, s, q, q, P, table, g, gt, gq, ws.sort.ka,
                          ws.sort.va, np, np, saved);
     int rc = launched();
     if (rc || !gt) return rc;
@@ -502,7 +552,7 @@ struct FwdKLaunch {
       case 64: hipLaunchKernelGGL((k_forward_k<DT, M, 64>), g, b, 0, s, q, P, table, out); break;
       case KALL: hipLaunchKernelGGL((k_forward_k<DT, M, KALL>), g, b, 0, s, q, P, table, out); break;
       default:
-        hipLaunchKernelGGL((k_forward<DT, M, false>), g, b, 0, s, q, P, table, out, (const uint32_t*)nullptr,
+        hipLaunchKernelGGL((k_forward<DT, M, IN_QUERY>), g, b, 0, s, q, P, table, out, (const uint32_t*)nullptr,
                            NbrList{nullptr, nullptr, nullptr});
         break;
     }
@@ -681,7 +731,7 @@ int lram_order(const float* q, int64_t B, int64_t H, const int32_t K[8], void* o
   OrderWs o;
   if ((rc = check_order(order, order_bytes, L, &o))) return rc;
   if (L == 0) return LRAM_OK;
-  return build_order<false>(q, P, o, (hipStream_t)stream);
+  return build_order<IN_QUERY>(q, P, o, (hipStream_t)stream);
 }
 
 int lram_forward(const float* q, int64_t B, int64_t H, const int32_t K[8], const void* table, int dtype,
@@ -705,7 +755,7 @@ int lram_theta_coords(const float* z, int64_t B, int64_t H, const int32_t K[8], 
   if (L == 0) return LRAM_OK;
   if (!q || misaligned16(q) || misaligned4(s)) return LRAM_EINVAL;
   hipLaunchKernelGGL(k_theta_coords, dim3((unsigned)((L + THREADS - 1) / THREADS)), dim3(THREADS), 0,
-                     (hipStream_t)stream, z, P, q, s);
+                     (hipStream_t)stream, z, P, q, 8, s, 1);
   return launched();
 }
 

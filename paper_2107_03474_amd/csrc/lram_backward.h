@@ -59,10 +59,10 @@ __device__ __forceinline__ void scatter_atomic(const WaveLds<KS, NBUF, WBUF>& W,
 // 2^20 rows): merged backward behind the activation layer 1,606 -> 1,368 us;
 // untruncated backward of 29,997 lookups (m = 32 fp32) 322 -> 247 us; 4,096
 // lookups at K = 4 21.3 -> 19.6 us.
-template <int DT, int M, bool TH, int KS, int NBUF, int WBUF>
+template <int DT, int M, int TH, int KS, int NBUF, int WBUF>
 __device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS, NBUF, WBUF>& W, int buf, const Tables& T,
                                            int count, const char* __restrict__ tb, const float* __restrict__ gout, int64_t l,
-                                           int lane, float* __restrict__ gq, const float* __restrict__ zin,
+                                           int lane, float* gq, const float* __restrict__ zin,
                                            const Params& P) {
   constexpr int R = chunk_rows<KS>();  // rows per chunk of the row loop
   using G = RowGeom<DT, M, R>;
@@ -190,13 +190,16 @@ __device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS, NBU
 // sorts last).
 // gate (nullable): the merged scatter's device-side choice -- this kernel does
 // nothing when the batch is merged instead (see merge_chosen).
+// TH: the lookups' input; z the activation layer's own input, for its chain.
+// IN_STAGED: q is grad_in itself, lookup l's record at the start of its row,
+// read by the wave that writes the row afterwards.
 // ORD: visit the lookups in the order perm (as k_forward).
 // SAVED: the forward's lists (NbrList saved) replace the search.
-template <int DT, int M, bool EMIT, bool TH, int KS = NB, bool ORD = false, bool SAVED = false>
-__global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH ? 3 : 4) k_backward(const float* __restrict__ q, Params P,
+template <int DT, int M, bool EMIT, int TH, int KS = NB, bool ORD = false, bool SAVED = false>
+__global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == IN_THETA ? 3 : 4) k_backward(const float* q, const float* __restrict__ z, Params P,
                                                       const void* __restrict__ table,
                                                       const float* __restrict__ gout, float* __restrict__ gtab,
-                                                      float* __restrict__ gq, uint32_t* __restrict__ pair_key,
+                                                      float* gq, uint32_t* __restrict__ pair_key,
                                                       uint2* __restrict__ pair_val, const uint32_t* __restrict__ gate,
                                                       const uint32_t* __restrict__ perm, NbrList saved) {
   static_assert(!EMIT || KS == NB, "the sorted scatter takes lists of 32");
@@ -211,7 +214,7 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH ? 3
   // scatter and query gradient of list buf, which is lookup l's (ok: inside the batch)
   auto finish = [&](const Frame& F, int buf, int count, int64_t l, bool ok) {
     if (!EMIT && gtab && count > 0) scatter_atomic<M, KS>(W, buf, count, gout, l, gtab, lane);
-    if (gq && ok) grad_query<DT, M, TH, KS>(F, W, buf, S.tab, count, tb, gout, l, lane, gq, q, P);
+    if (gq && ok) grad_query<DT, M, TH, KS>(F, W, buf, S.tab, count, tb, gout, l, lane, gq, z, P);
     if (EMIT && gtab && lane < NB && ok) {
       const int32_t s = W.nbr[buf][lane].slot;
       pair_key[l * NB + lane] = s >= 0 ? (uint32_t)s : P.N;
@@ -248,7 +251,7 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH ? 3
   } else {
     static_assert(KS == NB || (!TH && !ORD && !SAVED && !EMIT), "other lists serve the plain lookup");
     Search<KS> srch(P, S.tab, W, S.tile, c.wave, lane);
-    const QuadCtx<false> Q(P, lane);
+    const QuadCtx<IN_QUERY> Q(P, lane);
     Frame* FR = S.frames[c.wave];
     for (int t0 = 0; t0 < c.nl; t0 += TILE) {
       const int nt = min(TILE, c.nl - t0);

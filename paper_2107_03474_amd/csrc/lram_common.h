@@ -58,6 +58,7 @@ struct Params {
   float twoK[8];     // torus side at the Lambda scale
   uint32_t N;
   int32_t lpw;       // lookups per wave (1..64)
+  int32_t stage;     // floats per staged record (input IN_STAGED)
   int64_t L;
   double cK[8];      // K_i / (2 pi): torus coordinate per radian of arg z_i (activation layer)
 };

@@ -73,8 +73,8 @@ __global__ void __launch_bounds__(THREADS, 4) k_neighbors(const float* __restric
   WaveCtx c;
   if constexpr (KS == NB) {
     wave_ctx(P, c);
-    TileInput<false, false> in(q, nullptr, c.base, c.nl, P, c.lane);
-    TileSearch<false, 2> ts(P, S, c.wave, c.lane);
+    TileInput<IN_QUERY, false> in(q, nullptr, c.base, c.nl, P, c.lane);
+    TileSearch<IN_QUERY, 2> ts(P, S, c.wave, c.lane);
     for (int t0 = 0; t0 < c.nl; t0 += TILE) {
       const int nt = min(TILE, c.nl - t0);
       ts.frames(in.v, in.have, nt);
@@ -96,7 +96,7 @@ __global__ void __launch_bounds__(THREADS, 4) k_neighbors(const float* __restric
   } else {
     if (!wave_ctx(P, c)) return;
     Search<KS> srch(P, S.tab, S.wave[c.wave], S.tile, c.wave, c.lane);
-    const QuadCtx<false> Q(P, c.lane);
+    const QuadCtx<IN_QUERY> Q(P, c.lane);
     Frame* FR = S.frames[c.wave];
     for (int t0 = 0; t0 < c.nl; t0 += TILE) {
       const int nt = min(TILE, c.nl - t0);
@@ -208,7 +208,7 @@ __device__ __forceinline__ void fwd_accumulate(const WaveLds<KS, NBUF, WBUF>& W,
 // its columns (one fp32, two bf16); the bits below are plain sums.
 template <int DT, int M>
 __device__ __forceinline__ void fwd_store(int lane, int64_t l, float (&acc)[FwdGeom<DT, M>::EPL],
-                                          void* __restrict__ out, bool ok = true) {
+                                          void* out, bool ok = true) {
   using G = FwdGeom<DT, M>;
   constexpr int Q = G::EPL / 4;
 #pragma unroll
@@ -231,7 +231,7 @@ __device__ __forceinline__ void fwd_store(int lane, int64_t l, float (&acc)[FwdG
 
 template <int DT, int M>
 __device__ __forceinline__ void fwd_consume(const WaveLds<NB, 2, 4>& W, int wb, int lane, int64_t l,
-                                            const uint4 (&v)[FwdGeom<DT, M>::NI], void* __restrict__ out,
+                                            const uint4 (&v)[FwdGeom<DT, M>::NI], void* out,
                                             bool ok = true) {
   float acc[FwdGeom<DT, M>::EPL];
 #pragma unroll
@@ -240,15 +240,16 @@ __device__ __forceinline__ void fwd_consume(const WaveLds<NB, 2, 4>& W, int wb, 
   fwd_store<DT, M>(lane, l, acc, out, ok);
 }
 
-// TH: the input is the activation layer's z [L][16] instead of q [L][8]; the
-// scale s is folded into the weights by the search.
+// TH: the lookups' input; the activation layer's scale s is folded into the
+// weights by the search.  IN_STAGED: q is the output itself, lookup l's record
+// at the start of its row, read by the wave that writes the row afterwards.
 // ORD: visit the lookups in the order perm (position -> lookup, e.g. sorted
 // by closest lattice point, so that lookups sharing rows run close together
 // in time and on the same XCD); outputs still go to the lookup's row.
 // SAVE: write every lookup's list for the backward (NbrList).
-template <int DT, int M, bool TH, bool ORD = false, bool SAVE = false>
-__global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH ? 3 : 4) k_forward(const float* __restrict__ q, Params P,
-                                                     const void* __restrict__ table, void* __restrict__ out,
+template <int DT, int M, int TH, bool ORD = false, bool SAVE = false>
+__global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == IN_THETA ? 3 : 4) k_forward(const float* q, Params P,
+                                                     const void* __restrict__ table, void* out,
                                                      const uint32_t* __restrict__ perm, NbrList save) {
   using G = FwdGeom<DT, M>;
   __shared__ SearchLds<NB, 2, 4> S;
@@ -304,7 +305,7 @@ __global__ void __launch_bounds__(THREADS) k_forward_k(const float* __restrict__
   if (!wave_ctx(P, c)) return;
   Search<KS> srch(P, S.tab, S.wave[c.wave], S.tile, c.wave, c.lane);
   WaveLds<KS>& W = S.wave[c.wave];
-  const QuadCtx<false> Q(P, c.lane);
+  const QuadCtx<IN_QUERY> Q(P, c.lane);
   Frame* FR = S.frames[c.wave];
   const char* tb = reinterpret_cast<const char*>(table);
   for (int t0 = 0; t0 < c.nl; t0 += TILE) {

@@ -43,7 +43,7 @@ __device__ __forceinline__ uint32_t cell_location(const float (&qq)[8], const Pa
 // SORT_HIST_COPIES of ghist, cleared).  The workgroups also clear the sort's
 // look-back states, clear[0, nclear), which no pass reads before this kernel
 // ends.  Each lookup's input is loaded one lookup ahead.
-template <bool TH>
+template <int TH>
 __global__ void __launch_bounds__(THREADS) k_cell_key(const float* __restrict__ q, Params P,
                                                       uint32_t* __restrict__ key, int passes,
                                                       uint32_t* __restrict__ ghist, uint32_t* __restrict__ clear,
@@ -59,12 +59,12 @@ __global__ void __launch_bounds__(THREADS) k_cell_key(const float* __restrict__ 
   const int64_t chunk = (P.L + gridDim.x - 1) / gridDim.x;
   const int64_t b = (int64_t)blockIdx.x * chunk, e = min<int64_t>(P.L, b + chunk);
   float4 v[in_vec4<TH>()];
-  if (b + t < e) load_input<TH>(q + (b + t) * in_stride<TH>(), v);
+  if (b + t < e) load_input<TH>(q + (b + t) * in_stride<TH>(P), v);
   for (int64_t l = b + t; l < e; l += THREADS) {
     float4 cur[in_vec4<TH>()];
 #pragma unroll
     for (int k = 0; k < in_vec4<TH>(); ++k) cur[k] = v[k];
-    if (l + THREADS < e) load_input<TH>(q + (l + THREADS) * in_stride<TH>(), v);
+    if (l + THREADS < e) load_input<TH>(q + (l + THREADS) * in_stride<TH>(P), v);
     float qq[8], scale;
     query_from<TH>(cur, P, qq, scale);
     const uint32_t loc = cell_location(qq, P);
@@ -82,16 +82,18 @@ __global__ void __launch_bounds__(THREADS) k_cell_key(const float* __restrict__ 
   }
 }
 
-// Activation layer coordinates: q[l] (8 fp32) and scale s[l] as the lookups see them.
-__global__ void __launch_bounds__(THREADS) k_theta_coords(const float* __restrict__ z, Params P,
-                                                          float* __restrict__ q, float* __restrict__ s) {
+// Activation layer coordinates as the lookups see them: q (8 fp32) and the
+// scale s of lookup l at q + l * qs and s + l * ss (s nullable).
+__global__ void __launch_bounds__(THREADS) k_theta_coords(const float* __restrict__ z, Params P, float* __restrict__ q,
+                                                          int qs, float* __restrict__ s, int ss) {
   const int64_t l = (int64_t)blockIdx.x * THREADS + threadIdx.x;
   if (l >= P.L) return;
   float qq[8], scale;
-  load_query<true>(z + l * 16, P, qq, scale);
-  reinterpret_cast<float4*>(q + l * 8)[0] = make_float4(qq[0], qq[1], qq[2], qq[3]);
-  reinterpret_cast<float4*>(q + l * 8)[1] = make_float4(qq[4], qq[5], qq[6], qq[7]);
-  if (s) s[l] = scale;
+  load_query<IN_THETA>(z + l * 16, P, qq, scale);
+  float4* o = reinterpret_cast<float4*>(q + l * qs);
+  o[0] = make_float4(qq[0], qq[1], qq[2], qq[3]);
+  o[1] = make_float4(qq[4], qq[5], qq[6], qq[7]);
+  if (s) s[l * ss] = scale;
 }
 
 // Number of positions whose sorted key equals a neighbour's, in COUNT_COPIES
@@ -224,11 +226,12 @@ constexpr int merge_waves_per_simd() {
 // point with a neighbour in the order (queries spread thinly over the torus)
 // has little to merge: it scatters with per-lookup atomics instead.
 // SAVED: the forward's lists (NbrList saved) replace the search.
-template <int DT, int M, bool TH, int KS = NB, bool SAVED = false>
-__global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS>())) k_backward_merged(const float* __restrict__ q, Params P,
+template <int DT, int M, int TH, int KS = NB, bool SAVED = false>
+__global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS>())) k_backward_merged(const float* q,
+                                                             const float* __restrict__ z, Params P,
                                                              const void* __restrict__ table,
                                                              const float* __restrict__ gout,
-                                                             float* __restrict__ gtab, float* __restrict__ gq,
+                                                             float* __restrict__ gtab, float* gq,
                                                              const uint32_t* __restrict__ skey,
                                                              const uint32_t* __restrict__ perm,
                                                              const uint32_t* __restrict__ gate, NbrList saved) {
@@ -253,7 +256,7 @@ __global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS>())) 
     // scatter or keep the pairs of list buf (the wave's i-th lookup, l), and its query gradient
     auto finish = [&](const Frame& F, int buf, int count, int i, int64_t l) {
       if (!merge && count > 0) scatter_atomic<M, KS>(W, buf, count, gout, l, gtab, lane);
-      if (gq && l < P.L) grad_query<DT, M, TH, KS>(F, W, buf, S.b.search.tab, count, tb, gout, l, lane, gq, q, P);
+      if (gq && l < P.L) grad_query<DT, M, TH, KS>(F, W, buf, S.b.search.tab, count, tb, gout, l, lane, gq, z, P);
       if (merge && !COMPACT) {
 #pragma unroll
         for (int j = lane; j < KS; j += WAVE) {

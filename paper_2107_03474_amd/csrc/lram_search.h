@@ -35,20 +35,32 @@ __device__ __forceinline__ void d8_round(const float (&y)[8], int (&r)[8]) {
   }
 }
 
-// Input float4s per lookup: q (8 floats) or z (16, the activation layer).
-template <bool TH>
-constexpr int in_vec4() { return TH ? 4 : 2; }
+// The lookups' input (the template parameter TH of everything that reads it):
+// q [L][8]; z [L][16] of the activation layer (Sec. 2.3), turned into q where
+// it is read; or q and the output scale s of the activation layer as
+// k_theta_coords left them, in records of Params::stage floats (q in the first
+// 8, s in the 9th).  The arguments of z take 8 fp64 atan2 and square roots per
+// lookup: in front of a tile's search no row loads cover that latency, and
+// their registers cost a wave per SIMD, so large batches have them formed by a
+// kernel of their own, in rows of the output that the lookups write last
+// (forward of 262,144 lookups, m = 64 fp32: 338 -> 281 us, of 524,288, m = 64
+// bf16: 505 -> 454 us, k_theta_coords' 17 and 25 us included).
+enum : int { IN_QUERY = 0, IN_THETA = 1, IN_STAGED = 2 };
+
+// Input float4s per lookup.
+template <int TH>
+constexpr int in_vec4() { return TH == IN_THETA ? 4 : 2; }
 
 // The query of one lookup and its output scale, from the lookup's input
-// vectors v.  TH = false: q itself (8 floats), scale 1.  TH = true, the
+// vectors v.  IN_QUERY: q itself (8 floats), scale 1.  IN_THETA, the
 // activation layer of Sec. 2.3: z_i = in[2i] + i in[2i+1], q_i = (K_i / 2 pi)
 // arg z_i formed in fp64 and rounded once to fp32, scale (sum_i 1/|z_i|)^-1 (0
 // when some z_i = 0); a non-finite input gives a NaN query (empty neighbour
 // list) and scale 0.
-template <bool TH>
+template <int TH>
 __device__ __forceinline__ void query_from(const float4 (&v)[in_vec4<TH>()], const Params P, float (&qq)[8],
                                            float& scale) {
-  if constexpr (!TH) {
+  if constexpr (TH != IN_THETA) {
     qq[0] = v[0].x; qq[1] = v[0].y; qq[2] = v[0].z; qq[3] = v[0].w;
     qq[4] = v[1].x; qq[5] = v[1].y; qq[6] = v[1].z; qq[7] = v[1].w;
     scale = 1.0f;
@@ -72,13 +84,13 @@ __device__ __forceinline__ void query_from(const float4 (&v)[in_vec4<TH>()], con
   }
 }
 
-template <bool TH>
+template <int TH>
 __device__ __forceinline__ void load_input(const float* __restrict__ in, float4 (&v)[in_vec4<TH>()]) {
 #pragma unroll
   for (int k = 0; k < in_vec4<TH>(); ++k) v[k] = reinterpret_cast<const float4*>(in)[k];
 }
 
-template <bool TH>
+template <int TH>
 __device__ __forceinline__ void load_query(const float* __restrict__ in, const Params P, float (&qq)[8],
                                            float& scale) {
   float4 v[in_vec4<TH>()];
@@ -130,7 +142,7 @@ __device__ __forceinline__ bool closest_point(const float (&qq)[8], bool have, c
 
 // Lane constants of phase A: lane = 4 * (lookup of the tile) + quarter; a
 // quarter holds the original coordinates 2 * quarter and 2 * quarter + 1.
-template <bool TH>
+template <int TH>
 struct QuadCtx {
   int n, kq;
   float tk0, tk1;    // torus sides at the Lambda scale
@@ -144,7 +156,7 @@ struct QuadCtx {
     for (int k = 1; k < 4; ++k) {
       tk0 = kq == k ? P.twoK[2 * k] : tk0;
       tk1 = kq == k ? P.twoK[2 * k + 1] : tk1;
-      if constexpr (TH) {
+      if constexpr (TH == IN_THETA) {
         ck0 = kq == k ? P.cK[2 * k] : ck0;
         ck1 = kq == k ? P.cK[2 * k + 1] : ck1;
       }
@@ -154,20 +166,24 @@ struct QuadCtx {
 
 // Input values of one quarter of a lookup: q_{2k}, q_{2k+1}, or z_{2k}, z_{2k+1}
 // as (Re, Im, Re, Im).
-template <bool TH>
+template <int TH>
 struct QuadIn {
-  float v[TH ? 4 : 2];
+  float v[TH == IN_THETA ? 4 : 2];
+  float s;  // IN_STAGED: the output scale
 };
 
-template <bool TH>
-__device__ __forceinline__ QuadIn<TH> load_quad(const float* __restrict__ in, size_t l, int kq) {
+template <int TH>
+__device__ __forceinline__ QuadIn<TH> load_quad(const float* in, size_t l, int kq, int stage) {
   QuadIn<TH> o;
-  if constexpr (TH) {
+  o.s = 1.0f;
+  if constexpr (TH == IN_THETA) {
     const float4 a = reinterpret_cast<const float4*>(in + l * 16)[kq];
     o.v[0] = a.x; o.v[1] = a.y; o.v[2] = a.z; o.v[3] = a.w;
   } else {
-    const float2 a = reinterpret_cast<const float2*>(in + l * 8)[kq];
+    const float* r = in + l * (size_t)(TH == IN_STAGED ? stage : 8);
+    const float2 a = reinterpret_cast<const float2*>(r)[kq];
     o.v[0] = a.x; o.v[1] = a.y;
+    if constexpr (TH == IN_STAGED) o.s = r[8];
   }
   return o;
 }
@@ -208,13 +224,13 @@ __device__ __forceinline__ void d8_round_quad(float y0, float y1, int kq, int& r
 // lane's quarter; have: the lookup exists).  The frames' sel words hold -z_r/2
 // afterwards; returns this lane's two v_perm selectors, which finish_frames
 // puts there once the selection has read z.
-template <bool TH>
+template <int TH>
 __device__ __forceinline__ uint2 make_frames(const QuadIn<TH>& in, bool have, const QuadCtx<TH>& Q, Frame* fr) {
   const int kq = Q.kq, i0 = 2 * kq, i1 = i0 + 1;
   const int quad0 = 4 * Q.n;
-  float q0, q1, scale = 1.0f;
+  float q0, q1, scale = in.s;
   bool fin = have;
-  if constexpr (TH) {
+  if constexpr (TH == IN_THETA) {
     const double a0 = in.v[0], b0 = in.v[1], a1 = in.v[2], b1 = in.v[3];
     fin = fin && isfinite(in.v[0]) && isfinite(in.v[1]) && isfinite(in.v[2]) && isfinite(in.v[3]);
     double inv = 1.0 / sqrt(a0 * a0 + b0 * b0) + 1.0 / sqrt(a1 * a1 + b1 * b1);
@@ -1038,7 +1054,7 @@ __device__ __forceinline__ uint32_t tile_select(const Frame* fr, const TileLds<N
 
 // Everything the kernels need of the search of the closest 32: a tile's
 // frames and selection, then pairs of its lookups.
-template <bool TH, int WBUF>
+template <int TH, int WBUF>
 struct TileSearch {
   using SL = SearchLds<NB, 2, WBUF>;
   SL& S;
@@ -1131,17 +1147,19 @@ struct TileSearch {
   }
 };
 
-// Input floats per lookup: q (8) or z (16, the activation layer).
-template <bool TH>
-constexpr int in_stride() { return TH ? 16 : 8; }
+// Input floats per lookup.
+template <int TH>
+__device__ __forceinline__ int in_stride(const Params& P) {
+  return TH == IN_STAGED ? P.stage : (TH == IN_THETA ? 16 : 8);
+}
 
 // The input of this lane's quarter of the tile at [base, base + nl) of the
 // lookups, or of the positions of the order perm (l: the quarter's lookup; an
 // index outside [0, L) -- an order not written for these lookups -- gets an
 // empty list, and the kernels write nothing for it).  Returns whether the
 // lookup exists.
-template <bool TH, bool ORD>
-__device__ __forceinline__ bool load_tile(const float* __restrict__ in, const uint32_t* __restrict__ perm, int64_t base,
+template <int TH, bool ORD>
+__device__ __forceinline__ bool load_tile(const float* in, const uint32_t* __restrict__ perm, int64_t base,
                                           int nl, const Params& P, int lane, QuadIn<TH>& v, uint32_t& l) {
   const int n = lane >> 2;
   bool have = n < nl;
@@ -1154,13 +1172,13 @@ __device__ __forceinline__ bool load_tile(const float* __restrict__ in, const ui
     src = have ? l : 0;
     if (n >= nl) l = 0xFFFFFFFFu;
   }
-  v = load_quad<TH>(in, src, lane & 3);
+  v = load_quad<TH>(in, src, lane & 3, P.stage);
   return have;
 }
 
 // The tiles of a wave's lookups [base, base + nl): each tile's input is loaded
 // one tile ahead, the first before the workgroup's barrier.
-template <bool TH, bool ORD>
+template <int TH, bool ORD>
 struct TileInput {
   const float* in;
   const uint32_t* perm;
@@ -1169,7 +1187,7 @@ struct TileInput {
   QuadIn<TH> v;
   uint32_t l, next_l;  // this lane's quarter's lookup of the current and of the next tile (ORD)
   bool have;
-  __device__ TileInput(const float* __restrict__ i, const uint32_t* __restrict__ pm, int64_t b, int n, const Params& P,
+  __device__ TileInput(const float* i, const uint32_t* __restrict__ pm, int64_t b, int n, const Params& P,
                        int ln)
       : in(i), perm(pm), base(b), nl(n), lane(ln), l(0), next_l(0), have(false) {
     if (nl > 0) have = load_tile<TH, ORD>(in, perm, base, min(TILE, nl), P, lane, v, next_l);
@@ -1190,11 +1208,11 @@ struct TileInput {
 
 // Frames of a tile for the general search (lists other than the closest 32).
 __device__ __forceinline__ void tile_frames(const float* __restrict__ q, int64_t base, int nl, const Params& P, Frame* fr,
-                                            const QuadCtx<false>& Q, int lane) {
-  QuadIn<false> v;
+                                            const QuadCtx<IN_QUERY>& Q, int lane) {
+  QuadIn<IN_QUERY> v;
   uint32_t l;
-  const bool have = load_tile<false, false>(q, nullptr, base, nl, P, lane, v, l);
-  const uint2 sel = make_frames<false>(v, have, Q, fr);
+  const bool have = load_tile<IN_QUERY, false>(q, nullptr, base, nl, P, lane, v, l);
+  const uint2 sel = make_frames<IN_QUERY>(v, have, Q, fr);
   wave_lds_sync();
   finish_frames(sel, lane, fr);
   wave_lds_sync();

@@ -17,8 +17,8 @@ __global__ void __launch_bounds__(THREADS, 4) k_access_hist(const float* __restr
   __shared__ SearchLds<> S;
   WaveCtx c;
   wave_ctx(P, c);
-  TileInput<false, false> in(q, nullptr, c.base, c.nl, P, c.lane);
-  TileSearch<false, 2> ts(P, S, c.wave, c.lane);
+  TileInput<IN_QUERY, false> in(q, nullptr, c.base, c.nl, P, c.lane);
+  TileSearch<IN_QUERY, 2> ts(P, S, c.wave, c.lane);
   for (int t0 = 0; t0 < c.nl; t0 += TILE) {
     const int nt = min(TILE, c.nl - t0);
     ts.frames(in.v, in.have, nt);
@@ -41,8 +41,8 @@ __global__ void __launch_bounds__(THREADS, 4) k_mark_touched(const float* __rest
   __shared__ SearchLds<> S;
   WaveCtx c;
   wave_ctx(P, c);
-  TileInput<false, false> in(q, nullptr, c.base, c.nl, P, c.lane);
-  TileSearch<false, 2> ts(P, S, c.wave, c.lane);
+  TileInput<IN_QUERY, false> in(q, nullptr, c.base, c.nl, P, c.lane);
+  TileSearch<IN_QUERY, 2> ts(P, S, c.wave, c.lane);
   for (int t0 = 0; t0 < c.nl; t0 += TILE) {
     const int nt = min(TILE, c.nl - t0);
     ts.frames(in.v, in.have, nt);

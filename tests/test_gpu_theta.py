@@ -166,3 +166,41 @@ def test_theta_workload(name):
     Gs = G.reshape(-1, w.m)[torch.from_numpy(idx).to(DEV)].cpu().numpy()
     gz_ref = oracle.theta_grad_z(zf[idx], w.K, nb, rows, s, Gs)
     assert _rel_rows(gz.reshape(-1, 16)[torch.from_numpy(idx).to(DEV)].cpu().numpy(), gz_ref).max() <= 1e-5
+
+
+@pytest.mark.parametrize("m,dtype", [(32, torch.float32), (32, torch.bfloat16), (64, torch.float32)])
+@pytest.mark.parametrize("L", [16384, 16384 + 77, 131072 + 3])
+def test_staged_coordinates(L, m, dtype):
+    """From 16,384 lookups on the coordinates are formed by a kernel of their own in the rows of the result; below
+    they are formed inside the lookup kernels.  Both give the same results (the scale's fp64 sum is taken in another
+    order: one fp32 unit of s, 6e-8 of a row, and one bf16 rounding of the output where it lies at a boundary), for
+    every scatter and also where the gradient is written over z itself."""
+    _say("theta staged L=%d m=%d %s" % (L, m, dtype))
+    K = (8, 4, 4, 6, 4, 4, 4, 4)
+    N = int(np.prod(K))
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    z = torch.randn((L, 16), generator=g, device=DEV)
+    z[5, 4] = float("nan")
+    z[9] = 0.0
+    z[11, 2:4] = 0.0
+    table = (torch.randn((N, m), generator=g, device=DEV) * 0.02).to(dtype)
+    G = torch.randn((L, m), generator=g, device=DEV)
+    cuts = list(range(0, L, 16000)) + [L]
+    out = lram.theta_forward(z, table, K)
+    ref = torch.cat([lram.theta_forward(z[a:b], table, K) for a, b in zip(cuts, cuts[1:])])
+    bar = 1e-6 if dtype == torch.float32 else 4e-3
+    d = (out.double() - ref.double()).norm(dim=1)
+    assert (d <= bar * ref.double().norm(dim=1)).all()
+    gt = torch.zeros((N, m), device=DEV)
+    parts = []
+    for a, b in zip(cuts, cuts[1:]):
+        parts.append(lram.theta_backward(z[a:b], table, K, G[a:b], grad_table=gt, mode="atomic")[1])
+    gz = torch.cat(parts)
+    for mode in ("atomic", "merged", "sorted"):
+        t2, z2 = lram.theta_backward(z, table, K, G, mode=mode)
+        assert ((z2.double() - gz.double()).norm(dim=1) <= 2e-6 * gz.double().norm(dim=1)).all(), mode
+        assert ((t2.double() - gt.double()).norm(dim=1) <= 2e-5 * gt.double().norm(dim=1).clamp(min=1e-9)).all(), mode
+    own = z.clone()
+    lram.theta_backward(own, table, K, G, grad_z=own, mode="atomic")
+    assert ((own.double() - gz.double()).norm(dim=1) <= 2e-6 * gz.double().norm(dim=1)).all()
