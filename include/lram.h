@@ -76,7 +76,10 @@ typedef enum {
   LRAM_SCATTER_ATOMIC = 0, /* fp32 atomic adds straight into grad_table */
   LRAM_SCATTER_SORTED = 1, /* sort (slot, lookup) pairs, one read-modify-write per touched row;
                               bit-reproducible from call to call */
-  LRAM_SCATTER_MERGED = 2, /* order lookups by their closest lattice point, merge equal slots within
+  LRAM_SCATTER_MERGED = 2, /* tables small against the batch's pairs (65,536 to 524,288 lookups of k = 32, at
+                              least 2 (m = 64) or 4 (m = 32) pairs per row, and the whole workspace given): sort
+                              the (slot, lookup) pairs, one atomic row per run of equal slots; otherwise
+                              order lookups by their closest lattice point, merge equal slots within
                               each batch of consecutive lookups (64 for lists of up to 32, 32 for
                               longer ones), one atomic row per distinct slot;
                               when fewer than a tenth of the lookups share their closest point with
@@ -168,7 +171,8 @@ int lram_forward(const float* q, int64_t B, int64_t H, const int32_t K[8], const
  * lram_backward_workspace_bytes -- device workspace needed by lram_backward
  * (and lram_backward_k, lram_theta_backward) for L = B*H lookups in the given
  * scatter mode (0 for LRAM_SCATTER_ATOMIC; the same for every k; the merged
- * scatter's workspace is an order buffer, lram_order_bytes).
+ * scatter can do with an order buffer, lram_order_bytes, and asks for 768 bytes
+ * per lookup from 65,536 to 524,288 lookups, where it may sort the pairs).
  */
 int lram_backward_workspace_bytes(int64_t B, int64_t H, int32_t m, int mode, size_t* bytes);
 
@@ -200,8 +204,9 @@ int lram_scatter_mode_resolved(int64_t B, int64_t H, int mode, int* resolved);
  * never address outside grad_table.  Without them the search is recomputed
  * from q.
  * workspace/ws_bytes: device buffer, 256-byte aligned, of at least
- * lram_backward_workspace_bytes (may be NULL for the atomic mode, and for the
- * merged mode when an order is given); its contents on entry do not matter,
+ * lram_backward_workspace_bytes (the merged mode also takes lram_order_bytes;
+ * may be NULL for the atomic mode, and for the merged mode when an order is
+ * given); its contents on entry do not matter,
  * and calls that may overlap need workspaces of their own.
  * LRAM_SCATTER_SORTED is bit-reproducible: the same inputs give the same
  * grad_table bits on every call (every row's sum is formed in one fixed

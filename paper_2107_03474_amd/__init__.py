@@ -318,7 +318,9 @@ def backward(q: torch.Tensor, table: torch.Tensor, K: Sequence[int], grad_out: t
              _dev(gq, "grad_q", torch.float32, q.shape, like=q) if gq is not None else None)
     mode_i = _MODES[mode]
     ws_bytes = backward_workspace_bytes(B, H, m, mode_i)
-    merged_with_order = order is not None and resolved_mode(B, H, mode_i) == "merged"
+    # the merged scatter takes an order in place of its own sort, and a larger
+    # workspace than an order where it may sort the pairs themselves
+    merged_with_order = order is not None and resolved_mode(B, H, mode_i) == "merged" and ws_bytes <= order.numel()
     if ws_bytes and workspace is None and not merged_with_order:
         workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
     if k != NB:

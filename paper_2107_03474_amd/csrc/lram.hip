@@ -41,8 +41,8 @@
 #include "lram_common.h"
 #include "lram_search.h"
 #include "lram_lookup.h"
-#include "lram_backward.h"
 #include "lram_sort.h"
+#include "lram_backward.h"
 #include "lram_merge.h"
 #include "lram_train.h"
 
@@ -104,6 +104,7 @@ int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t
   P->N = (uint32_t)N;
   P->L = *L;
   P->stage = 0;
+  P->passes = 0;
   P->lpw = lookups_per_wave(*L, true);
   return LRAM_OK;
 }
@@ -238,8 +239,8 @@ int radix_passes(uint32_t N) {
 // Stable LSD radix sort of the n (key, payload) pairs in (ka, va), keys in
 // [0, N]: the result is in (ka, va) after an even number of passes and in
 // (kb, vb) after an odd one.  IDENT: the payload of element i is i (va is
-// not read).  Kernels: clear the scratch, count every pass's digits, then one
-// single-pass scatter per digit.
+// not read).  One single-pass scatter per digit; the scratch is cleared and
+// every pass's digits are counted by then.
 template <typename V, bool IDENT, typename S>
 int radix_passes_run(const Radix<V>& r, int passes, hipStream_t s) {
   uint32_t* kin = r.ka;
@@ -264,23 +265,22 @@ int radix_passes_run(const Radix<V>& r, int passes, hipStream_t s) {
   return LRAM_OK;
 }
 
-// Stable LSD radix sort of the n (key, payload) pairs in (ka, va), keys in
-// [0, N]: the result is in (ka, va) after an even number of passes and in
-// (kb, vb) after an odd one.  IDENT: the payload of element i is i (va is
-// not read).  Kernels: clear the scratch, count every pass's digits, then one
-// single-pass scatter per digit (32-bit look-back states below 2^30 elements).
-template <typename V, bool IDENT>
-int radix_sort(const Radix<V>& r, uint32_t N, hipStream_t s) {
-  if (r.n <= 0) return LRAM_OK;
-  const int passes = radix_passes(N);
-  const bool small = r.n < SORT_SMALL_STATES;
-  const int64_t words = SORT_HDR_WORDS + (int64_t)passes * r.states * RADIX * (small ? 1 : 2);
+// Clears the scratch of a sort (digit counts and look-back states); the kernel
+// that forms the keys then counts their digits into hdr.
+template <typename V>
+int clear_sort(const Radix<V>& r, int passes, hipStream_t s) {
+  const int64_t words = SORT_HDR_WORDS + (int64_t)passes * r.states * RADIX * (r.n < SORT_SMALL_STATES ? 1 : 2);
   const int64_t zb = (words + THREADS - 1) / THREADS;
   hipLaunchKernelGGL(k_zero_words, dim3((unsigned)(zb < 1024 ? zb : 1024)), dim3(THREADS), 0, s, r.hdr, words);
-  hipLaunchKernelGGL(k_digit_hist, dim3((unsigned)(r.tiles < 1024 ? r.tiles : 1024)), dim3(THREADS), 0, s,
-                     (const uint32_t*)r.ka, r.n, passes, r.hdr);
-  if (int rc = launched()) return rc;
-  return small ? radix_passes_run<V, IDENT, uint32_t>(r, passes, s) : radix_passes_run<V, IDENT, uint64_t>(r, passes, s);
+  return launched();
+}
+
+// The passes of a sort whose digits are counted (32-bit look-back states below
+// 2^30 elements).
+template <typename V, bool IDENT>
+int sort_counted(const Radix<V>& r, int passes, hipStream_t s) {
+  return r.n < SORT_SMALL_STATES ? radix_passes_run<V, IDENT, uint32_t>(r, passes, s)
+                                 : radix_passes_run<V, IDENT, uint64_t>(r, passes, s);
 }
 
 // The lookup order of lram_order, which is also the merged scatter's
@@ -355,6 +355,47 @@ size_t sorted_layout(int64_t L, int32_t m, SortedWs* ws, char* base) {
   return c.off;
 }
 
+// Workspace of the merged scatter's sorted runs (see RUNS_MAX): the sort of the
+// 32 L (location, (lookup, w)) pairs.
+size_t runs_layout(int64_t L, Radix<uint2>* r, char* base) {
+  Carver c{base};
+  const int64_t n = L * NB;
+  char* ka = c.take(n * 4);
+  char* kb = c.take(n * 4);
+  char* va = c.take(n * 8);
+  char* vb = c.take(n * 8);
+  carve_radix_scratch<uint2>(n, c, r);
+  if (r) {
+    r->ka = (uint32_t*)ka;
+    r->kb = (uint32_t*)kb;
+    r->va = (uint2*)va;
+    r->vb = (uint2*)vb;
+  }
+  return c.off;
+}
+
+// The merged scatter sorts the pairs themselves (runs of one location, k_run_sum)
+// where the table is small against them: row atomics then number about one per
+// touched row, not one per row and batch of 64 lookups.  Microseconds of a
+// backward pass of 262,144 lookups (8.4 M pairs), batch merge / sorted runs:
+//   m = 64, 2^18 rows uniform 1,624 / 859, clustered 1,287 / 851; 2^20 1,733 / 913, 1,379 / 931;
+//           2^22 1,873 / 1,523, 1,423 / 1,313; 2^24 1,942 / 2,280, 1,414 / 1,730
+//   m = 32, 2^18 846 / 582, 682 / 570; 2^20 936 / 610, 730 / 604; 2^22 919 / 875, 733 / 782
+// so the line lies at two pairs per row (m = 64) and four (m = 32; its row
+// atomics cost half).  Lookups around very few centres (64) merge better by
+// batches (657 / 804 at 2^18 rows): the queries are not known here.
+// The runs need their workspace (768 bytes per lookup, 410 MB at RUNS_MAX); an
+// order-sized one, and batches outside [RUNS_MIN, RUNS_MAX], keep the batch merge.
+constexpr int64_t RUNS_MIN = 65536, RUNS_MAX = int64_t(1) << 19;
+bool runs_chosen(int64_t L, uint32_t N, int32_t m) {
+  return L >= RUNS_MIN && L <= RUNS_MAX && L * NB >= (m == 64 ? 2 : 4) * (int64_t)N;
+}
+
+size_t merged_bytes(int64_t L) {
+  const size_t order = order_layout(L, nullptr, nullptr);
+  return L >= RUNS_MIN && L <= RUNS_MAX ? std::max(order, runs_layout(L, nullptr, nullptr)) : order;
+}
+
 // Fills an order: closest-point keys, the stable sort (its result lands in
 // sort.ka / sort.va whatever the number of passes), and the merge gate's count.
 template <int TH>
@@ -406,19 +447,19 @@ void launch_atomic(const float* q, const float* z, const Params& Pq, const void*
   if constexpr (TH == IN_QUERY && KS == NB) {
     if (perm && saved.on())
       hipLaunchKernelGGL((k_backward<DT, M, false, IN_QUERY, NB, true, true>), grid, b, 0, s, q, z, P, table, g, gt, gq, nk,
-                         nv, gate, perm, saved);
+                         nv, gate, perm, saved, nk);
     else if (perm)
       hipLaunchKernelGGL((k_backward<DT, M, false, IN_QUERY, NB, true, false>), grid, b, 0, s, q, z, P, table, g, gt, gq,
-                         nk, nv, gate, perm, saved);
+                         nk, nv, gate, perm, saved, nk);
     else if (saved.on())
       hipLaunchKernelGGL((k_backward<DT, M, false, IN_QUERY, NB, false, true>), grid, b, 0, s, q, z, P, table, g, gt, gq,
-                         nk, nv, gate, perm, saved);
+                         nk, nv, gate, perm, saved, nk);
     else
       hipLaunchKernelGGL((k_backward<DT, M, false, IN_QUERY, NB>), grid, b, 0, s, q, z, P, table, g, gt, gq, nk, nv, gate,
-                         perm, saved);
+                         perm, saved, nk);
   } else {
     hipLaunchKernelGGL((k_backward<DT, M, false, TH, KS>), grid, b, 0, s, q, z, P, table, g, gt, gq, nk, nv, gate,
-                       perm, saved);
+                       perm, saved, nk);
   }
 }
 
@@ -504,34 +545,66 @@ struct BwdMergedLaunch {
   }
 };
 
+// The pairs of a location sort: search and dq, the pairs with their digits
+// counted, then the sort's passes.
+template <int DT, int M>
+int sorted_pairs(const float* q, const Params& Pq, const void* table, const float* g, float* gt, float* gq,
+                 const Radix<uint2>& r, bool th, NbrList saved, hipStream_t s) {
+  Params P = Pq;
+  P.passes = radix_passes(P.N);  // keys lie in [0, N]
+  const dim3 grid(grid_for(P)), b(THREADS);
+  const uint32_t* const np = nullptr;
+  int rc = LRAM_OK;
+  if (gt && (rc = clear_sort(r, P.passes, s))) return rc;
+  if (th) {
+    rc = with_theta_input(q, P, gq, s, [&](auto in, const float* at, const Params& Pt) {
+      hipLaunchKernelGGL((k_backward<DT, M, true, decltype(in)::value>), grid, b, 0, s, at, q, Pt, table, g, gt, gq,
+                         r.ka, r.va, np, np, saved, r.hdr);
+      return launched();
+    });
+  } else if (saved.on()) {
+    hipLaunchKernelGGL((k_backward<DT, M, true, IN_QUERY, NB, false, true>), grid, b, 0, s, q, q, P, table, g, gt, gq,
+                       r.ka, r.va, np, np, saved, r.hdr);
+    rc = launched();
+  } else {
+    hipLaunchKernelGGL((k_backward<DT, M, true, IN_QUERY>), grid, b, 0, s, q, q, P, table, g, gt, gq, r.ka, r.va, np,
+                       np, saved, r.hdr);
+    rc = launched();
+  }
+  if (rc || !gt) return rc;
+  return sort_counted<uint2, false>(r, P.passes, s);
+}
+
+// The merged scatter by sorted runs.
+template <int DT, int M>
+struct BwdRunsLaunch {
+  static int go(const float* q, const Params& P, const void* table, const float* g, float* gt, float* gq,
+                const Radix<uint2>& r, bool th, NbrList saved, hipStream_t s) {
+    if (int rc = sorted_pairs<DT, M>(q, P, table, g, gt, gq, r, th, saved, s)) return rc;
+    const bool odd = radix_passes(P.N) & 1;
+    const int64_t per_block = (int64_t)RUN_SPAN * WAVES;
+    hipLaunchKernelGGL((k_run_sum<M>), dim3((unsigned)((r.n + per_block - 1) / per_block)), dim3(THREADS), 0, s,
+                       (const uint32_t*)(odd ? r.kb : r.ka), (const uint2*)(odd ? r.vb : r.va), r.n, P.N, (uint32_t)P.L,
+                       g, gt);
+    return launched();
+  }
+};
+
 template <int DT, int M>
 struct BwdSortedLaunch {
   static int go(const float* q, const Params& P, const void* table, const float* g, float* gt, float* gq,
                 const SortedWs& ws, bool th, NbrList saved, hipStream_t s) {
-    const dim3 grid(grid_for(P)), b(THREADS);
-    const uint32_t* const np = nullptr;
-    if (th)
-      hipLaunchKernelGGL((k_backward<DT, M, true, IN_THETA>), grid, b, 0, s, q, q, P, table, g, gt, gq, ws.sort.ka,
-                         ws.sort.va, np, np, saved);
-    else if (saved.on())
-      hipLaunchKernelGGL((k_backward<DT, M, true, IN_QUERY, NB, false, true>), grid, b, 0, s, q, q, P, table, g, gt, gq,
-                         ws.sort.ka, ws.sort.va, np, np, saved);
-    else
-      hipLaunchKernelGGL((k_backward<DT, M, true, IN_QUERY>), grid, b, 0, s, q, q, P, table, g, gt, gq, ws.sort.ka,
-                         ws.sort.va, np, np, saved);
-    int rc = launched();
-    if (rc || !gt) return rc;
-    if ((rc = radix_sort<uint2, false>(ws.sort, P.N, s))) return rc;  // keys lie in [0, N]
+    if (int rc = sorted_pairs<DT, M>(q, P, table, g, gt, gq, ws.sort, th, saved, s)) return rc;
+    if (!gt) return LRAM_OK;
     const bool odd = radix_passes(P.N) & 1;
     const uint32_t* keys = odd ? ws.sort.kb : ws.sort.ka;
     const uint2* vals = odd ? ws.sort.vb : ws.sort.va;
     const int64_t per_block = THREADS / M;
     const unsigned blocks = (unsigned)((ws.groups + per_block - 1) / per_block);
-    hipLaunchKernelGGL((k_segreduce<M>), dim3(blocks), b, 0, s, keys, vals, ws.sort.n, P.N, (uint32_t)P.L, g, gt,
-                       ws.span, ws.edge,
-                       ws.flags);
-    hipLaunchKernelGGL((k_segfix<M>), dim3(blocks), b, 0, s, keys, ws.sort.n, ws.span, (const float*)ws.edge,
-                       (const uint32_t*)ws.flags, ws.groups, gt);
+    hipLaunchKernelGGL((k_segreduce<M>), dim3(blocks), dim3(THREADS), 0, s, keys, vals, ws.sort.n, P.N, (uint32_t)P.L, g,
+                       gt, ws.span, ws.edge, ws.flags);
+    hipLaunchKernelGGL((k_segfix<M>), dim3(blocks), dim3(THREADS), 0, s, keys, ws.sort.n, ws.span,
+                       (const float*)ws.edge, (const uint32_t*)ws.flags, ws.groups, gt);
     return launched();
   }
 };
@@ -625,6 +698,12 @@ int backward_impl(const float* in, int64_t B, int64_t H, const int32_t K[8], con
       const size_t need = order_layout(L, nullptr, nullptr);
       if (!workspace || ws_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255)) return LRAM_EWORKSPACE;
       order_layout(L, &o, reinterpret_cast<char*>(workspace));
+    }
+    if (width == NB && grad_table && workspace && runs_chosen(L, P.N, m) && ws_bytes >= merged_bytes(L) &&
+        (reinterpret_cast<uintptr_t>(workspace) & 255) == 0) {
+      Radix<uint2> r{};
+      runs_layout(L, &r, reinterpret_cast<char*>(workspace));
+      return dispatch<BwdRunsLaunch>(dtype, m, in, P, table, grad_out, grad_table, grad_in, r, th, saved, stream);
     }
     return dispatch<BwdMergedLaunch>(dtype, m, in, P, table, grad_out, grad_table, grad_in, o, order != nullptr, th,
                                      width, saved, stream);
@@ -772,8 +851,7 @@ int lram_backward_workspace_bytes(int64_t B, int64_t H, int32_t m, int mode, siz
     return LRAM_OK;
   }
   if (H != 0 && B > INT64_MAX / H / NB) return LRAM_EINVAL;
-  *bytes = mode == LRAM_SCATTER_SORTED ? sorted_layout(B * H, m, nullptr, nullptr)
-                                       : order_layout(B * H, nullptr, nullptr);
+  *bytes = mode == LRAM_SCATTER_SORTED ? sorted_layout(B * H, m, nullptr, nullptr) : merged_bytes(B * H);
   return LRAM_OK;
 }
 
@@ -792,6 +870,9 @@ int lram_backward_noalloc(const float* q, int64_t B, int64_t H, const int32_t K[
                           void* stream) {
   size_t need = 0;
   if (int rc = lram_backward_workspace_bytes(B, H, m, mode, &need)) return rc;
+  int resolved = mode;
+  if (int rc = resolve_mode(B, H, mode, &resolved)) return rc;
+  if (resolved == LRAM_SCATTER_MERGED) need = order_layout(B * H, nullptr, nullptr);  // all that it cannot do without
   if (need > LRAM_STATIC_SCRATCH_BYTES) return LRAM_EWORKSPACE;
   void* ws = nullptr;
   if (need > 0)

@@ -186,8 +186,9 @@ __device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS, NBU
 
 // The value gradient is either added straight into grad_table with fp32
 // atomics (EMIT = false), or emitted as (location, (lookup, w_j)) pairs for
-// the sorted segmented reduction (EMIT = true; padding gets the key N, which
-// sorts last).
+// the location sort (EMIT = true; padding gets the key N, which sorts last),
+// whose digits are counted here into ghist (the counts hide behind the row
+// loads; a kernel of their own took 37 us for 8.4 M pairs).
 // gate (nullable): the merged scatter's device-side choice -- this kernel does
 // nothing when the batch is merged instead (see merge_chosen).
 // TH: the lookups' input; z the activation layer's own input, for its chain.
@@ -201,11 +202,17 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == 
                                                       const float* __restrict__ gout, float* __restrict__ gtab,
                                                       float* gq, uint32_t* __restrict__ pair_key,
                                                       uint2* __restrict__ pair_val, const uint32_t* __restrict__ gate,
-                                                      const uint32_t* __restrict__ perm, NbrList saved) {
+                                                      const uint32_t* __restrict__ perm, NbrList saved,
+                                                      uint32_t* __restrict__ ghist) {
   static_assert(!EMIT || KS == NB, "the sorted scatter takes lists of 32");
   static_assert(!(SAVED || ORD) || (KS == NB && !TH), "orders and saved lists serve the k = 32 lookup");
   __shared__ SearchLds<KS> S;
+  __shared__ uint32_t digits[EMIT ? SORT_PASSES_MAX : 1][EMIT ? RADIX : 1];
   if (gate && merge_chosen(*gate, P.L)) return;
+  if constexpr (EMIT) {  // (the search's first barrier follows)
+#pragma unroll
+    for (int p = 0; p < SORT_PASSES_MAX; ++p) digits[p][threadIdx.x] = 0u;
+  }
   WaveCtx c;
   wave_ctx(P, c, ORD);
   const int lane = c.lane;
@@ -217,7 +224,11 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == 
     if (gq && ok) grad_query<DT, M, TH, KS>(F, W, buf, S.tab, count, tb, gout, l, lane, gq, z, P);
     if (EMIT && gtab && lane < NB && ok) {
       const int32_t s = W.nbr[buf][lane].slot;
-      pair_key[l * NB + lane] = s >= 0 ? (uint32_t)s : P.N;
+      const uint32_t key = s >= 0 ? (uint32_t)s : P.N;
+      pair_key[l * NB + lane] = key;
+#pragma unroll
+      for (int p = 0; p < SORT_PASSES_MAX; ++p)
+        if (p < P.passes) atomicAdd(&digits[p][(key >> (p * RADIX_BITS)) & (RADIX - 1)], 1u);
       pair_val[l * NB + lane] = make_uint2((uint32_t)l, __float_as_uint(W.wgt[buf][lane]));
     }
   };
@@ -246,6 +257,14 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == 
           if (2 * p + 1 < nt) finish(ts.FR[2 * p + 1], 1, ts.count1, l1, ok);
           wave_lds_sync();
         }
+      }
+    }
+    if constexpr (EMIT) {
+      __syncthreads();
+      uint32_t* g = ghist + (blockIdx.x % SORT_HIST_COPIES) * (SORT_PASSES_MAX * RADIX);
+      for (int p = 0; p < P.passes; ++p) {
+        const uint32_t n = digits[p][threadIdx.x];
+        if (gtab && n) atomicAdd(&g[p * RADIX + threadIdx.x], n);
       }
     }
   } else {

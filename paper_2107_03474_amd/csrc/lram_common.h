@@ -59,6 +59,7 @@ struct Params {
   uint32_t N;
   int32_t lpw;       // lookups per wave (1..64)
   int32_t stage;     // floats per staged record (input IN_STAGED)
+  int32_t passes;    // radix passes of a location sort
   int64_t L;
   double cK[8];      // K_i / (2 pi): torus coordinate per radian of arg z_i (activation layer)
 };

@@ -37,8 +37,8 @@ __device__ __forceinline__ uint32_t cell_location(const float (&qq)[8], const Pa
 }
 
 // key[l] = cell_location of lookup l, and the digit counts of the keys for
-// the first `passes` passes of the radix sort that orders them (as
-// k_digit_hist: each workgroup counts one contiguous chunk of lookups in
+// the first `passes` passes of the radix sort that orders them (each
+// workgroup counts one contiguous chunk of lookups in
 // per-wave LDS counters and adds its nonzero bins to copy blockIdx %
 // SORT_HIST_COPIES of ghist, cleared).  The workgroups also clear the sort's
 // look-back states, clear[0, nclear), which no pass reads before this kernel

@@ -70,34 +70,9 @@ __global__ void __launch_bounds__(THREADS) k_zero_words(uint32_t* __restrict__ p
 }
 
 // Global digit counts of every pass: ghist[copy][p][d] summed over the copies
-// is the number of keys whose digit p is d.  Each workgroup counts one
-// contiguous chunk in LDS (per-wave counters, so fewer LDS atomics collide)
-// and adds its nonzero bins to its copy.
-__global__ void __launch_bounds__(THREADS) k_digit_hist(const uint32_t* __restrict__ keys, int64_t n, int passes,
-                                                        uint32_t* __restrict__ ghist) {
-  __shared__ uint32_t h[WAVES][SORT_PASSES_MAX][RADIX];
-  const int t = threadIdx.x, w = t / WAVE;
-#pragma unroll
-  for (int k = 0; k < WAVES; ++k)
-#pragma unroll
-    for (int p = 0; p < SORT_PASSES_MAX; ++p) h[k][p][t] = 0;
-  __syncthreads();
-  const int64_t chunk = (n + gridDim.x - 1) / gridDim.x;
-  const int64_t b = (int64_t)blockIdx.x * chunk, e = min<int64_t>(n, b + chunk);
-  for (int64_t i = b + t; i < e; i += THREADS) {
-    const uint32_t k = keys[i];
-#pragma unroll
-    for (int p = 0; p < SORT_PASSES_MAX; ++p)
-      if (p < passes) atomicAdd(&h[w][p][(k >> (p * RADIX_BITS)) & (RADIX - 1)], 1u);
-  }
-  __syncthreads();
-  uint32_t* g = ghist + (blockIdx.x % SORT_HIST_COPIES) * (SORT_PASSES_MAX * RADIX);
-#pragma unroll
-  for (int p = 0; p < SORT_PASSES_MAX; ++p) {
-    const uint32_t c = h[0][p][t] + h[1][p][t] + h[2][p][t] + h[3][p][t];
-    if (p < passes && c) atomicAdd(&g[p * RADIX + t], c);
-  }
-}
+// is the number of keys whose digit p is d.  The kernels that form the keys
+// (k_cell_key, k_backward) count them: each workgroup in LDS, then its nonzero
+// bins into its copy.
 
 // Exclusive prefix sum of x over the workgroup's threads (thread t holds
 // entry t); `part` is WAVES words of LDS.
@@ -428,6 +403,98 @@ __global__ void __launch_bounds__(THREADS) k_segfix(const uint32_t* __restrict__
     if (!(flags[g] & SEG_THROUGH)) break;
   }
   gtab[(size_t)key * M + col] += acc;
+}
+
+// Value-gradient rows of the sorted pairs by row atomics (the merged scatter of
+// small tables): a wave walks a span of RUN_SPAN pairs in location order, sums
+// w * G[lookup] while the location stays the same and adds every run's row
+// with one atomic instruction that nothing waits for; runs cut by a span's end
+// are added twice.  M lanes hold a row's columns; with M = 32 the two halves of
+// the wave take alternate pairs.  Pairs, locations and so every branch are
+// uniform over the wave (scalar).
+// Bound by the upstream rows it gathers: 8.4 M pairs of 256 bytes from a 67 MB
+// array take 302 us into 2^18 rows and 336 us into 2^20 (a bare gather 274 us);
+// the bit-reproducible reduction above waits for the table's row at every
+// run's end and takes 1,190 us.
+constexpr int RUN_SPAN = 256;   // pairs per wave
+constexpr int RUN_BATCH = 16;   // gather instructions in flight per wave
+
+template <int M>
+__global__ void __launch_bounds__(THREADS) k_run_sum(const uint32_t* __restrict__ keys, const uint2* __restrict__ vals,
+                                                     int64_t n, uint32_t N, uint32_t nl,
+                                                     const float* __restrict__ gout, float* __restrict__ gtab) {
+  constexpr int H = WAVE / M;
+  const int lane = threadIdx.x % WAVE, col = lane % M, h = lane / M;
+  const int64_t b = ((int64_t)blockIdx.x * WAVES + (int)uniform(threadIdx.x / WAVE)) * RUN_SPAN;
+  if (b >= n) return;
+  const int64_t e = min<int64_t>(n, b + RUN_SPAN);
+  uint32_t cur = N;  // location of the run being summed (N: none)
+  float acc = 0.0f;
+  auto flush = [&] {
+    if (cur >= N) return;
+    float s = acc;
+    if constexpr (H == 2) s = add_halves_f32<32>(acc, acc);
+    if (h == 0) unsafeAtomicAdd(gtab + (size_t)cur * M + col, s);
+  };
+  for (int64_t c = b; c < e; c += WAVE) {
+    const bool in = c + lane < e;
+    const uint32_t k = in ? keys[c + lane] : N;
+    const uint2 v = in ? vals[c + lane] : make_uint2(0u, 0u);
+    const int nv = __popcll(__ballot(k < N));  // padding sorts last
+#pragma unroll 1
+    for (int j0 = 0; j0 < nv; j0 += RUN_BATCH * H) {
+      float g[RUN_BATCH];
+#pragma unroll
+      for (int u = 0; u < RUN_BATCH; ++u) {
+        const int j = j0 + u * H;
+        g[u] = 0.0f;
+        if (j < nv) {
+          // (the second half's pair may lie past the end: it then reads lookup 0 and counts for nothing)
+          uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)v.x, j);
+          if constexpr (H == 2) l = h ? (uint32_t)__builtin_amdgcn_readlane((int)v.x, j + 1) : l;
+          g[u] = gout[(size_t)min(l, nl - 1) * M + col];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < RUN_BATCH; ++u) {
+        const int j = j0 + u * H;
+        if (j >= nv) break;
+        const uint32_t k0 = (uint32_t)__builtin_amdgcn_readlane((int)k, j);
+        const float w0 = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)v.y, j));
+        if constexpr (H == 1) {
+          if (k0 != cur) {
+            flush();
+            cur = k0;
+            acc = w0 * g[u];
+          } else {
+            acc = fmaf(w0, g[u], acc);
+          }
+        } else {
+          const bool two = j + 1 < nv;
+          const uint32_t k1 = two ? (uint32_t)__builtin_amdgcn_readlane((int)k, j + 1) : N;
+          const float w1 = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)v.y, j + 1));
+          const float w = h ? w1 : w0;
+          if (k0 != cur) {
+            flush();
+            cur = k0;
+            acc = 0.0f;
+          }
+          if (k1 == k0) {
+            acc = fmaf(w, g[u], acc);
+          } else {
+            acc = h == 0 ? fmaf(w, g[u], acc) : acc;
+            if (two) {
+              flush();
+              cur = k1;
+              acc = h == 1 ? w * g[u] : 0.0f;
+            }
+          }
+        }
+      }
+    }
+    if (nv < WAVE) break;
+  }
+  flush();
 }
 
 }  // namespace

@@ -1,0 +1,115 @@
+"""The merged scatter by sorted runs (tables small against the pairs): dV and dq against the atomic scatter.
+
+Both scatters add the same fp32 products w_j G in different orders: a row of n additions of fp32 numbers differs by at
+most n 2^-24 of the sum of magnitudes.  Rows here hold up to a few thousand pairs of random sign; the bar is 2e-5 of
+the row's norm plus 1e-6 of the largest row (rows whose pairs nearly cancel), and for one row that every lookup hits
+(131,072 additions) its own bound.  dq does not depend on the scatter: the same bits.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2107_03474_amd as lram
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _say(*a):
+    print(*a, flush=True)
+
+
+def _compare(q, K, m, dtype, seed, merged):
+    N = int(np.prod(K))
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    table = (torch.randn((N, m), generator=g, device=DEV) * 0.02).to(dtype)
+    G = torch.randn((q.shape[0], m), generator=g, device=DEV)
+    a, qa = lram.backward(q, table, K, G, mode="atomic")
+    b, qb = merged(q, table, K, G)
+    assert torch.equal(qa, qb)
+    da, db = a.double(), b.double()
+    err, size = (da - db).norm(dim=1), da.norm(dim=1)
+    assert (err <= 2e-5 * size + 1e-6 * size.max()).all()
+    assert torch.equal((a != 0).any(1), (b != 0).any(1))
+    return table, G
+
+
+def _merged(q, table, K, G):
+    return lram.backward(q, table, K, G, mode="merged")
+
+
+@pytest.mark.parametrize("m,dtype", [(32, torch.float32), (64, torch.float32), (32, torch.bfloat16), (64, torch.bfloat16)])
+@pytest.mark.parametrize("L,K", [
+    (65535, (4, 4, 4, 4, 4, 4, 4, 4)),     # below RUNS_MIN: the batch merge
+    (65536, (4, 4, 4, 4, 4, 4, 4, 4)),
+    (65537, (4, 4, 6, 4, 6, 4, 4, 8)),     # ragged, an uneven torus, two to four pairs per row
+    (131072 + 5, (2, 2, 4, 2, 2, 4, 2, 2)),  # 1,024 rows, both lifts of a side of 2, long runs
+    (131072, (8, 8, 8, 8, 4, 4, 8, 4)),    # 2^22 rows / 2^22 pairs: the batch merge on this side of the line
+])
+def test_runs(L, K, m, dtype):
+    _say("runs L=%d K=%s m=%d %s" % (L, K, m, dtype))
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + m)
+    q = torch.rand((L, 8), generator=g, device=DEV) * torch.tensor(K, device=DEV)
+    q[::97, 3] = float("nan")                              # padding pairs
+    q[1::1013] = torch.round(q[1::1013].nan_to_num())      # lattice points: lists of one
+    _compare(q, K, m, dtype, L, _merged)
+
+
+@pytest.mark.parametrize("m", [32, 64])
+def test_one_query(m):
+    """Every lookup the same: 32 runs over all spans."""
+    _say("one query m=%d" % m)
+    K, L = (4,) * 8, 131072
+    q = torch.full((L, 8), 1.3, device=DEV) + torch.arange(8, device=DEV) * 0.11
+    table = torch.randn((4 ** 8, m), device=DEV)
+    G = torch.rand((L, m), device=DEV) + 0.5               # one sign: sums of L terms, relative error below L 2^-24
+    gt, _ = lram.backward(q, table, K, G, mode="merged")
+    slot, w, _ = lram.neighbors(q[:1], K)
+    ref = w[0].double()[:, None] * G.double().sum(0)[None]
+    got = gt[slot[0].long()].double()
+    assert ((got - ref).norm(dim=1) <= 1e-4 * ref.norm(dim=1)).all()
+    rest = torch.ones(4 ** 8, dtype=torch.bool, device=DEV)
+    rest[slot[0].long()] = False
+    assert not gt[rest].any()
+
+
+def test_all_lookups_non_finite():
+    q = torch.full((70000, 8), float("inf"), device=DEV)
+    gt, gq = lram.backward(q, torch.randn((4 ** 8, 32), device=DEV), (4,) * 8, torch.randn((70000, 32), device=DEV),
+                           mode="merged")
+    assert not gt.any() and not gq.any()
+
+
+def test_other_callers():
+    """An order-sized workspace, an order, the library's own scratch, saved lists and the activation layer."""
+    K, L, m = (4, 4, 4, 4, 4, 4, 8, 8), 70001, 64
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    q = torch.rand((L, 8), generator=g, device=DEV) * torch.tensor(K, device=DEV)
+    nbytes = lram.order_layout(L, 1)[0]
+    assert lram.backward_workspace_bytes(L, 1, m, "merged") > nbytes
+    small = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+    table, G = _compare(q, K, m, torch.float32, 1, lambda *a: lram.backward(*a, mode="merged", workspace=small))
+    _compare(q, K, m, torch.float32, 1, lambda *a: lram.backward(*a, mode="merged", order=lram.order(q, K)))
+
+    def noalloc(q, table, K, G):
+        gt = torch.zeros(table.shape, device=DEV)
+        gq = torch.empty_like(q)
+        lram.backward_noalloc(q, table, K, G, gt, gq, mode="merged")
+        return gt, gq
+
+    _compare(q, K, m, torch.float32, 1, noalloc)
+
+    def saved(q, table, K, G):
+        nl = lram.new_lists(q)
+        lram.forward(q, table, K, lists=nl)
+        return lram.backward(q, table, K, G, mode="merged", lists=nl)
+
+    _compare(q, K, m, torch.float32, 1, saved)
+    z = torch.randn((L, 16), generator=g, device=DEV)
+    ta, za = lram.theta_backward(z, table, K, G, mode="atomic")
+    tb, zb = lram.theta_backward(z, table, K, G, mode="merged")
+    assert torch.equal(za, zb)
+    assert ((ta.double() - tb.double()).norm(dim=1) <= 2e-5 * ta.double().norm(dim=1) + 1e-6 * ta.double().norm(dim=1).max()).all()
