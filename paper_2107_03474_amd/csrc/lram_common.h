@@ -147,8 +147,8 @@ constexpr int CANDS = E8_NSTRICT + E8_NBOUNDARY;
 constexpr uint32_t CAND_NONE = 0xFFFFu;
 template <int KS>
 struct alignas(16) TileLds {
-  uint32_t a[KS == NB ? E8_TILE_BLOCKS : 1][KS == NB ? WAVE : 4];  // operands of the distance product (two bf16)
-  uint2 cand[KS == NB ? CANDS + 1 : 2];                            // packed bytes
+  uint4 rows[KS == NB ? E8_TILE_BLOCKS * TILE : 1];  // points of the distance product, eight bf16 each
+  uint2 cand[KS == NB ? CANDS + 1 : 2];              // packed bytes
   uint16_t idx[WAVES][KS == NB ? TILE : 1][KS == NB ? NB : 2];
 };
 

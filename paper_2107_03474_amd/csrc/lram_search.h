@@ -226,8 +226,8 @@ __device__ __forceinline__ void d8_round_quad(float y0, float y1, int kq, int& r
 // puts there once the selection has read z.
 template <int TH>
 __device__ __forceinline__ uint2 make_frames(const QuadIn<TH>& in, bool have, const QuadCtx<TH>& Q, Frame* fr) {
-  const int kq = Q.kq, i0 = 2 * kq, i1 = i0 + 1;
-  const int quad0 = 4 * Q.n;
+  const int kq = opaque(Q.kq), n = opaque(Q.n), i0 = 2 * kq, i1 = i0 + 1;  // (opaque: as in tile_select)
+  const int quad0 = 4 * n;
   float q0, q1, scale = in.s;
   bool fin = have;
   if constexpr (TH == IN_THETA) {
@@ -283,7 +283,7 @@ __device__ __forceinline__ uint2 make_frames(const QuadIn<TH>& in, bool have, co
   const bool f0 = par && r0 == 7, f1 = par && r1 == 7;
   n0 ^= f0 ? 1u : 0u;
   n1 ^= f1 ? 1u : 0u;
-  Frame& F = fr[Q.n];
+  Frame& F = fr[n];
   reinterpret_cast<uint4*>(F.rec)[kq] = make_uint4(__float_as_uint(x0), 2u * (uint32_t)c0 | n0, __float_as_uint(x1),
                                                    2u * (uint32_t)c1 | n1);
   F.sel[r0] = __float_as_uint(f0 ? 0.5f * a0 : -0.5f * a0);
@@ -833,37 +833,43 @@ struct Search {
 // closest of a random query, and ten always are, so the selection is a choice
 // of 22 out of 64, and it does not need the recipe's distances:
 //   1. distances of the candidates to the 16 queries in F come from the matrix
-//      cores, |p|^2/4 - z.p/2 (v_mfma_f32_16x16x4, quarter units, |z|^2/4 left
-//      out): a lane holds 16 of its lookup's 64 candidates in registers;
+//      cores, |p|^2/4 - z.p/2 (quarter units, |z|^2/4 left out): a lane holds 16
+//      of its lookup's 64 candidates in registers.  The points' coordinates are
+//      exact in bf16 and z is the sum of three bf16 numbers (8 bits of its
+//      mantissa each), so one v_mfma_f32_16x16x32_bf16 forms 16 x 16 distances
+//      with exact products and fp32 sums (the third of its depth times zero is
+//      idle); two v_mfma_f32_16x16x4_f32 took four times its cycles and
+//      2,150 clocks of a tile's latency;
 //   2. a threshold with 22 of the 64 below it is found by interpolation on the
 //      count (about four rounds, all 16 lookups at once, no LDS);
 //   3. the choice is accepted if no candidate -- of the 64, of the ten (all
 //      below) or of the remaining 158 (all above) -- lies within TILE_EPS of
 //      the threshold and the threshold is clear of the support's edge: the
-//      recipe's order of the two sides is then the same (the product and the
-//      recipe both stay within 2e-6 quarter units of the distance in exact
-//      arithmetic).  Otherwise the lookup takes the general search (about
+//      recipe's order of the two sides is then the same (the product stays
+//      within 24 half units of 2^-21 = 5.7e-6 quarter units of the distance in
+//      exact arithmetic, 1e-6 observed, and the recipe within 1e-6).  Otherwise the lookup takes the general search (about
 //      1 in 1,000 random queries, and queries next to a lattice point or hole);
 //   4. the recipe's distances, locations and weights of the chosen 32 alone are
 //      formed two lookups at a time, one neighbour to a lane.
 // About 75 VALU instructions per lookup.  Measured before and after: lists of
-// 100,003 lookups 173 -> 68 us; flags of 262,144 lookups 132 -> 66 us; forward of
+// 100,003 lookups 173 -> 65 us; flags of 262,144 lookups 132 -> 59 us; forward of
 // 262,144 lookups (2^18 rows, m = 64 fp32) 328 -> 249 us, of 131,072 (m = 64 bf16)
-// 114 -> 69 us, of 4,194,304 (1e8 rows, m = 32 bf16, ordered) 2,538 -> 2,061 us.
+// 114 -> 69 us, of 4,194,304 (1e8 rows, m = 32 bf16, ordered) 2,538 -> 2,039 us.
 // The rows of the product: blocks 0-3 the 64, block 4 the ten (rows 0-9) and
 // six others, blocks 5-14 the others.
 
 constexpr int TILE_PICK = NB - TILE_ALWAYS;
-constexpr float TILE_EPS = 8e-6f;    // quarter units: 3.2e-5 in distance^2
-constexpr float TILE_STEP = 1.2e-5f; // a threshold placed next to a candidate keeps this far from it
+constexpr float TILE_EPS = 1e-5f;    // quarter units: 4e-5 in distance^2
+constexpr float TILE_STEP = 1.4e-5f; // a threshold placed next to a candidate keeps this far from it
 constexpr float TILE_EDGE = 7.999f;  // as KEY_SUSPECT
 constexpr int TILE_ROUNDS = 7;
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 struct TileOps {
-  uint32_t a[E8_TILE_BLOCKS][WAVE];  // A operands: row lane % 16, F coordinates lane / 16 and 4 + lane / 16, two bf16
-  float c[2][16];                    // |p|^2 / 4 of the rows of blocks 3 and 4 (mixed norms)
+  uint32_t rows[E8_TILE_BLOCKS * TILE][4];  // F coordinates of the rows' points, eight bf16
+  float c[2][16];                           // |p|^2 / 4 of the rows of blocks 3 and 4 (mixed norms)
   uint32_t cand[CANDS + 1][2];       // packed bytes 4 (p_r - CMIN)
 };
 
@@ -882,7 +888,7 @@ constexpr TileOps make_tile_ops() {
       float n2 = 0.0f;
       for (int r = 0; r < 8; ++r) {
         // |p_r| <= 4: exact in the upper half of its fp32 bits
-        o.a[b][(r % 4) * 16 + m] |= (__builtin_bit_cast(uint32_t, (float)p[r]) >> 16) << (16 * (r / 4));
+        o.rows[16 * b + m][r / 2] |= (__builtin_bit_cast(uint32_t, (float)p[r]) >> 16) << (16 * (r % 2));
         n2 += (float)(p[r] * p[r]);
       }
       if (b == 3 || b == 4) o.c[b - 3][m] = 0.25f * n2;
@@ -927,13 +933,12 @@ __device__ __forceinline__ void init_tile(SL& S) {
     for (int i = threadIdx.x; i < words / 4; i += THREADS) dst[i] = src[i];
   };
   static_assert((CANDS + 1) % 2 == 0 && sizeof(S.tile.cand) == sizeof(c_tile.cand), "candidates in 16-byte pieces");
-  copy(&c_tile.a[0][0], &S.tile.a[0][0], E8_TILE_BLOCKS * WAVE);
+  copy(&c_tile.rows[0][0], &S.tile.rows[0].x, E8_TILE_BLOCKS * TILE * 4);
   copy(&c_tile.cand[0][0], &S.tile.cand[0].x, 2 * (CANDS + 1));
   __syncthreads();
 }
 
-// Sum, unsigned minimum and signed minimum over the four lanes of a lookup
-// (lane % 16 = lookup).
+// f over the four lanes of a lookup (lane % 16 = lookup).
 template <typename F>
 __device__ __forceinline__ uint32_t over_groups(uint32_t x, F f) {
   const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
@@ -945,15 +950,32 @@ __device__ __forceinline__ uint32_t over_groups(uint32_t x, F f) {
 // Steps 1 to 3 for the frames of a tile: writes every accepted lookup's
 // candidate indices to idx and returns the accepted lookups' bits.
 __device__ __forceinline__ uint32_t tile_select(const Frame* fr, const TileLds<NB>& tile, uint16_t (*idx)[NB], int lane) {
-  const int n = lane & 15, g = lane >> 4;
+  // (opaque: what follows from the lane is formed again for every tile; held
+  // for the whole wave it costs the row loads their registers)
+  const int ln = opaque(lane), n = ln & 15, g = ln >> 4;
   const Frame& F = fr[n];
-  const float zl = __uint_as_float(F.sel[g]), zh = __uint_as_float(F.sel[4 + g]);
   const float r2 = F.r2;
-  const int ln = opaque(lane);
+  // the matrix's B operand: lane group g holds the g-th 8 bits of -z_r / 2
+  bf16x8_t z;
+  {
+    const uint4 lo = reinterpret_cast<const uint4*>(F.sel)[0], hi = reinterpret_cast<const uint4*>(F.sel)[1];
+    const uint32_t in[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    const uint32_t m1 = g >= 1 ? 0xFFFF0000u : 0u, m2 = g >= 2 ? 0xFFFF0000u : 0u, some = g < 3 ? ~0u : 0u;
+    uint32_t x[8], w[4];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      float y = __uint_as_float(in[r]);
+      y -= __uint_as_float(__float_as_uint(y) & m1);  // exact: the leading bits
+      y -= __uint_as_float(__float_as_uint(y) & m2);
+      x[r] = __float_as_uint(y);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[r] = __builtin_amdgcn_perm(x[2 * r + 1], x[2 * r], 0x07060302u) & some;
+    z = __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
+  }
   auto product = [&](int b, f32x4_t c) {
-    const uint32_t p = tile.a[b][lane];
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(bf16_lo(p), zl, c, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(bf16_hi(p), zh, c, 0, 0, 0);
+    const bf16x8_t p = __builtin_bit_cast(bf16x8_t, tile.rows[16 * b + n]);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(p, z, c, 0, 0, 0);
   };
   f32x4_t mixed[2];
 #pragma unroll
@@ -997,14 +1019,17 @@ __device__ __forceinline__ uint32_t tile_select(const Frame* fr, const TileLds<N
       up = min(up, t);                                      // smallest non-negative difference
       dn = (uint32_t)min((int)dn, (int)t);                  // negative difference of smallest magnitude
     }
+    // magnitudes as bits (which order like them), infinite where the lane has none on that side
+    up = min(up, KEY_INF);
+    dn = min(dn ^ 0x80000000u, KEY_INF);
     mine = __popc(mask);
     cnt = (int)over_groups((uint32_t)mine, [](uint32_t a, uint32_t b) { return a + b; });
-    up = over_groups(up, [](uint32_t a, uint32_t b) { return min(a, b); });
-    dn = over_groups(dn, [](uint32_t a, uint32_t b) { return (uint32_t)min((int)a, (int)b); });
     const int miss = F.valid ? TILE_PICK - cnt : 0;
     if (__ballot(miss != 0) == 0) break;
+    const bool less = miss > 0;
+    // distance to the next candidate on the side that is short
+    const float gap = __uint_as_float(over_groups(less ? up : dn, [](uint32_t a, uint32_t b) { return min(a, b); }));
     if (miss != 0) {
-      const bool less = miss > 0;
       if (less) {
         lo = T;
         clo = cnt;
@@ -1013,7 +1038,7 @@ __device__ __forceinline__ uint32_t tile_select(const Frame* fr, const TileLds<N
         chi = cnt;
       }
       // past the next candidate, which is right when one is missing (or too many)
-      const float step = less ? T + __uint_as_float(up) + TILE_STEP : T + __uint_as_float(dn) - TILE_STEP;
+      const float step = less ? T + gap + TILE_STEP : T - gap - TILE_STEP;
       const bool both = clo >= 0 && chi >= 0;
       float x = both ? lo + (hi - lo) * (float)(TILE_PICK - clo) * __builtin_amdgcn_rcpf((float)(chi - clo))
                      : T + 0.0091f * (float)miss;
@@ -1023,7 +1048,7 @@ __device__ __forceinline__ uint32_t tile_select(const Frame* fr, const TileLds<N
   }
   // accepted: 22 of the 64, all ten and none of the others below, none near, clear of the edge
   uint32_t below = 0;
-  float near = fminf(__uint_as_float(up), -__uint_as_float(dn));
+  float near = __uint_as_float(min(up, dn));
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const float t = va[i] - T;
@@ -1099,6 +1124,7 @@ struct TileSearch {
         if (lane < NB) S.tile.idx[wave][t][lane] = (uint16_t)CAND_NONE;
         wave_lds_sync();
         const Sel s = read_sel(FR[t]);
+        one.lane = opaque(one.lane);  // (as in tile_select)
         if (s.valid) one.run(FR[t], s, t);
       }
       wave_lds_sync();

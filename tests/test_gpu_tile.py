@@ -11,6 +11,7 @@ import torch
 
 import oracle
 import paper_2107_03474_amd as lram
+from test_tile_search_model import near_ties
 from test_gpu_parity import _rel_rows, _say, check_neighbors, special_queries
 
 pytestmark = pytest.mark.gpu
@@ -72,3 +73,10 @@ def test_step(L, m, dtype):
     rest = np.ones(N, bool)
     rest[uniq] = False
     assert not got[rest].any()
+
+
+@pytest.mark.parametrize("gap", [1e-6, 1e-5, 3e-5, 1e-4])
+def test_near_ties(gap):
+    """The 32nd and 33rd distances closer than, about as far as and farther apart than the tile search's margin."""
+    _say("tile near ties", gap)
+    check_neighbors(near_ties(gap, 6000, int(1e7 * gap)), (8,) * 8)

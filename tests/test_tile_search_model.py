@@ -1,7 +1,7 @@
 """CPU model of the tile search's rule for the closest 32, checked against the oracle.
 
 The tile search forms the candidates' distances to the query in F as |p|^2/4 -
-z.p/2 in fp32 (quarter units), finds a threshold T with 22 of 64 chosen
+z.p/2 with exact products and fp32 sums (z in three bf16 parts; quarter units), finds a threshold T with 22 of 64 chosen
 candidates below it, and accepts those and ten more as the closest 32 when no
 candidate of the strict list lies within TILE_EPS of T on either side, the ten
 are below, every other one is above, and 4 T + |z|^2 is below the support's
@@ -41,12 +41,41 @@ def test_tile_rows():
     assert (n2[ROWS[:3]] == 8).all() and (n2[ROWS[5:10]] == 8).all() and (n2[ROWS[10:]] == 16).all()
 
 
+def _parts(z):
+    """-z/2 as three bf16 numbers (8 bits of the mantissa each): exact."""
+    y, out = (-0.5 * z).astype(np.float32), []
+    for _ in range(3):
+        top = (y.view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32)
+        out.append(top)
+        y = y - top
+    assert not y.any()
+    return out
+
+
 def _quarter_distances(z):
-    """|p|^2/4 - z.p/2 of every strict candidate as the matrix product forms it (fp32, one rounding per term)."""
+    """|p|^2/4 - z.p/2 of every strict candidate as a matrix product forms it: exact products of bf16 numbers, an fp32
+    rounding after every addition (the order inside the matrix cores is theirs)."""
     d = np.broadcast_to(((STRICT ** 2).sum(1) / 4).astype(np.float32), (z.shape[0], len(STRICT))).copy()
-    for r in range(8):
-        d = (d.astype(np.float64) + (-0.5 * z[:, r:r + 1].astype(np.float64)) * STRICT[None, :, r]).astype(np.float32)
+    for part in _parts(z):
+        for r in range(8):
+            d = (d.astype(np.float64) + part[:, r:r + 1].astype(np.float64) * STRICT[None, :, r]).astype(np.float32)
     return d
+
+
+def near_ties(gap, n, seed, K=(8,) * 8):
+    """Queries moved until their 32nd and 33rd distances differ by about `gap`."""
+    rng = np.random.default_rng(seed)
+    q = rng.random((n, 8)) * np.asarray(K)
+    for _ in range(3):
+        nb = oracle.neighbors(q.astype(np.float32), K, k=64)
+        x = 2.0 * q
+        a = nb["lift"][:, 31].astype(np.float64)
+        b = nb["lift"][:, 32].astype(np.float64)
+        # |x - b|^2 - |x - a|^2 is linear in x: step along its gradient 2 (a - b) to the wanted gap
+        g = 2.0 * (a - b)
+        diff = ((x - b) ** 2).sum(1) - ((x - a) ** 2).sum(1)
+        q = (x + ((gap - diff) / (g * g).sum(1))[:, None] * g) / 2.0
+    return np.mod(q, np.asarray(K)).astype(np.float32)
 
 
 def _accepted(z, step):
@@ -75,9 +104,9 @@ def _check(q, K, least):
     z = np.zeros_like(y)
     np.put_along_axis(z, r, (y * s).astype(np.float32), 1)
     nb = oracle.neighbors(q, K)
-    # error of the product against exact arithmetic, well inside TILE_EPS / 2
+    # error of the product against exact arithmetic: 24 additions of sums below 8, half a unit of 2^-21 each
     exact = ((STRICT ** 2).sum(1) / 4.0)[None] - 0.5 * z.astype(np.float64) @ STRICT.T
-    assert np.abs(_quarter_distances(z) - exact).max() < 2e-6
+    assert np.abs(_quarter_distances(z) - exact).max() < 24 * 2.0 ** -22 < EPS
     for step in (None, 1, -1):
         ok, below = _accepted(z, step)
         assert ok.mean() >= least, (step, ok.mean())
@@ -99,20 +128,8 @@ def test_accepted_lists_are_the_oracles(K):
 
 @pytest.mark.parametrize("gap", [1e-7, 1e-6, 4e-6, 1.6e-5, 3.2e-5, 6.4e-5, 2e-4])
 def test_near_ties(gap):
-    """Queries moved until their 32nd and 33rd distances differ by about `gap`: accepted or not, never wrong."""
-    K = (8,) * 8
-    rng = np.random.default_rng(int(1e9 * gap))
-    q = rng.random((300, 8)) * 8
-    for _ in range(3):
-        nb = oracle.neighbors(q.astype(np.float32), K, k=64)
-        x = 2.0 * q
-        a = nb["lift"][:, 31].astype(np.float64)
-        b = nb["lift"][:, 32].astype(np.float64)
-        # |x - b|^2 - |x - a|^2 is linear in x: step along its gradient 2 (a - b) to the wanted gap
-        g = 2.0 * (a - b)
-        diff = ((x - b) ** 2).sum(1) - ((x - a) ** 2).sum(1)
-        q = (x + ((gap - diff) / (g * g).sum(1))[:, None] * g) / 2.0
-    _check(np.mod(q, 8).astype(np.float32), K, 0.0)
+    """Accepted or not, never wrong."""
+    _check(near_ties(gap, 300, int(1e9 * gap)), (8,) * 8, 0.0)
 
 
 def test_special_points():
