@@ -894,6 +894,7 @@ int lram_access_histogram(const float* q, int64_t B, int64_t H, const int32_t K[
   if (rc) return rc;
   if (L == 0) return LRAM_OK;
   if (!hist || misaligned4(hist)) return LRAM_EINVAL;
+  P.lpw = std::min<int32_t>(P.lpw, TILE);  // one tile to a wave
   hipLaunchKernelGGL(k_access_hist, dim3(grid_for(P)), dim3(THREADS), 0, (hipStream_t)stream, q, P, hist);
   return launched();
 }
