@@ -41,7 +41,8 @@ __device__ __forceinline__ void scatter_atomic(const WaveLds<KS, NBUF, WBUF>& W,
 // dL/dq = s dq:
 //   dL/da_i = dL/ds s^2 a_i / r_i^3 - dL/dq_i c_i b_i / r_i^2,
 //   dL/db_i = dL/ds s^2 b_i / r_i^3 + dL/dq_i c_i a_i / r_i^2,
-// written to gq[l][16] (zero where s = 0); zin is z.
+// written to gq[l][16] (zero where s = 0) by theta_chain for a whole tile:
+// grad_query leaves dq and dL/ds of tile position t in LDS.
 //
 // <G, v_j> and the sums over j are formed in fp64 (fp32 x fp32 products are
 // exact there).  Next to a lattice point one term carries all of dq (and
@@ -60,10 +61,9 @@ __device__ __forceinline__ void scatter_atomic(const WaveLds<KS, NBUF, WBUF>& W,
 // untruncated backward of 29,997 lookups (m = 32 fp32) 322 -> 247 us; 4,096
 // lookups at K = 4 21.3 -> 19.6 us.
 template <int DT, int M, int TH, int KS, int NBUF, int WBUF>
-__device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS, NBUF, WBUF>& W, int buf, const Tables& T,
+__device__ __forceinline__ void grad_query(Frame& F, WaveLds<KS, NBUF, WBUF>& W, int buf, const Tables& T, int t,
                                            int count, const char* __restrict__ tb, const float* __restrict__ gout, int64_t l,
-                                           int lane, float* gq, const float* __restrict__ zin,
-                                           const Params& P) {
+                                           int lane, float* gq) {
   constexpr int R = chunk_rows<KS>();  // rows per chunk of the row loop
   using G = RowGeom<DT, M, R>;
   constexpr int LE = G::LPR / G::NP;   // lanes that share a row's dot product in the end (2, or 4 for chunks of 16)
@@ -161,27 +161,47 @@ __device__ __forceinline__ void grad_query(const Frame& F, const WaveLds<KS, NBU
   }
   // one lane per coordinate writes it
   if ((lane & (IC == 4 ? 14 : 28)) == 0) {
-    const double dqk = dq[0];
-    if constexpr (!TH) {
-      gq[l * 8 + i] = (float)dqk;
-    } else {
-      double ci = P.cK[0];
+    if constexpr (TH == IN_QUERY)
+      gq[l * 8 + i] = (float)dq[0];
+    else
+      W.dq[t][i] = dq[0];
+  }
+  if constexpr (TH != IN_QUERY)
+    if (lane == 0) *reinterpret_cast<double*>(&F.r2) = dls;
+}
+
+// The activation layer's chain for the nt lookups of a tile, one coordinate to
+// a lane: its fp64 divisions and square roots run for eight lookups at once
+// rather than lookup by lookup on eight of 64 lanes (262,144 lookups, m = 64 fp32:
+// the backward's search and gradient 443 -> 400 us).  lookup: the lookup at a
+// tile position, negative where nothing is written.
+template <typename WL, typename Lookup>
+__device__ __forceinline__ void theta_chain(const Frame* FR, const WL& W, int nt, int lane, Lookup lookup, float* gq,
+                                            const float* __restrict__ z, const Params& P) {
+  const int i = lane & 7;
+  double ci = P.cK[0];
 #pragma unroll
-      for (int k = 1; k < 8; ++k) ci = i == k ? P.cK[k] : ci;
-      const double sc = F.s;
+  for (int k = 1; k < 8; ++k) ci = i == k ? P.cK[k] : ci;
+  wave_lds_sync();
+#pragma unroll 1
+  for (int t = lane >> 3; t < TILE; t += 8) {
+    const int64_t l = lookup(t);
+    if (t < nt && l >= 0) {
+      const double sc = FR[t].s, dls = *reinterpret_cast<const double*>(&FR[t].r2);
       double ga = 0.0, gb = 0.0;
       if (sc > 0.0) {
-        const float2 ab = *reinterpret_cast<const float2*>(zin + l * 16 + 2 * i);
+        const float2 ab = *reinterpret_cast<const float2*>(z + l * 16 + 2 * i);
         const double a = ab.x, b = ab.y;
         const double r2 = a * a + b * b;
         const double ir2 = 1.0 / r2, ir3 = ir2 / sqrt(r2);  // 1/r^2, 1/r^3
-        const double ds = dls * sc * sc, dqs = dqk * sc * ci;
+        const double ds = dls * sc * sc, dqs = W.dq[t][i] * sc * ci;
         ga = ds * a * ir3 - dqs * b * ir2;
         gb = ds * b * ir3 + dqs * a * ir2;
       }
       *reinterpret_cast<float2*>(gq + l * 16 + 2 * i) = make_float2((float)ga, (float)gb);
     }
   }
+  wave_lds_sync();
 }
 
 // The value gradient is either added straight into grad_table with fp32
@@ -219,9 +239,9 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == 
   const char* tb = reinterpret_cast<const char*>(table);
   WaveLds<KS, (KS == NB ? 2 : 1)>& W = S.wave[c.wave];
   // scatter and query gradient of list buf, which is lookup l's (ok: inside the batch)
-  auto finish = [&](const Frame& F, int buf, int count, int64_t l, bool ok) {
+  auto finish = [&](Frame& F, int buf, int t, int count, int64_t l, bool ok) {
     if (!EMIT && gtab && count > 0) scatter_atomic<M, KS>(W, buf, count, gout, l, gtab, lane);
-    if (gq && ok) grad_query<DT, M, TH, KS>(F, W, buf, S.tab, count, tb, gout, l, lane, gq, z, P);
+    if (gq && ok) grad_query<DT, M, TH, KS>(F, W, buf, S.tab, t, count, tb, gout, l, lane, gq);
     if (EMIT && gtab && lane < NB && ok) {
       const int32_t s = W.nbr[buf][lane].slot;
       const uint32_t key = s >= 0 ? (uint32_t)s : P.N;
@@ -244,7 +264,7 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == 
           bool ok;
           const int64_t l = in.lookup(t0, t, P, ok);
           const int count = ts.one.load(ts.FR[t], read_sel(ts.FR[t]), 0, saved, l, P.N);
-          finish(ts.FR[t], 0, count, l, ok);
+          finish(ts.FR[t], 0, t, count, l, ok);
           wave_lds_sync();
         }
       } else {
@@ -252,12 +272,14 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == 
           ts.pair(p, 0);
           bool ok;
           const int64_t l0 = in.lookup(t0, 2 * p, P, ok);
-          finish(ts.FR[2 * p], 0, ts.count0, l0, ok);
+          finish(ts.FR[2 * p], 0, 2 * p, ts.count0, l0, ok);
           const int64_t l1 = in.lookup(t0, 2 * p + 1, P, ok);
-          if (2 * p + 1 < nt) finish(ts.FR[2 * p + 1], 1, ts.count1, l1, ok);
+          if (2 * p + 1 < nt) finish(ts.FR[2 * p + 1], 1, 2 * p + 1, ts.count1, l1, ok);
           wave_lds_sync();
         }
       }
+      if constexpr (TH != IN_QUERY)
+        if (gq) theta_chain(ts.FR, W, nt, lane, [&](int t) { return c.base + t0 + t; }, gq, z, P);
     }
     if constexpr (EMIT) {
       __syncthreads();
@@ -277,7 +299,7 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == 
       tile_frames(q, c.base + t0, nt, P, FR, Q, lane);
       for (int t = 0; t < nt; ++t) {
         const int count = srch.run(FR[t], read_sel(FR[t]), 0);
-        finish(FR[t], 0, count, c.base + t0 + t, true);
+        finish(FR[t], 0, t, count, c.base + t0 + t, true);
         wave_lds_sync();
       }
     }

@@ -5,6 +5,8 @@
 
 #pragma once
 
+#include <cstddef>
+
 namespace {
 
 constexpr int NB = LRAM_NEIGHBOURS;  // 32, Sec. 2.6
@@ -76,9 +78,10 @@ struct alignas(16) Frame {
                       // (during the tile selection: bits of -z_r / 2, z the query in F)
   uint32_t valid;     // query finite
   float s;            // output scale: 1, or (sum 1/|z_i|)^-1 behind the activation layer
-  float r2;           // |z|^2
-  uint32_t pad;
+  float r2;           // |z|^2; the activation layer's backward puts dL/ds here, a double over r2 and pad,
+  uint32_t pad;       // once the tile is searched
 };
+static_assert(offsetof(Frame, r2) % 8 == 0 && sizeof(Frame) == 112, "a double fits over r2 and pad");
 
 // A selected neighbour as handed from the search to the gather / scatter.
 struct alignas(16) Nbr {
@@ -98,6 +101,7 @@ struct alignas(16) WaveLds {
   union {
     uint32_t tie[tie_max<KS>()][2];
     uint32_t hist[64];  // distance histogram of the selection, 64 buckets on [4, 8) (read before ties are listed)
+    double dq[KS == 32 ? TILE : 1][8];  // dq of a tile's lookups behind the activation layer (after the searches)
   };
 };
 

@@ -254,9 +254,9 @@ __global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS>())) 
     auto& W = S.b.search.wave[wave];
     const char* tb = reinterpret_cast<const char*>(table);
     // scatter or keep the pairs of list buf (the wave's i-th lookup, l), and its query gradient
-    auto finish = [&](const Frame& F, int buf, int count, int i, int64_t l) {
+    auto finish = [&](Frame& F, int buf, int count, int i, int64_t l) {
       if (!merge && count > 0) scatter_atomic<M, KS>(W, buf, count, gout, l, gtab, lane);
-      if (gq && l < P.L) grad_query<DT, M, TH, KS>(F, W, buf, S.b.search.tab, count, tb, gout, l, lane, gq, z, P);
+      if (gq && l < P.L) grad_query<DT, M, TH, KS>(F, W, buf, S.b.search.tab, i, count, tb, gout, l, lane, gq);
       if (merge && !COMPACT) {
 #pragma unroll
         for (int j = lane; j < KS; j += WAVE) {
@@ -303,6 +303,14 @@ __global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS>())) 
             wave_lds_sync();
           }
         }
+        if constexpr (TH != IN_QUERY)
+          if (gq)
+            theta_chain(ts.FR, W, nl, lane,
+                        [&](int t) {
+                          const int64_t l = (int64_t)(uint32_t)__shfl((int)my_l, 4 * t);
+                          return l < P.L ? l : (int64_t)-1;
+                        },
+                        gq, z, P);
       }
     } else if (nl > 0) {
       Search<KS> srch(P, S.b.search.tab, W, S.b.search.tile, wave, lane);

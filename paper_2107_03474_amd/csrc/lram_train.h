@@ -16,9 +16,10 @@ namespace {
 // pairs in LDS, a 4,096-entry open-addressing hash over the search's LDS sums
 // the weights of every distinct location, and each sum is added with one
 // atomic.  Bound by the scalar atomics (each a 64-byte request at the memory
-// side, about 16 G/s): pair by pair 262,144 lookups of half clustered queries
-// and flags and statistics took 713 us, merged 654 us (2^22 rows).  Hot locations also receive fewer, larger terms,
-// so their fp32 sums are rounded less often.
+// side, about 16 G/s): 262,144 lookups of half clustered queries on 2^22 rows,
+// flags and statistics included, took 713 us pair by pair and take 654 us
+// merged.  Hot locations also receive fewer, larger terms, so their fp32 sums
+// are rounded less often.
 struct alignas(16) HistLds {
   int32_t loc[MERGE_P];
   float w[MERGE_P];
