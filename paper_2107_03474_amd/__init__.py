@@ -294,6 +294,18 @@ def backward_workspace_bytes(B: int, H: int, m: int, mode="auto") -> int:
     return n.value
 
 
+def _new_workspace(nbytes: int, B: int, H: int, N: int, mode: int, k: int, order, like) -> Optional[torch.Tensor]:
+    """A backward's workspace of ``nbytes``.  The merged scatter needs only an
+    order's bytes, none when it is given an order, unless it may sort the pairs:
+    lists of 32 and at least two pairs per row."""
+    if resolved_mode(B, H, mode) == "merged":
+        if k != NB or NB * B * H < 2 * N:
+            nbytes = order_layout(B, H)[0]
+        if order is not None and nbytes <= order.numel():
+            return None
+    return torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+
+
 def backward(q: torch.Tensor, table: torch.Tensor, K: Sequence[int], grad_out: torch.Tensor,
              grad_table: Optional[torch.Tensor] = None, want_grad_q: bool = True, mode="auto",
              workspace: Optional[torch.Tensor] = None, grad_q: Optional[torch.Tensor] = None, k: int = NB,
@@ -318,11 +330,8 @@ def backward(q: torch.Tensor, table: torch.Tensor, K: Sequence[int], grad_out: t
              _dev(gq, "grad_q", torch.float32, q.shape, like=q) if gq is not None else None)
     mode_i = _MODES[mode]
     ws_bytes = backward_workspace_bytes(B, H, m, mode_i)
-    # the merged scatter takes an order in place of its own sort, and a larger
-    # workspace than an order where it may sort the pairs themselves
-    merged_with_order = order is not None and resolved_mode(B, H, mode_i) == "merged" and ws_bytes <= order.numel()
-    if ws_bytes and workspace is None and not merged_with_order:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
+    if ws_bytes and workspace is None:
+        workspace = _new_workspace(ws_bytes, B, H, N, mode_i, k, order, q)
     if k != NB:
         if order is not None or lists is not None:
             raise LramError("order and saved lists are offered for k = 32 only")
@@ -420,7 +429,7 @@ def theta_backward(z: torch.Tensor, table: torch.Tensor, K: Sequence[int], grad_
     mode_i = _MODES[mode]
     ws_bytes = backward_workspace_bytes(B, H, m, mode_i)
     if ws_bytes and workspace is None:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=z.device)
+        workspace = _new_workspace(ws_bytes, B, H, N, mode_i, NB, None, z)
     _check(lib.lram_theta_backward(
         _dev(z, "z", torch.float32), B, H, _K(K), _dev(table, "table", like=z), _table_dtype(table), N, m,
         _dev(grad_out, "grad_out", torch.float32, z.shape[:-1] + (m,), like=z),

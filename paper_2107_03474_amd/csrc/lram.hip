@@ -5,25 +5,30 @@
 // kernel f(r) = (1 - r^2/8)^4 (Sec. 2.5), truncated to the 32 closest points
 // and found through the symmetry reduction of Sec. 2.6, plus its backward.
 //
-// Work decomposition (one wave = 64 lanes, up to 64 lookups per wave):
-//   phase A  lane-per-lookup: wrap, E8 closest point (D8 and D8+1/2 decoders
-//            with a parity fix), and the signed permutation that carries the
-//            offset into the fundamental region F; the result (a 96-byte
-//            "frame") goes to LDS.
-//   phase B  wave-per-lookup: the wave builds three 8x8 per-query tables in LDS
-//            (squared coordinate error, location contribution, coordinate
-//            error) indexed by (original coordinate, candidate coordinate
-//            value), scans the 232 candidate points of F (4 per lane) with one
-//            v_perm + one LDS read per coordinate, selects the closest 32 (a
-//            64-bucket histogram of the fp32 distance bits, then a ballot /
-//            popcount bisection inside one bucket), and then gather-reduces
-//            (forward) or scatters and forms dq (backward).  The row loads of
-//            lookup t are in flight while the wave searches lookup t+1
-//            (neighbour lists are double-buffered).
-// The value-gradient scatter has three forms: row atomics, a location sort
-// with a segmented reduction, and a per-batch merge of lookups ordered by
-// their closest lattice point.  No MFMA: the path is a gather / scatter bound
-// by HBM and by memory-side atomics, not a contraction.
+// Work decomposition (one wave = 64 lanes, tiles of 16 lookups):
+//   phase A  four lanes per lookup: wrap, E8 closest point (D8 and D8+1/2
+//            decoders with a parity fix), and the signed permutation that
+//            carries the offset into the fundamental region F; the result (a
+//            112-byte "frame") goes to LDS.
+//   tile     a wave per 16 lookups: the distances of the 232 candidate points
+//            of F to the 16 queries from the matrix cores, a threshold per
+//            lookup that separates the closest 32, and a margin check that
+//            makes the choice the definition's; a lookup that fails it is
+//            searched by the whole wave (the general search, which lists of
+//            16, 64 and the whole support always take: distances from the
+//            tables below, a histogram of the fp32 distance bits, a ballot
+//            bisection inside one bucket).
+//   pairs    two lookups at a time: three 8x8 per-query tables in LDS (squared
+//            coordinate error, location contribution, coordinate error)
+//            indexed by (original coordinate, candidate coordinate value), one
+//            v_perm + one LDS read per coordinate and neighbour, and then
+//            gather-reduce (forward) or scatter and dq (backward).  The row
+//            loads of a pair are in flight while the next pair is finished.
+// The value-gradient scatter has four forms: row atomics, a location sort with
+// a segmented reduction, a per-batch merge of lookups ordered by their closest
+// lattice point, and, for tables small against the batch, a location sort with
+// one row atomic per run.  The path is a gather / scatter bound by HBM and by
+// memory-side atomics; its only contraction is the tile's distances.
 
 #include <hip/hip_runtime.h>
 #include <algorithm>
@@ -699,8 +704,10 @@ int backward_impl(const float* in, int64_t B, int64_t H, const int32_t K[8], con
       if (!workspace || ws_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255)) return LRAM_EWORKSPACE;
       order_layout(L, &o, reinterpret_cast<char*>(workspace));
     }
-    if (width == NB && grad_table && workspace && runs_chosen(L, P.N, m) && ws_bytes >= merged_bytes(L) &&
-        (reinterpret_cast<uintptr_t>(workspace) & 255) == 0) {
+    // a workspace that shares memory with the order stays untouched: the caller may use the order again
+    const bool shared = order && workspace && overlap(order, order_bytes / 4, workspace, ws_bytes / 4);
+    if (width == NB && grad_table && workspace && !shared && runs_chosen(L, P.N, m) &&
+        ws_bytes >= merged_bytes(L) && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0) {
       Radix<uint2> r{};
       runs_layout(L, &r, reinterpret_cast<char*>(workspace));
       return dispatch<BwdRunsLaunch>(dtype, m, in, P, table, grad_out, grad_table, grad_in, r, th, saved, stream);

@@ -94,6 +94,13 @@ def test_other_callers():
     table, G = _compare(q, K, m, torch.float32, 1, lambda *a: lram.backward(*a, mode="merged", workspace=small))
     _compare(q, K, m, torch.float32, 1, lambda *a: lram.backward(*a, mode="merged", order=lram.order(q, K)))
 
+    # one buffer for both: the order is still there afterwards
+    both = torch.empty(lram.backward_workspace_bytes(L, 1, m, "merged"), dtype=torch.uint8, device=DEV)
+    both[:nbytes] = lram.order(q, K)[:nbytes]
+    before = both.clone()
+    _compare(q, K, m, torch.float32, 1, lambda *a: lram.backward(*a, mode="merged", order=both, workspace=both))
+    assert torch.equal(both, before)
+
     def noalloc(q, table, K, G):
         gt = torch.zeros(table.shape, device=DEV)
         gq = torch.empty_like(q)
