@@ -15,11 +15,13 @@ namespace {
 // A workgroup merges its lookups' pairs first: 64 lookups leave (location, w)
 // pairs in LDS, a 4,096-entry open-addressing hash over the search's LDS sums
 // the weights of every distinct location, and each sum is added with one
-// atomic.  Bound by the scalar atomics (each a 64-byte request at the memory
-// side, about 16 G/s): 262,144 lookups of half clustered queries on 2^22 rows,
-// flags and statistics included, took 713 us pair by pair and take 654 us
-// merged.  Hot locations also receive fewer, larger terms, so their fp32 sums
-// are rounded less often.
+// atomic.  Bound by the memory side's atomic requests of 64 bytes, and by those
+// that follow each other on one line.  Flags, histogram and statistics of
+// 262,144 lookups, pair by pair / merged with the entries scattered / with a
+// line's entries together (hist_entry): half clustered on 2^22 rows 713 / 654 /
+// 563 us; of 240,000 projected lookups on 2^16 rows 745 / 785 / 452 us, of
+// 720,000 on 2^15 rows 2,360 / 2,546 / 1,103 us.  Hot locations also receive
+// fewer, larger terms, so their fp32 sums are rounded less often.
 struct alignas(16) HistLds {
   int32_t loc[MERGE_P];
   float w[MERGE_P];
@@ -31,6 +33,13 @@ struct alignas(16) HistLds {
     } hash;
   };
 };
+
+// First hash entry of a location: the 16 locations of a 64-byte line of the
+// histogram take 16 consecutive entries, so those a batch reads leave in one
+// instruction, as one request.
+__device__ __forceinline__ uint32_t hist_entry(uint32_t l) {
+  return ((((l >> 4) * 0x9E3779B1u) >> (32 - (MERGE_HBITS - 4))) << 4) | (l & 15);
+}
 
 __global__ void __launch_bounds__(THREADS, 3) k_access_hist(const float* __restrict__ q, Params P,
                                                             float* __restrict__ hist) {
@@ -69,7 +78,7 @@ __global__ void __launch_bounds__(THREADS, 3) k_access_hist(const float* __restr
   for (int k = 0; k < MERGE_PPT; ++k) {
     const int32_t l = S.loc[k * THREADS + t];
     if (l >= 0) {
-      uint32_t e = ((uint32_t)l * 0x9E3779B1u) >> (32 - MERGE_HBITS);
+      uint32_t e = hist_entry((uint32_t)l);
       while (true) {
         const int32_t old = atomicCAS(&S.hash.tag[e], MERGE_EMPTY, l);
         if (old == MERGE_EMPTY || old == l) break;
