@@ -68,22 +68,6 @@ bool misaligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3) !=
 // inline / staged: 16,383 and 16,384 lookups 25.3 / 24.8 us).
 constexpr int64_t STAGE_MIN = 16384;
 
-// Lookups per wave.  A wave that searches tiles spends a tile's cost whatever
-// the tile holds (about 900 instructions; 120 more for each pair of lookups), so
-// small batches put two lookups on a wave, more once every SIMD has two
-// waves, up to a whole tile from 32,768 lookups on.  Forward, lookups per
-// wave 1 / 2 / 4 / 8 / 16 / 32 / 64: 4,096 lookups 16.2 / 12.1 / 12.0 / 13.8 / 17 / - / - us;
-// 16,384 lookups 48 / 28 / 21 / 19.9 / 22 / 37 / -; 65,536 - / 95 / 67 / 55 / 51 / 57 / 87;
-// 262,144 (2^20 rows, m = 64 fp32) - / - / 352 / 309 / 304 / 305 / 320.  The general search
-// (tile = false) costs the same for every lookup: one each until every SIMD
-// has four waves, then up to 64.
-int32_t lookups_per_wave(int64_t L, bool tile) {
-  const int64_t simds = 256 * 4;
-  if (!tile) return (int32_t)std::min<int64_t>(std::max<int64_t>((L + 4 * simds - 1) / (4 * simds), 1), WAVE);
-  const int64_t lpw = (L + 2 * simds - 1) / (2 * simds);
-  return (int32_t)std::min<int64_t>(std::max<int64_t>((lpw + 1) / 2 * 2, 2), L < (int64_t(1) << 19) ? TILE : 2 * TILE);
-}
-
 int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t* L, Params* P) {
   if (B < 0 || H < 0 || !K) return LRAM_EINVAL;
   if (H != 0 && B > INT64_MAX / H) return LRAM_EINVAL;
@@ -131,10 +115,7 @@ int launched() {
   return LRAM_OK;
 }
 
-unsigned grid_for(const Params& P) {
-  const int64_t per_block = (int64_t)P.lpw * WAVES;
-  return (unsigned)((P.L + per_block - 1) / per_block);
-}
+unsigned grid_for(const Params& P) { return (unsigned)blocks_for(P.L, P.lpw); }
 
 template <template <int, int> class Launcher, typename... Args>
 int dispatch(int dtype, int32_t m, Args... args) {
@@ -901,10 +882,16 @@ int lram_access_histogram(const float* q, int64_t B, int64_t H, const int32_t K[
   if (rc) return rc;
   if (L == 0) return LRAM_OK;
   if (!hist || misaligned4(hist)) return LRAM_EINVAL;
-  P.lpw = std::min<int32_t>(P.lpw, TILE);  // one tile to a wave
-  hipLaunchKernelGGL(k_access_hist, dim3(grid_for(P)), dim3(THREADS), 0, (hipStream_t)stream, q, P, hist);
-  return launched();
+  for (int64_t l0 = 0; l0 < L; l0 += HIST_PIECE) {
+    P.L = std::min(L - l0, HIST_PIECE);
+    P.lpw = std::min<int32_t>(lookups_per_wave(P.L, true), TILE);  // one tile to a wave
+    hipLaunchKernelGGL(k_access_hist, dim3(grid_for(P)), dim3(THREADS), 0, (hipStream_t)stream, q + 8 * l0, P, hist);
+    if ((rc = launched())) return rc;
+  }
+  return LRAM_OK;
 }
+
+
 
 int lram_access_stats(const float* hist, int64_t N, double* out, void* stream) {
   if (N <= 0 || !hist || !out || misaligned4(hist) || (reinterpret_cast<uintptr_t>(out) & 7)) return LRAM_EINVAL;

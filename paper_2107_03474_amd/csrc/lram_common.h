@@ -7,12 +7,11 @@
 
 #include <cstddef>
 
+#include "lram_plain.h"
+
 namespace {
 
 constexpr int NB = LRAM_NEIGHBOURS;  // 32, Sec. 2.6
-constexpr int WAVE = 64;
-constexpr int WAVES = 4;                 // waves per workgroup
-constexpr int THREADS = WAVE * WAVES;
 constexpr int NS_STRICT = (E8_NSTRICT + WAVE - 1) / WAVE;      // 4 candidate slots per lane
 constexpr int NS_BOUND = (E8_NBOUNDARY + WAVE - 1) / WAVE;     // 3
 constexpr int NS_ALL = NS_STRICT + NS_BOUND;
@@ -26,7 +25,6 @@ static_assert(NV == 8, "each per-query table row holds the 8 possible candidate 
 static_assert(WAVES <= 4, "the wave index and the list of a pair are folded into byte-sized LDS offsets");
 constexpr int KMAX = 8192;  // per-coordinate torus side bound: lattice coordinates fit in int16
 constexpr int XCDS = 8;  // accelerator complex dies of an MI355X
-constexpr int64_t LMAX = (int64_t(1) << 31) - 1;  // lookups per call
 
 // Candidates tied (equal fp32 distance bits) at the k-th place of a truncated
 // list.  Large sets of equal distances inside the support arise only from the
@@ -65,10 +63,6 @@ struct Params {
   int64_t L;
   double cK[8];      // K_i / (2 pi): torus coordinate per radian of arg z_i (activation layer)
 };
-
-// Lookups that a wave searches together: phase A spreads each over four lanes,
-// the tile selection over four lanes of a matrix product's result.
-constexpr int TILE = 16;
 
 // Per-lookup frame written by phase A (112 bytes).
 struct alignas(16) Frame {

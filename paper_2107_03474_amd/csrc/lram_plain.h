@@ -1,0 +1,51 @@
+// lram_plain.h -- part of liblram.
+//
+// Launch geometry in plain C++ (no HIP), so that a host compiler can check it
+// over every size the entry points accept.
+
+#pragma once
+
+#include <stdint.h>
+
+namespace {
+
+constexpr int WAVE = 64;
+constexpr int WAVES = 4;                 // waves per workgroup
+constexpr int THREADS = WAVE * WAVES;
+// Lookups that a wave searches together: phase A spreads each over four lanes,
+// the tile selection over four lanes of a matrix product's result.
+constexpr int TILE = 16;
+constexpr int64_t SIMDS = 256 * 4;
+constexpr int64_t LMAX = (int64_t(1) << 31) - 1;  // lookups per call
+
+// Lookups per wave.  A wave that searches tiles spends a tile's cost whatever
+// the tile holds (about 900 instructions; 120 more for each pair of lookups), so
+// small batches put two lookups on a wave, more once every SIMD has two
+// waves, up to a whole tile from 32,768 lookups on.  Forward, lookups per
+// wave 1 / 2 / 4 / 8 / 16 / 32 / 64: 4,096 lookups 16.2 / 12.1 / 12.0 / 13.8 / 17 / - / - us;
+// 16,384 lookups 48 / 28 / 21 / 19.9 / 22 / 37 / -; 65,536 - / 95 / 67 / 55 / 51 / 57 / 87;
+// 262,144 (2^20 rows, m = 64 fp32) - / - / 352 / 309 / 304 / 305 / 320.  The general search
+// (tile = false) costs the same for every lookup: one each until every SIMD
+// has four waves, then up to 64.  From 2^30 lookups on a wave takes 64 either way:
+// 32 would make a grid of 2^32 work-items, which no launch accepts.
+constexpr int32_t lookups_per_wave(int64_t L, bool tile) {
+  if (!tile || L >= (int64_t(1) << 30)) {
+    const int64_t lpw = (L + 4 * SIMDS - 1) / (4 * SIMDS);
+    return (int32_t)(lpw < 1 ? 1 : (lpw > WAVE ? WAVE : lpw));
+  }
+  const int64_t lpw = ((L + 2 * SIMDS - 1) / (2 * SIMDS) + 1) / 2 * 2;
+  const int64_t top = L < (int64_t(1) << 19) ? TILE : 2 * TILE;
+  return (int32_t)(lpw < 2 ? 2 : (lpw > top ? top : lpw));
+}
+
+// Workgroups that cover L lookups, lpw to a wave.
+constexpr int64_t blocks_for(int64_t L, int32_t lpw) {
+  const int64_t per_block = (int64_t)lpw * WAVES;
+  return (L + per_block - 1) / per_block;
+}
+
+// Lookups per launch of the access histogram, whose waves take one tile each:
+// four work-items per lookup.  Larger batches are launched in pieces.
+constexpr int64_t HIST_PIECE = int64_t(1) << 29;
+
+}  // namespace

@@ -1,0 +1,74 @@
+"""Launch geometry on the CPU: lram_plain.h compiled by the host compiler.
+
+A launch takes fewer than 2^32 work-items; every batch size that the entry points accept (L < 2^31) has to stay below
+that in the kernels that cover the batch with lookups_per_wave, and in the access histogram's pieces.
+"""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2107_03474_amd", "csrc")
+
+PROGRAM = r"""
+#include <algorithm>
+#include <cstdio>
+#include "lram_plain.h"
+int main() {
+  const int64_t items = int64_t(1) << 32;
+  for (int s = 0; s <= 31; ++s)
+    for (int64_t d = -200; d <= 200; ++d) {
+      const int64_t L = (int64_t(1) << s) + d;
+      if (L < 1 || L > LMAX) continue;
+      for (bool tile : {false, true}) {
+        const int32_t lpw = lookups_per_wave(L, tile);
+        const int64_t blocks = blocks_for(L, lpw);
+        if (lpw < 1 || lpw > WAVE || blocks * WAVES * lpw < L || blocks * THREADS >= items)
+          std::printf("L = %lld tile = %d: %d lookups per wave, %lld blocks\n", (long long)L, tile, lpw, (long long)blocks);
+      }
+      int64_t covered = 0;
+      for (int64_t l0 = 0; l0 < L; l0 += HIST_PIECE) {
+        const int64_t n = std::min(L - l0, HIST_PIECE);
+        const int64_t blocks = blocks_for(n, std::min<int32_t>(lookups_per_wave(n, true), TILE));
+        covered += n;
+        if (blocks * THREADS >= items) std::printf("histogram L = %lld: %lld blocks\n", (long long)L, (long long)blocks);
+      }
+      if (covered != L) std::printf("histogram L = %lld: %lld covered\n", (long long)L, (long long)covered);
+    }
+  return 0;
+}
+"""
+
+
+def run_host(tmp_path, program):
+    """Output of a C++ program that includes the library's plain headers."""
+    src, exe = tmp_path / "t.cc", tmp_path / "t"
+    src.write_text(program)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
+
+
+def test_every_accepted_batch_launches(tmp_path):
+    assert run_host(tmp_path, PROGRAM) == ""
+
+
+@pytest.mark.gpu
+def test_histogram_of_a_billion_lookups():
+    """2^30 lookups, the first size whose tiles would make 2^32 work-items in one launch, on 2^20 locations: the total
+    is the sum of the weights of a sample of the same queries (a fp32 histogram entry sums about 32,768 terms, partly
+    merged before: relative error below 2^15 2^-24 = 2e-3)."""
+    import torch
+
+    import paper_2107_03474_amd as lram
+
+    K, L, dev = (4, 4, 4, 4, 8, 8, 8, 8), 1 << 30, "cuda"
+    if torch.cuda.mem_get_info()[0] < 60 << 30:
+        pytest.skip("needs 34 GB for the queries")
+    g = torch.Generator(device=dev)
+    g.manual_seed(0)
+    piece = torch.rand((1 << 20, 8), generator=g, device=dev) * torch.tensor(K, device=dev)
+    q = piece.repeat(L >> 20, 1)
+    hist = lram.access_histogram(q, K).double()
+    ref = lram.access_histogram(piece, K).double() * (L >> 20)
+    assert ((hist - ref).abs() <= 2e-3 * ref).all()
