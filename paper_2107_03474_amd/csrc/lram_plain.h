@@ -1,7 +1,7 @@
 // lram_plain.h -- part of liblram.
 //
-// Launch geometry in plain C++ (no HIP), so that a host compiler can check it
-// over every size the entry points accept.
+// Launch geometry and index arithmetic in plain C++ (no HIP), so that a host
+// compiler can check them over every size the entry points accept.
 
 #pragma once
 
@@ -36,6 +36,20 @@ constexpr int32_t lookups_per_wave(int64_t L, bool tile) {
   const int64_t lpw = ((L + 2 * SIMDS - 1) / (2 * SIMDS) + 1) / 2 * 2;
   const int64_t top = L < (int64_t(1) << 19) ? TILE : 2 * TILE;
   return (int32_t)(lpw < 2 ? 2 : (lpw > top ? top : lpw));
+}
+
+// h mod K for K even, at least 2, and h in [-K - 3, K + 3] (as uint32_t: two's
+// complement): a parity for K = 2; otherwise h + 2 K lies in [K - 3, 3 K + 3], never
+// negative, and three periods come off one by one, each by an unsigned minimum (a
+// step too far leaves the range).  The last minimum keeps any other h
+// below K, so that nothing can address outside the table.
+constexpr uint32_t torus_coord(uint32_t h, uint32_t K) {
+  auto least = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
+  uint32_t Y = h + 2u * K;
+  Y = least(Y, Y - K);
+  Y = least(Y, Y - K);
+  Y = least(Y, Y - K);
+  return K == 2u ? (h & 1u) : least(Y, K - 1u);
 }
 
 // Workgroups that cover L lookups, lpw to a wave.

@@ -585,18 +585,8 @@ struct Search {
     const int k = ((int)r.y >> 1) + ((tp ^ neg) - neg);
     const float e = __uint_as_float(r.x) - (float)k;
     const float e2 = e * e;
-    // floor(k / 2) mod K: |x_i| < 2K, |x_i - c_i| <= 2 and |p| <= 4 put it within
-    // [-K-3, K+3], one period up within [-3, 2K+3]; for K >= 4 two periods down
-    // and one up, each taken by an unsigned minimum (a step the wrong way
-    // leaves the range), bring it into [0, K); K = 2 is a parity.  The last
-    // minimum makes sure no rounding surprise can ever address outside the table.
-    const uint32_t K = (uint32_t)tK;
-    const uint32_t half = (uint32_t)(k >> 1);
-    uint32_t Y = half + K;
-    Y = min(Y, Y - K);
-    Y = min(Y, Y - K);
-    Y = min(Y, Y + K);
-    Y = K == 2u ? (half & 1u) : min(Y, K - 1u);
+    // floor(k / 2) mod K: |x_i| < 2K, |x_i - c_i| <= 2 and |p| <= 4 put floor(k / 2) within [-K-3, K+3]
+    const uint32_t Y = torus_coord((uint32_t)(k >> 1), (uint32_t)tK);
     const uint32_t sl = Y * tS + (tN0 & (uint32_t)-(k & 1));
     const uint32_t o = toff + 32u * (uint32_t)h;
     *reinterpret_cast<float*>(reinterpret_cast<char*>(S.qt) + o) = e2;

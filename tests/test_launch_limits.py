@@ -1,4 +1,4 @@
-"""Launch geometry on the CPU: lram_plain.h compiled by the host compiler.
+"""Launch geometry and index arithmetic on the CPU: lram_plain.h compiled by the host compiler.
 
 A launch takes fewer than 2^32 work-items; every batch size that the entry points accept (L < 2^31) has to stay below
 that in the kernels that cover the batch with lookups_per_wave, and in the access histogram's pieces.
@@ -51,6 +51,29 @@ def run_host(tmp_path, program):
 
 def test_every_accepted_batch_launches(tmp_path):
     assert run_host(tmp_path, PROGRAM) == ""
+
+
+WRAP = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "lram_plain.h"
+int main() {
+  for (int K = 2; K <= 8192; K += K < 64 ? 2 : 62)
+    for (int h = -K - 3; h <= K + 3; ++h) {
+      const uint32_t want = (uint32_t)(((h % K) + K) % K), got = torus_coord((uint32_t)h, (uint32_t)K);
+      if (got != want) std::printf("K = %d h = %d: %u, not %u\n", K, h, got, want);
+    }
+  for (uint32_t K : {2u, 4u, 6u, 8192u})
+    for (uint32_t h = 0; h < 0xFFFF0000u; h += 65521u)
+      if (torus_coord(h, K) >= K) std::printf("K = %u h = %u: outside\n", K, h);
+  return 0;
+}
+"""
+
+
+def test_torus_coordinates(tmp_path):
+    """The wrap of the per-query tables over the whole range of a point's coordinate, and inside the table for any."""
+    assert run_host(tmp_path, WRAP) == ""
 
 
 @pytest.mark.gpu
