@@ -835,10 +835,13 @@ struct Search {
 //   3. the choice is accepted if no candidate -- of the 64, of the ten (all
 //      below) or of the remaining 158 (all above) -- lies within TILE_EPS of
 //      the threshold and the threshold is clear of the support's edge: the
-//      recipe's order of the two sides is then the same (the product stays
-//      within 24 half units of 2^-21 = 5.7e-6 quarter units of the distance in
-//      exact arithmetic, 1e-6 observed, and the recipe within 1e-6).  Otherwise the lookup takes the general search (about
-//      1 in 1,000 random queries, and queries next to a lattice point or hole);
+//      recipe's order of the two sides is then the same.  In quarter units: a
+//      distance is 24 additions of sums below 8, each within one unit of
+//      2^-21 whether the matrix cores round to nearest or truncate (1.15e-5
+//      together; 1e-6 observed), z moves it by 2.4e-7 and the recipe's own
+//      rounding by 7.8e-7: 1.25e-5 in all.  Otherwise the lookup
+//      takes the general search (about 1 in 700 random queries, and queries
+//      next to a lattice point or hole);
 //   4. the recipe's distances, locations and weights of the chosen 32 alone are
 //      formed two lookups at a time, one neighbour to a lane.
 // About 75 VALU instructions per lookup.  Measured before and after: lists of
@@ -849,8 +852,8 @@ struct Search {
 // six others, blocks 5-14 the others.
 
 constexpr int TILE_PICK = NB - TILE_ALWAYS;
-constexpr float TILE_EPS = 1e-5f;    // quarter units: 4e-5 in distance^2
-constexpr float TILE_STEP = 1.4e-5f; // a threshold placed next to a candidate keeps this far from it
+constexpr float TILE_EPS = 1.5e-5f;  // quarter units: 6e-5 in distance^2
+constexpr float TILE_STEP = 2e-5f;   // a threshold placed next to a candidate keeps this far from it
 constexpr float TILE_EDGE = 7.999f;  // as KEY_SUSPECT
 constexpr int TILE_ROUNDS = 7;
 

@@ -52,13 +52,19 @@ def _parts(z):
     return out
 
 
-def _quarter_distances(z):
+def _toward_zero(d):
+    """fp64 -> fp32, truncated."""
+    f = d.astype(np.float32)
+    return np.where(np.abs(f.astype(np.float64)) > np.abs(d), np.nextafter(f, np.float32(0)), f)
+
+
+def _quarter_distances(z, rounding=lambda d: d.astype(np.float32)):
     """|p|^2/4 - z.p/2 of every strict candidate as a matrix product forms it: exact products of bf16 numbers, an fp32
-    rounding after every addition (the order inside the matrix cores is theirs)."""
+    rounding after every addition (the order inside the matrix cores and their rounding are theirs)."""
     d = np.broadcast_to(((STRICT ** 2).sum(1) / 4).astype(np.float32), (z.shape[0], len(STRICT))).copy()
     for part in _parts(z):
         for r in range(8):
-            d = (d.astype(np.float64) + part[:, r:r + 1].astype(np.float64) * STRICT[None, :, r]).astype(np.float32)
+            d = rounding(d.astype(np.float64) + part[:, r:r + 1].astype(np.float64) * STRICT[None, :, r])
     return d
 
 
@@ -78,10 +84,9 @@ def near_ties(gap, n, seed, K=(8,) * 8):
     return np.mod(q, np.asarray(K)).astype(np.float32)
 
 
-def _accepted(z, step):
+def _accepted(z, step, q):
     """Accepted lookups; the threshold at the middle of the gap (step None), or STEP past either of its ends (the
-    thresholds that the kernel's own steps take)."""
-    q = _quarter_distances(z)
+    thresholds that the kernel's own steps take).  q: the candidates' distances."""
     v = np.sort(q[:, VAR], axis=1)
     if step is None:
         T = (v[:, 21] + v[:, 22]) * np.float32(0.5)
@@ -104,18 +109,31 @@ def _check(q, K, least):
     z = np.zeros_like(y)
     np.put_along_axis(z, r, (y * s).astype(np.float32), 1)
     nb = oracle.neighbors(q, K)
-    # error of the product against exact arithmetic: 24 additions of sums below 8, half a unit of 2^-21 each
     exact = ((STRICT ** 2).sum(1) / 4.0)[None] - 0.5 * z.astype(np.float64) @ STRICT.T
-    assert np.abs(_quarter_distances(z) - exact).max() < 24 * 2.0 ** -22 < EPS
-    for step in (None, 1, -1):
-        ok, below = _accepted(z, step)
-        assert ok.mean() >= least, (step, ok.mean())
-        for l in np.nonzero(ok)[0]:
-            p = STRICT[below[l]]
-            k = c[l] + s[l] * p[:, r[l]]
-            assert len(p) == 32
-            slots = oracle.locations(k.astype(np.int32), K)
-            assert set(slots.tolist()) == set(nb["slot"][l].tolist()), (step, l, q[l])
+    for rounding, unit in ((lambda d: d.astype(np.float32), 2.0 ** -22), (_toward_zero, 2.0 ** -21)):
+        # against exact arithmetic: 24 additions of sums below 8, half a unit of 2^-21 each, a whole one truncated
+        d = _quarter_distances(z, rounding)
+        assert np.abs(d - exact).max() < 24 * unit
+        for step in (None, 1, -1):
+            ok, below = _accepted(z, step, d)
+            assert ok.mean() >= least, (step, ok.mean())
+            for l in np.nonzero(ok)[0]:
+                p = STRICT[below[l]]
+                k = c[l] + s[l] * p[:, r[l]]
+                assert len(p) == 32
+                slots = oracle.locations(k.astype(np.int32), K)
+                assert set(slots.tolist()) == set(nb["slot"][l].tolist()), (step, l, q[l])
+
+
+def test_margin():
+    """The margin covers, in quarter units: the product's error whichever way the matrix cores round (24 additions of
+    sums below 8, one unit of 2^-21 each at most); z's (differences of norm at most 2, so 2 * 2^-24 in norm, times
+    |p| / 2 <= 2); and the recipe's (seven additions below 8, squares and differences each rounded by 2^-24 relative,
+    squares summing below 8)."""
+    product = 24 * 2.0 ** -21
+    z = 2 * 2.0 ** -24 * 2
+    recipe = (7 * 2.0 ** -22 + 8 * 2.0 ** -24 + 2 * 8 * 2.0 ** -24) / 4
+    assert product + z + recipe < EPS < STEP
 
 
 @pytest.mark.parametrize("K", [(4,) * 8, (14,) * 8, (4, 6, 8, 10, 4, 4, 6, 4)])
