@@ -171,8 +171,8 @@ int lram_forward(const float* q, int64_t B, int64_t H, const int32_t K[8], const
  * lram_backward_workspace_bytes -- device workspace needed by lram_backward
  * (and lram_backward_k, lram_theta_backward) for L = B*H lookups in the given
  * scatter mode (0 for LRAM_SCATTER_ATOMIC; the same for every k; the merged
- * scatter can do with an order buffer, lram_order_bytes, and asks for 768 bytes
- * per lookup from 65,536 to 524,288 lookups, where it may sort the pairs).
+ * scatter can do with an order buffer, lram_order_bytes, and asks for about
+ * 800 bytes per lookup from 65,536 to 524,288 lookups, where it may sort the pairs).
  */
 int lram_backward_workspace_bytes(int64_t B, int64_t H, int32_t m, int mode, size_t* bytes);
 

@@ -294,12 +294,14 @@ def backward_workspace_bytes(B: int, H: int, m: int, mode="auto") -> int:
     return n.value
 
 
-def _new_workspace(nbytes: int, B: int, H: int, N: int, mode: int, k: int, order, like) -> Optional[torch.Tensor]:
+def _new_workspace(nbytes: int, B: int, H: int, N: int, m: int, mode: int, k: int, want_grad_table: bool, order,
+                   like) -> Optional[torch.Tensor]:
     """A backward's workspace of ``nbytes``.  The merged scatter needs only an
     order's bytes, none when it is given an order, unless it may sort the pairs:
-    lists of 32 and at least two pairs per row."""
+    lists of 32, a table gradient and enough pairs per row (two for m = 64, four
+    for m = 32)."""
     if resolved_mode(B, H, mode) == "merged":
-        if k != NB or NB * B * H < 2 * N:
+        if k != NB or not want_grad_table or NB * B * H < (2 if m == 64 else 4) * N:
             nbytes = order_layout(B, H)[0]
         if order is not None and nbytes <= order.numel():
             return None
@@ -331,7 +333,7 @@ def backward(q: torch.Tensor, table: torch.Tensor, K: Sequence[int], grad_out: t
     mode_i = _MODES[mode]
     ws_bytes = backward_workspace_bytes(B, H, m, mode_i)
     if ws_bytes and workspace is None:
-        workspace = _new_workspace(ws_bytes, B, H, N, mode_i, k, order, q)
+        workspace = _new_workspace(ws_bytes, B, H, N, m, mode_i, k, grad_table is not False, order, q)
     if k != NB:
         if order is not None or lists is not None:
             raise LramError("order and saved lists are offered for k = 32 only")
@@ -429,7 +431,7 @@ def theta_backward(z: torch.Tensor, table: torch.Tensor, K: Sequence[int], grad_
     mode_i = _MODES[mode]
     ws_bytes = backward_workspace_bytes(B, H, m, mode_i)
     if ws_bytes and workspace is None:
-        workspace = _new_workspace(ws_bytes, B, H, N, mode_i, NB, None, z)
+        workspace = _new_workspace(ws_bytes, B, H, N, m, mode_i, NB, grad_table is not False, None, z)
     _check(lib.lram_theta_backward(
         _dev(z, "z", torch.float32), B, H, _K(K), _dev(table, "table", like=z), _table_dtype(table), N, m,
         _dev(grad_out, "grad_out", torch.float32, z.shape[:-1] + (m,), like=z),

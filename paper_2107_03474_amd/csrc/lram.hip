@@ -187,7 +187,8 @@ struct Carver {
 // (ka, va) and (kb, vb), and the sort's scratch: hdr [SORT_HDR_WORDS] (global
 // digit counts, failure word, gate-count partials) followed by the count
 // states [SORT_PASSES_MAX][tiles + groups][RADIX], all cleared by the sort
-// itself.
+// itself.  States are 8 bytes where a layout keeps to that (an order's bytes are
+// documented) or the sort is large, 4 where the sort reads them as such.
 template <typename V>
 struct Radix {
   uint32_t *ka, *kb;
@@ -200,13 +201,13 @@ struct Radix {
 };
 
 template <typename V>
-void carve_radix_scratch(int64_t n, Carver& c, Radix<V>* r) {
+void carve_radix_scratch(int64_t n, Carver& c, Radix<V>* r, bool always_wide = true) {
   const int64_t tiles = (n + SORT_TILE - 1) / SORT_TILE;
   const int64_t states = tiles + (tiles + LOOKBACK_GROUP - 1) / LOOKBACK_GROUP;
   // hdr and the states are contiguous (SORT_HDR_WORDS * 4 is a multiple of 256)
   static_assert((SORT_HDR_WORDS * 4) % 256 == 0, "sort scratch layout");
   char* h = c.take((size_t)SORT_HDR_WORDS * 4);
-  char* st = c.take((size_t)SORT_PASSES_MAX * states * RADIX * 8);
+  char* st = c.take((size_t)SORT_PASSES_MAX * states * RADIX * (always_wide || n >= SORT_SMALL_STATES ? 8 : 4));
   if (r) {
     r->hdr = (uint32_t*)h;
     r->state = (uint64_t*)st;
@@ -350,7 +351,7 @@ size_t runs_layout(int64_t L, Radix<uint2>* r, char* base) {
   char* kb = c.take(n * 4);
   char* va = c.take(n * 8);
   char* vb = c.take(n * 8);
-  carve_radix_scratch<uint2>(n, c, r);
+  carve_radix_scratch<uint2>(n, c, r, false);
   if (r) {
     r->ka = (uint32_t*)ka;
     r->kb = (uint32_t*)kb;
@@ -370,7 +371,7 @@ size_t runs_layout(int64_t L, Radix<uint2>* r, char* base) {
 // so the line lies at two pairs per row (m = 64) and four (m = 32; its row
 // atomics cost half).  Lookups around very few centres (64) merge better by
 // batches (657 / 804 at 2^18 rows): the queries are not known here.
-// The runs need their workspace (768 bytes per lookup, 410 MB at RUNS_MAX); an
+// The runs need their workspace (801 bytes per lookup, 420 MB at RUNS_MAX); an
 // order-sized one, and batches outside [RUNS_MIN, RUNS_MAX], keep the batch merge.
 constexpr int64_t RUNS_MIN = 65536, RUNS_MAX = int64_t(1) << 19;
 bool runs_chosen(int64_t L, uint32_t N, int32_t m) {

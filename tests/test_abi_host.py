@@ -8,6 +8,8 @@ import subprocess
 
 import pytest
 
+import torch
+
 import paper_2107_03474_amd as lram
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -212,6 +214,28 @@ def test_auto_mode(lib):
     n = ctypes.c_size_t(1)
     assert lib.lram_backward_workspace_bytes(4, 1, 32, 3, ctypes.byref(n)) == 0 and n.value == 0
     assert lib.lram_backward_workspace_bytes(8192, 16, 32, 3, ctypes.byref(n)) == 0 and n.value >= 131072 * 16
+
+
+def test_merged_workspace_sizes(lib):
+    """The binding's own workspace: an order's bytes (none when it is given one) unless the merged scatter may sort the
+    pairs; the sorted runs' 24 bytes per pair and 4-byte look-back states (four passes of 257 digits per 4,096 pairs)."""
+    from paper_2107_03474_amd import _new_workspace, backward_workspace_bytes, order_layout
+
+    like = torch.empty(0)
+    for L in (65535, 65536, 131072, 524288, 524289):
+        order_bytes = order_layout(L, 1)[0]
+        order = torch.empty(order_bytes, dtype=torch.uint8)
+        for m, per_row in ((32, 4), (64, 2)):
+            whole = backward_workspace_bytes(L, 1, m, "merged")
+            assert (whole > order_bytes) == (65536 <= L <= 524288)
+            assert whole <= max(order_bytes, 32 * L * (24 + 1.04 * 4 * 4 * 256 / 4096) + (1 << 17))
+            most = 32 * L // per_row  # rows of the largest table whose pairs are sorted
+            for N, k, table, runs in ((most, 32, True, True), (most + 1, 32, True, False), (most, 16, True, False),
+                                      (most, 32, False, False)):
+                want = whole if runs else order_bytes
+                assert _new_workspace(whole, L, 1, N, m, 2, k, table, None, like).numel() == want, (L, m, N, k, table)
+                got = _new_workspace(whole, L, 1, N, m, 2, k, table, order, like)
+                assert (got is None) == (want == order_bytes), (L, m, N, k, table)
 
 
 def test_no_oracle_in_product():
