@@ -68,7 +68,8 @@ bool misaligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3) !=
 // inline / staged: 16,383 and 16,384 lookups 25.3 / 24.8 us).
 constexpr int64_t STAGE_MIN = 16384;
 
-int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t* L, Params* P) {
+// th: the activation layer, whose small batches form their coordinates inline.
+int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t* L, Params* P, bool th = false) {
   if (B < 0 || H < 0 || !K) return LRAM_EINVAL;
   if (H != 0 && B > INT64_MAX / H) return LRAM_EINVAL;
   *L = B * H;
@@ -94,7 +95,8 @@ int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t
   P->L = *L;
   P->stage = 0;
   P->passes = 0;
-  P->lpw = lookups_per_wave(*L, true);
+  P->tiled = tile_search(*L, th);
+  P->lpw = lookups_per_wave(*L, P->tiled);
   return LRAM_OK;
 }
 
@@ -423,7 +425,7 @@ template <int DT, int M, int TH, int KS>
 void launch_atomic(const float* q, const float* z, const Params& Pq, const void* table, const float* g, float* gt, float* gq,
                    const uint32_t* gate, const uint32_t* perm, NbrList saved, hipStream_t s) {
   Params P = Pq;
-  P.lpw = lookups_per_wave(P.L, KS == NB);
+  if (KS != NB) P.lpw = lookups_per_wave(P.L, false);
   // behind the gate large batches launch half the workgroups: where the gate
   // sends the batch to the merge, each still costs its dispatch (32,768 of
   // them 18 us at 4,194,304 lookups)
@@ -605,7 +607,7 @@ template <int DT, int M>
 struct FwdKLaunch {
   static int go(const float* q, const Params& Pq, const void* table, void* out, int width, hipStream_t s) {
     Params P = Pq;
-    P.lpw = lookups_per_wave(P.L, width == NB);
+    if (width != NB) P.lpw = lookups_per_wave(P.L, false);
     const dim3 g(grid_for(P)), b(THREADS);
     switch (width) {
       case 16: hipLaunchKernelGGL((k_forward_k<DT, M, 16>), g, b, 0, s, q, P, table, out); break;
@@ -643,7 +645,7 @@ int forward_impl(const float* in, int64_t B, int64_t H, const int32_t K[8], cons
                  hipStream_t stream) {
   int64_t L;
   Params P;
-  int rc = check_common(in, B, H, K, &L, &P);
+  int rc = check_common(in, B, H, K, &L, &P, th);
   if (rc) return rc;
   rc = check_table(table, dtype, N, m, P, L);
   if (rc) return rc;
@@ -664,7 +666,7 @@ int backward_impl(const float* in, int64_t B, int64_t H, const int32_t K[8], con
                   hipStream_t stream) {
   int64_t L;
   Params P;
-  int rc = check_common(in, B, H, K, &L, &P);
+  int rc = check_common(in, B, H, K, &L, &P, th);
   if (rc) return rc;
   rc = check_table(table, dtype, N, m, P, L);
   if (rc) return rc;
@@ -885,7 +887,7 @@ int lram_access_histogram(const float* q, int64_t B, int64_t H, const int32_t K[
   if (!hist || misaligned4(hist)) return LRAM_EINVAL;
   for (int64_t l0 = 0; l0 < L; l0 += HIST_PIECE) {
     P.L = std::min(L - l0, HIST_PIECE);
-    P.lpw = std::min<int32_t>(lookups_per_wave(P.L, true), TILE);  // one tile to a wave
+    P.lpw = std::min<int32_t>(lookups_per_wave(P.L, P.tiled), TILE);  // one tile to a wave
     hipLaunchKernelGGL(k_access_hist, dim3(grid_for(P)), dim3(THREADS), 0, (hipStream_t)stream, q + 8 * l0, P, hist);
     if ((rc = launched())) return rc;
   }
@@ -984,7 +986,7 @@ int lram_neighbors_k(const float* q, int64_t B, int64_t H, const int32_t K[8], i
   if (rc) return rc;
   if (L == 0) return LRAM_OK;
   if (!slot || !w || misaligned4(slot) || misaligned4(w) || misaligned4(d2)) return LRAM_EINVAL;
-  P.lpw = lookups_per_wave(L, width == NB);
+  if (width != NB) P.lpw = lookups_per_wave(L, false);
   const dim3 g(grid_for(P)), b(THREADS);
   hipStream_t s = (hipStream_t)stream;
   switch (width) {

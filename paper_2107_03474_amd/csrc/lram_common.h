@@ -60,6 +60,7 @@ struct Params {
   int32_t lpw;       // lookups per wave (1..64)
   int32_t stage;     // floats per staged record (input IN_STAGED)
   int32_t passes;    // radix passes of a location sort
+  int32_t tiled;     // the closest 32 are searched tile by tile (tile_search)
   int64_t L;
   double cK[8];      // K_i / (2 pi): torus coordinate per radian of arg z_i (activation layer)
 };

@@ -18,16 +18,27 @@ constexpr int TILE = 16;
 constexpr int64_t SIMDS = 256 * 4;
 constexpr int64_t LMAX = (int64_t(1) << 31) - 1;  // lookups per call
 
+// Whether the closest 32 of a batch are searched tile by tile, or one lookup per
+// wave by the general search: a tile's selection is a longer chain than one
+// lookup's scan, and two lookups on a wave scatter one after the other, so it pays
+// once a SIMD would have more than four waves (two behind the activation
+// layer's inline coordinates, whose kernels are built for two).  us, tiles with
+// two lookups per wave / general search with one (2^16 rows, m = 32 fp32): forward of
+// 300 lookups 9.8 / 6.9, of 2,048 9.7 / 7.3, of 4,096 10.4 / 9.0; backward 12.9 / 8.3, 14.3 /
+// 12.8, 19.9 / 19.6; flags 9.1 / 6.3, 9.0 / 6.7, 9.7 / 8.1.  From 4,097 on two lookups
+// share a wave either way: forward 10.1 / 12.7, backward 22.6 / 26.4.  Activation
+// layer, forward (2^18 rows, m = 64 fp32): 2,048 lookups 9.3 / 8.9, 3,072 11.9 / 13.9.
+constexpr bool tile_search(int64_t L, bool inline_theta) { return L > (inline_theta ? 2 : 4) * SIMDS; }
+
 // Lookups per wave.  A wave that searches tiles spends a tile's cost whatever
 // the tile holds (about 900 instructions; 120 more for each pair of lookups), so
 // small batches put two lookups on a wave, more once every SIMD has two
 // waves, up to a whole tile from 32,768 lookups on.  Forward, lookups per
-// wave 1 / 2 / 4 / 8 / 16 / 32 / 64: 4,096 lookups 16.2 / 12.1 / 12.0 / 13.8 / 17 / - / - us;
-// 16,384 lookups 48 / 28 / 21 / 19.9 / 22 / 37 / -; 65,536 - / 95 / 67 / 55 / 51 / 57 / 87;
-// 262,144 (2^20 rows, m = 64 fp32) - / - / 352 / 309 / 304 / 305 / 320.  The general search
-// (tile = false) costs the same for every lookup: one each until every SIMD
-// has four waves, then up to 64.  From 2^30 lookups on a wave takes 64 either way:
-// 32 would make a grid of 2^32 work-items, which no launch accepts.
+// wave 2 / 4 / 8 / 16 / 32 / 64: 16,384 lookups 28 / 21 / 19.9 / 22 / 37 / - us; 65,536 95 / 67 / 55 /
+// 51 / 57 / 87; 262,144 (2^20 rows, m = 64 fp32) - / 352 / 309 / 304 / 305 / 320.  The
+// general search (tile = false) costs the same for every lookup: one each until
+// every SIMD has four waves, then up to 64.  From 2^30 lookups on a wave takes 64
+// either way: 32 would make a grid of 2^32 work-items, which no launch accepts.
 constexpr int32_t lookups_per_wave(int64_t L, bool tile) {
   if (!tile || L >= (int64_t(1) << 30)) {
     const int64_t lpw = (L + 4 * SIMDS - 1) / (4 * SIMDS);

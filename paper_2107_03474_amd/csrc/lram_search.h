@@ -915,18 +915,18 @@ constexpr bool tile_norms_ok() {
 static_assert(E8_TILE_BLOCKS == 15 && tile_norms_ok(), "blocks of one norm but for 3 and 4, every candidate in a row");
 __constant__ __align__(16) TileOps c_tile = make_tile_ops();
 
-// Copies the product's operands and the candidates to LDS; every thread of the
-// workgroup, before the first search.  (Read from memory by every tile, the
+// Copies the product's operands (rows: tiles are searched) and the candidates to
+// LDS; every thread of the workgroup, before the first search.  (Read from memory by every tile, the
 // operands cost small batches three dependent loads' latency.)
 template <typename SL>
-__device__ __forceinline__ void init_tile(SL& S) {
+__device__ __forceinline__ void init_tile(SL& S, bool rows) {
   auto copy = [](const uint32_t* from, uint32_t* to, int words) {
     const uint4* src = reinterpret_cast<const uint4*>(from);
     uint4* dst = reinterpret_cast<uint4*>(to);
     for (int i = threadIdx.x; i < words / 4; i += THREADS) dst[i] = src[i];
   };
   static_assert((CANDS + 1) % 2 == 0 && sizeof(S.tile.cand) == sizeof(c_tile.cand), "candidates in 16-byte pieces");
-  copy(&c_tile.rows[0][0], &S.tile.rows[0].x, E8_TILE_BLOCKS * TILE * 4);
+  if (rows) copy(&c_tile.rows[0][0], &S.tile.rows[0].x, E8_TILE_BLOCKS * TILE * 4);
   copy(&c_tile.cand[0][0], &S.tile.cand[0].x, 2 * (CANDS + 1));
   __syncthreads();
 }
@@ -1083,12 +1083,13 @@ struct TileSearch {
   int wave, lane;
   uint32_t accepted;  // bits of the tile's lookups whose list starts with the ten
   uint32_t exist;     // bits of its lookups
+  bool tiled;         // otherwise the general search takes every lookup
 
   // every thread of the workgroup constructs it (a barrier), before any leaves
   __device__ TileSearch(const Params P, SL& s, int w, int l)
       : S(s), W(s.wave[w]), one(P, s.tab, s.wave[w], s.tile, w, l), Q(P, l), FR(s.frames[w]), wave(w), lane(l),
-        accepted(0), exist(0) {
-    init_tile(s);
+        accepted(0), exist(0), tiled(P.tiled != 0) {
+    init_tile(s, tiled);
   }
 
   // The lookup of this lane's quarter: position + lane / 4.
@@ -1101,7 +1102,7 @@ struct TileSearch {
     const uint2 sel = make_frames<TH>(in, have, Q, FR);
     wave_lds_sync();
     if constexpr (SELECT) {
-      accepted = uniform(tile_select(FR, S.tile, S.tile.idx[wave], lane));
+      if (tiled) accepted = uniform(tile_select(FR, S.tile, S.tile.idx[wave], lane));
       wave_lds_sync();
     }
     finish_frames(sel, lane, FR);

@@ -38,6 +38,61 @@ def test_lists(L, K):
     check_neighbors(mixed_queries(L, K, L), K)
 
 
+@pytest.mark.parametrize("L", [4095, 4096, 4097, 4099])
+def test_line_between_searches(L):
+    """Either side of the size at which tiles replace the general search, one lookup per wave: lists bit-exact, and
+    the forward, the saved lists and the gradients of the same queries in a batch of the other kind."""
+    _say("tile line L=%d" % L)
+    K = (4, 4, 6, 4, 4, 8, 4, 4)
+    q_np = np.resize(mixed_queries(300, K, L), (L, 8))
+    check_neighbors(q_np, K)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    table = torch.randn((int(np.prod(K)), 64), generator=g, device=DEV) * 0.02
+    G = torch.randn((L, 64), generator=g, device=DEV)
+    q = torch.from_numpy(q_np).to(DEV)
+    other = torch.cat([q, q[:4200 - 64]]) if L <= 4096 else q[:4096]
+    n = min(L, other.shape[0])
+    nl, nl2 = lram.new_lists(q), lram.new_lists(other)
+    out, out2 = lram.forward(q, table, K, lists=nl), lram.forward(other, table, K, lists=nl2)
+    # the same 32 products in the searches' own orders: 32 additions, 32 2^-24 of the terms' sum, far below 1e-5
+    assert _rel_rows(out[:n].cpu().numpy(), out2[:n].cpu().numpy()).max() <= 1e-5
+    assert torch.equal(nl.slot[:n].sort(1)[0], nl2.slot[:n].sort(1)[0])
+    G2 = torch.cat([G, G])[:other.shape[0]]
+    for kw, kw2 in (({}, {}), ({"lists": nl}, {"lists": nl2})):
+        gt, gq = lram.backward(q, table, K, G, mode="atomic", **kw)
+        _, gq2 = lram.backward(other, table, K, G2, grad_table=False, mode="atomic", **kw2)
+        a, b = gq[:n].cpu().numpy(), gq2[:n].cpu().numpy()
+        size = np.linalg.norm(b, axis=1)
+        assert (np.linalg.norm(a - b, axis=1) <= np.maximum(1e-5 * size, 1e-6 * size.max())).all()
+        nb = oracle.neighbors(q_np, K)
+        uniq, acc = oracle.grad_table_rows(nb, G.cpu().numpy())
+        assert _rel_rows(gt.cpu().numpy()[uniq], acc).max() <= 2e-5
+
+
+@pytest.mark.parametrize("m,dtype", [(32, torch.float32), (64, torch.float32), (64, torch.bfloat16)])
+@pytest.mark.parametrize("L", [2047, 2048, 2049])
+def test_line_between_searches_activation_layer(L, m, dtype):
+    """theta against the lookup on its own coordinates, scaled (one rounding each: 2^-23, 2^-8 in bf16)."""
+    _say("tile line theta L=%d" % L)
+    K = (4, 4, 6, 4, 4, 8, 4, 4)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    table = (torch.randn((int(np.prod(K)), m), generator=g, device=DEV) * 0.02).to(dtype)
+    z = torch.randn((L, 16), generator=g, device=DEV)
+    z[::101, 3] = float("nan")
+    q, s = lram.theta_coords(z, K)
+    ref = (lram.forward(q, table.float(), K).double() * s.double()[:, None]).cpu().numpy()
+    got = lram.theta_forward(z, table, K).double().cpu().numpy()
+    assert _rel_rows(got, ref).max() <= (1e-5 if dtype == torch.float32 else 1e-2)
+    G = torch.randn((L, m), generator=g, device=DEV)
+    gt, _ = lram.theta_backward(z, table, K, G, mode="atomic")
+    gt2, _ = lram.backward(q, table, K, G * s[:, None], mode="atomic")
+    a, b = gt.double().cpu().numpy(), gt2.double().cpu().numpy()
+    size = np.linalg.norm(b, axis=1)
+    assert (np.linalg.norm(a - b, axis=1) <= 2e-5 * size + 1e-6 * size.max()).all()
+
+
 @pytest.mark.parametrize("m,dtype", [(32, "f32"), (64, "f32"), (32, "bf16"), (64, "bf16")])
 @pytest.mark.parametrize("L", [1, 3, 17, 40000])
 def test_step(L, m, dtype):

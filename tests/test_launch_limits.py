@@ -53,6 +53,26 @@ def test_every_accepted_batch_launches(tmp_path):
     assert run_host(tmp_path, PROGRAM) == ""
 
 
+SMALL = r"""
+#include <cstdio>
+#include "lram_plain.h"
+int main() {
+  for (int th = 0; th < 2; ++th)
+    for (int64_t L = 1; L <= 5000; ++L) {
+      const bool tile = tile_search(L, th);
+      const int32_t lpw = lookups_per_wave(L, tile);
+      if (tile != (L > (th ? 2048 : 4096)) || (tile ? lpw < 2 : lpw != 1)) std::printf("%d: %lld %d %d\n", th, (long long)L, tile, lpw);
+    }
+  return 0;
+}
+"""
+
+
+def test_small_batches_take_one_lookup_per_wave(tmp_path):
+    """While a wave per lookup fits the SIMDs at the kernels' occupancy, no lookup waits for another's scatter."""
+    assert run_host(tmp_path, SMALL) == ""
+
+
 WRAP = r"""
 #include <cstdio>
 #include <initializer_list>
