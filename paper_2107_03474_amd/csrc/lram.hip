@@ -887,8 +887,13 @@ int lram_access_histogram(const float* q, int64_t B, int64_t H, const int32_t K[
   if (!hist || misaligned4(hist)) return LRAM_EINVAL;
   for (int64_t l0 = 0; l0 < L; l0 += HIST_PIECE) {
     P.L = std::min(L - l0, HIST_PIECE);
-    P.lpw = std::min<int32_t>(lookups_per_wave(P.L, P.tiled), TILE);  // one tile to a wave
-    hipLaunchKernelGGL(k_access_hist, dim3(grid_for(P)), dim3(THREADS), 0, (hipStream_t)stream, q + 8 * l0, P, hist);
+    P.tiled = tile_search(P.L, false);
+    P.lpw = hist_lookups_per_wave(P.L);
+    const dim3 g(grid_for(P)), b(THREADS);
+    if (hist_merged(P.L))
+      hipLaunchKernelGGL(k_access_hist<true>, g, b, 0, (hipStream_t)stream, q + 8 * l0, P, hist);
+    else
+      hipLaunchKernelGGL(k_access_hist<false>, g, b, 0, (hipStream_t)stream, q + 8 * l0, P, hist);
     if ((rc = launched())) return rc;
   }
   return LRAM_OK;

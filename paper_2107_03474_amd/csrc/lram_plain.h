@@ -69,6 +69,15 @@ constexpr int64_t blocks_for(int64_t L, int32_t lpw) {
   return (L + per_block - 1) / per_block;
 }
 
+// The access histogram: whether a batch's pairs are merged per workgroup before
+// they are added (measured beside k_access_hist), and the lookups per wave.
+constexpr bool hist_merged(int64_t L) { return L >= 16384; }
+constexpr int32_t hist_lookups_per_wave(int64_t L) {
+  if (!hist_merged(L)) return lookups_per_wave(L, tile_search(L, false));
+  const int32_t lpw = lookups_per_wave(L, false);
+  return L < 98304 ? (lpw < TILE / 2 ? lpw : TILE / 2) : TILE;
+}
+
 // Lookups per launch of the access histogram, whose waves take one tile each:
 // four work-items per lookup.  Larger batches are launched in pieces.
 constexpr int64_t HIST_PIECE = int64_t(1) << 29;

@@ -12,26 +12,31 @@ namespace {
 // of the pairs that read location s; then the fraction of locations read and
 // the KL divergence of the weighted access distribution from uniform.
 
-// A workgroup merges its lookups' pairs first: 64 lookups leave (location, w)
-// pairs in LDS, a 4,096-entry open-addressing hash over the search's LDS sums
-// the weights of every distinct location, and each sum is added with one
-// atomic.  Bound by the memory side's atomic requests of 64 bytes, and by those
-// that follow each other on one line.  Flags, histogram and statistics of
-// 262,144 lookups, pair by pair / merged with the entries scattered / with a
-// line's entries together (hist_entry): half clustered on 2^22 rows 713 / 654 /
-// 563 us; of 240,000 projected lookups on 2^16 rows 745 / 785 / 452 us, of
-// 720,000 on 2^15 rows 2,360 / 2,546 / 1,103 us.  Hot locations also receive
-// fewer, larger terms, so their fp32 sums are rounded less often.
-struct alignas(16) HistLds {
-  int32_t loc[MERGE_P];
-  float w[MERGE_P];
-  union {
-    SearchLds<NB, 2> search;
-    struct {
-      int32_t tag[MERGE_H];
-      float sum[MERGE_H];
-    } hash;
-  };
+// A workgroup merges its lookups' pairs first: the lanes keep the (location, w)
+// pairs of a tile per wave in registers, a 4,096-entry open-addressing hash in the
+// search's LDS sums the weights of every distinct location, and each sum is
+// added with one atomic.  Bound by the memory side's atomic requests of 64
+// bytes, and by those that follow each other on one line.  Queries that share
+// nothing gain nothing from it and wait for the merge (a CU's workgroups search
+// and add in step), so small batches add pair by pair, and a wave takes half a
+// tile until the grid holds several workgroups per CU.  us, pair by pair /
+// merged with 4 / 8 / 16 lookups per wave; 8^8 rows uniform, 2^18 rows 64 clusters,
+// 2^15 rows projected:
+//    16,384 lookups  28 / 31 / 33 / -    40 / 41 / 42 / -    41 / 37 / 34 / -
+//    32,768          50 / 58 / 55 / 62   77 / 76 / 72 / 74   79 / 71 / 60 / 54
+//    65,536          94 / 103 / 104 / 108  133 / 133 / 125 / 122  150 / 134 / 109 / 93
+//   131,072         185 / 196 / 188 / 199  265 / 267 / 249 / 234  294 / 255 / 212 / 172
+//   262,144         361 / 379 / 378 / 379  481 / 481 / 457 / 414  588 / 507 / 418 / 330
+// With the pairs in LDS (50,080 bytes, three workgroups per CU) instead of in
+// registers (33,792, four): 62, 114, 203, 391 for the uniform queries and 54, 103, 172,
+// 330 for the projected ones from 32,768 on.  Hot locations also receive fewer,
+// larger terms, so their fp32 sums are rounded less often.
+union alignas(16) HistLds {
+  SearchLds<NB, 2> search;
+  struct {
+    int32_t tag[MERGE_H];
+    float sum[MERGE_H];
+  } hash;
 };
 
 // First hash entry of a location: the 16 locations of a 64-byte line of the
@@ -41,60 +46,81 @@ __device__ __forceinline__ uint32_t hist_entry(uint32_t l) {
   return ((((l >> 4) * 0x9E3779B1u) >> (32 - (MERGE_HBITS - 4))) << 4) | (l & 15);
 }
 
-__global__ void __launch_bounds__(THREADS, 3) k_access_hist(const float* __restrict__ q, Params P,
+// MERGE: one tile to a wave at most, its pairs merged; otherwise pair by pair.
+template <bool MERGE>
+__global__ void __launch_bounds__(THREADS, 4) k_access_hist(const float* __restrict__ q, Params P,
                                                             float* __restrict__ hist) {
-  __shared__ HistLds S;
+  __shared__ std::conditional_t<MERGE, HistLds, SearchLds<NB, 2>> S;
   WaveCtx c;
   wave_ctx(P, c);
-  {
-    TileInput<IN_QUERY, false> in(q, nullptr, c.base, c.nl, P, c.lane);
-    TileSearch<IN_QUERY, 2> ts(P, S.search, c.wave, c.lane);
-    const int h = c.lane >> 5, j = c.lane & 31;
-    int32_t* loc = S.loc + c.wave * (TILE * NB);
-    float* w = S.w + c.wave * (TILE * NB);
-    if (c.nl > 0) ts.frames(in.v, in.have, c.nl);
-    for (int p = 0; 2 * p < TILE; ++p) {
-      int32_t s = -1;
-      float wt = 0.0f;
-      if (2 * p < c.nl) {
+  const int h = c.lane >> 5, j = c.lane & 31;
+  TileInput<IN_QUERY, false> in(q, nullptr, c.base, c.nl, P, c.lane);
+  if constexpr (!MERGE) {
+    TileSearch<IN_QUERY, 2> ts(P, S, c.wave, c.lane);
+    for (int t0 = 0; t0 < c.nl; t0 += TILE) {
+      const int nt = min(TILE, c.nl - t0);
+      ts.frames(in.v, in.have, nt);
+      in.advance(t0, P);
+      for (int p = 0; 2 * p < nt; ++p) {
         ts.pair(p, 0);
-        s = ts.W.nbr[h][j].slot;
-        wt = ts.W.wgt[h][j];
+        const int32_t s = ts.W.nbr[h][j].slot;
+        if (s >= 0) unsafeAtomicAdd(hist + s, ts.W.wgt[h][j]);
+        wave_lds_sync();
       }
-      loc[64 * p + c.lane] = s;
-      w[64 * p + c.lane] = wt;
+    }
+  } else {
+    constexpr int NP = TILE / 2;  // pairs of lookups per tile, one entry of each to a lane
+    int32_t loc[NP];
+    float w[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      loc[k] = -1;
+      w[k] = 0.0f;
+    }
+    TileSearch<IN_QUERY, 2> ts(P, S.search, c.wave, c.lane);
+    if (c.nl > 0) ts.frames(in.v, in.have, c.nl);
+#pragma unroll 1
+    for (int p = 0; 2 * p < c.nl; ++p) {
+      ts.pair(p, 0);
+      const int32_t s = ts.W.nbr[h][j].slot;
+      const float wt = ts.W.wgt[h][j];
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {  // (selected: a runtime index would put the arrays into memory)
+        loc[k] = k == p ? s : loc[k];
+        w[k] = k == p ? wt : w[k];
+      }
       wave_lds_sync();
     }
-  }
-  __syncthreads();
-  const int t = threadIdx.x;
+    __syncthreads();  // the search's LDS becomes the hash
+    const int t = threadIdx.x;
 #pragma unroll
-  for (int k = 0; k < MERGE_HPT; ++k) {
-    S.hash.tag[k * THREADS + t] = MERGE_EMPTY;
-    S.hash.sum[k * THREADS + t] = 0.0f;
-  }
-  __syncthreads();
+    for (int k = 0; k < MERGE_HPT; ++k) {
+      S.hash.tag[k * THREADS + t] = MERGE_EMPTY;
+      S.hash.sum[k * THREADS + t] = 0.0f;
+    }
+    __syncthreads();
 #pragma unroll
-  for (int k = 0; k < MERGE_PPT; ++k) {
-    const int32_t l = S.loc[k * THREADS + t];
-    if (l >= 0) {
-      uint32_t e = hist_entry((uint32_t)l);
-      while (true) {
-        const int32_t old = atomicCAS(&S.hash.tag[e], MERGE_EMPTY, l);
-        if (old == MERGE_EMPTY || old == l) break;
-        e = (e + 1) & (MERGE_H - 1);
+    for (int k = 0; k < NP; ++k) {
+      const int32_t l = loc[k];
+      if (l >= 0) {
+        uint32_t e = hist_entry((uint32_t)l);
+        while (true) {
+          const int32_t old = atomicCAS(&S.hash.tag[e], MERGE_EMPTY, l);
+          if (old == MERGE_EMPTY || old == l) break;
+          e = (e + 1) & (MERGE_H - 1);
+        }
+        unsafeAtomicAdd(&S.hash.sum[e], w[k]);
       }
-      unsafeAtomicAdd(&S.hash.sum[e], S.w[k * THREADS + t]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < MERGE_HPT; ++k) {
+      const int32_t l = S.hash.tag[k * THREADS + t];
+      if (l >= 0) unsafeAtomicAdd(hist + l, S.hash.sum[k * THREADS + t]);
     }
   }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < MERGE_HPT; ++k) {
-    const int32_t l = S.hash.tag[k * THREADS + t];
-    if (l >= 0) unsafeAtomicAdd(hist + l, S.hash.sum[k * THREADS + t]);
-  }
 }
-static_assert(WAVES * TILE * NB == MERGE_P, "a workgroup's lookups are one tile per wave");
+static_assert(WAVES * TILE * NB < MERGE_H, "a workgroup's pairs leave empty entries");
 
 // touched[s] = 1 for every location s in a lookup's list of its closest 32
 // (the rows a backward of these lookups writes): plain byte stores, every

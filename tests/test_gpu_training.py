@@ -52,6 +52,36 @@ def test_access_stats(K):
     np.testing.assert_allclose(st["kl"], kl, rtol=1e-6)
 
 
+@pytest.mark.parametrize("K", [(2, 2, 2, 2, 2, 2, 2, 2), (4, 4, 4, 4, 4, 4, 4, 2), (4, 6, 8, 4, 4, 6, 4, 8)])
+@pytest.mark.parametrize("L", [1, 3, 65, 4097, 16383, 16384, 32768 + 5, 70001, 98304 + 1])
+def test_histogram_sizes(L, K):
+    """Every form of the histogram kernel (pair by pair; merged per workgroup with 4, 8 and 16 lookups to a wave), ragged
+    last tiles and waves, non-finite queries, clustered and uniform ones, few locations (dense lines of the hash, which
+    wraps) and many, added to what is there.  Bar: the n positive terms of a location and its old value meet in at most
+    2 n fp32 additions (in LDS, then in memory), each rounded by at most 2^-24 of the final sum."""
+    N = int(np.prod(K))
+    rng = np.random.default_rng(L + N)
+    n = min(L, 4000)  # the oracle's share; the batch repeats it
+    q = rng.random((n, 8)) * np.asarray(K)
+    q[: n // 2] = np.asarray(K) / 2.0 + 0.3 * rng.standard_normal((n // 2, 8))
+    q = q.astype(np.float32)
+    bad = rng.random(n) < 0.02
+    q[bad, 3] = rng.choice([np.nan, np.inf, -np.inf], bad.sum())
+    times = np.bincount(np.arange(L) % n, minlength=n)
+    nb = oracle.neighbors(np.where(bad[:, None], 0.0, q).astype(np.float32), K)
+    w = np.where(bad[:, None], 0.0, nb["w32"].astype(np.float64)) * times[:, None]
+    real = nb["slot"] >= 0
+    ref = np.bincount(nb["slot"][real], weights=w[real], minlength=N)
+    old = rng.random(N).astype(np.float32)
+    hist = torch.from_numpy(old).to(DEV)
+    lram.access_histogram(torch.from_numpy(np.resize(q, (L, 8))).to(DEV), K, hist=hist)
+    got = hist.cpu().numpy().astype(np.float64)
+    untouched = np.bincount(nb["slot"][real & ~bad[:, None]], minlength=N) == 0
+    assert np.array_equal(got[untouched], old[untouched].astype(np.float64))
+    pairs = np.bincount(nb["slot"][real], weights=np.broadcast_to(times[:, None], real.shape)[real], minlength=N)
+    assert (np.abs(got - old - ref) <= 2 * pairs * 2.0 ** -24 * (old + ref)).all()
+
+
 @pytest.mark.parametrize("N,offset", [(1, 0), (3, 1), (1023, 0), (1025, 1), (262145, 0), (1048579, 3), (2097152, 0)])
 def test_access_stats_sizes(N, offset):
     """One value, remainders of the 16-byte loads, unaligned arrays, one to many workgroups: fp64 sums of at most

@@ -30,7 +30,9 @@ int main() {
       int64_t covered = 0;
       for (int64_t l0 = 0; l0 < L; l0 += HIST_PIECE) {
         const int64_t n = std::min(L - l0, HIST_PIECE);
-        const int64_t blocks = blocks_for(n, std::min<int32_t>(lookups_per_wave(n, true), TILE));
+        const int32_t lpw = hist_lookups_per_wave(n);
+        const int64_t blocks = blocks_for(n, lpw);
+        if (lpw < 1 || (hist_merged(n) && lpw > TILE)) std::printf("histogram L = %lld: %d\n", (long long)L, lpw);
         covered += n;
         if (blocks * THREADS >= items) std::printf("histogram L = %lld: %lld blocks\n", (long long)L, (long long)blocks);
       }
