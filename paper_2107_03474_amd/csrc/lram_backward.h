@@ -226,10 +226,10 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == 
                                                       uint32_t* __restrict__ ghist) {
   static_assert(!EMIT || KS == NB, "the sorted scatter takes lists of 32");
   static_assert(!(SAVED || ORD) || (KS == NB && !TH), "orders and saved lists serve the k = 32 lookup");
-  __shared__ SearchLds<KS> S;
+  __shared__ ListLds<KS, SAVED> S;
   __shared__ uint32_t digits[EMIT ? SORT_PASSES_MAX : 1][EMIT ? RADIX : 1];
   if (gate && merge_chosen(*gate, P.L)) return;
-  if constexpr (EMIT) {  // (the search's first barrier follows)
+  if constexpr (EMIT) {
 #pragma unroll
     for (int p = 0; p < SORT_PASSES_MAX; ++p) digits[p][threadIdx.x] = 0u;
   }
@@ -237,7 +237,7 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == 
   wave_ctx(P, c, ORD);
   const int lane = c.lane;
   const char* tb = reinterpret_cast<const char*>(table);
-  WaveLds<KS, (KS == NB ? 2 : 1)>& W = S.wave[c.wave];
+  auto& W = S.wave[c.wave];
   // scatter and query gradient of list buf, which is lookup l's (ok: inside the batch)
   auto finish = [&](Frame& F, int buf, int t, int count, int64_t l, bool ok) {
     if (!EMIT && gtab && count > 0) scatter_atomic<M, KS>(W, buf, count, gout, l, gtab, lane);
@@ -254,10 +254,11 @@ __global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == 
   };
   if constexpr (KS == NB) {
     TileInput<TH, ORD> in(q, perm, c.base, c.nl, P, lane);
-    TileSearch<TH, 2> ts(P, S, c.wave, lane);
+    TileSearch<TH, SAVED ? 1 : 2, !SAVED> ts(P, S, c.wave, lane);
+    if constexpr (EMIT && SAVED) __syncthreads();  // (the digits' counters; a search's own barrier otherwise)
     for (int t0 = 0; t0 < c.nl; t0 += TILE) {
       const int nt = min(TILE, c.nl - t0);
-      ts.template frames<!SAVED>(in.v, in.have, nt);
+      ts.frames(in.v, in.have, nt);
       in.advance(t0, P);
       if constexpr (SAVED) {
         for (int t = 0; t < nt; ++t) {

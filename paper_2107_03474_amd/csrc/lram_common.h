@@ -144,21 +144,26 @@ constexpr int TILE_VAR = 64;
 constexpr int TILE_ALWAYS = 10;
 constexpr int CANDS = E8_NSTRICT + E8_NBOUNDARY;
 constexpr uint32_t CAND_NONE = 0xFFFFu;
-template <int KS>
+template <bool ON>
 struct alignas(16) TileLds {
-  uint4 rows[KS == NB ? E8_TILE_BLOCKS * TILE : 1];  // points of the distance product, eight bf16 each
-  uint2 cand[KS == NB ? CANDS + 1 : 2];              // packed bytes
-  uint16_t idx[WAVES][KS == NB ? TILE : 1][KS == NB ? NB : 2];
+  uint4 rows[ON ? E8_TILE_BLOCKS * TILE : 1];  // points of the distance product, eight bf16 each
+  uint2 cand[ON ? CANDS + 1 : 2];              // packed bytes
+  uint16_t idx[WAVES][ON ? TILE : 1][ON ? NB : 2];
 };
 
-// LDS of the search for lists of KS neighbours.
-template <int KS = NB, int NBUF = (KS == NB ? 2 : 1), int WBUF = NBUF>
+// LDS of the search for lists of KS neighbours; SELECT: the search runs (saved
+// lists need the frames, the tables and one list).
+template <int KS = NB, int NBUF = (KS == NB ? 2 : 1), int WBUF = NBUF, bool SELECT = true>
 struct alignas(16) SearchLds {
+  static constexpr bool TILED = KS == NB && SELECT;
   Tables tab;
   WaveLds<KS, NBUF, WBUF> wave[WAVES];
   Frame frames[WAVES][TILE];
-  TileLds<KS> tile;
+  TileLds<TILED> tile;
 };
+// The search of one entry's kernel: two lists, or one saved list.
+template <int KS, bool SAVED>
+using ListLds = SearchLds<KS, (KS == NB && !SAVED ? 2 : 1), (KS == NB && !SAVED ? 2 : 1), !SAVED>;
 
 __device__ __forceinline__ float lds_f32(const float* base, uint32_t byte_off) {
   return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + byte_off);

@@ -188,7 +188,7 @@ struct alignas(16) MergeWork {
   uint32_t ngroups;
 };
 
-template <int M, int KS>
+template <int M, int KS, bool SAVED = false>
 struct alignas(16) FusedLds {
   union {
     struct {
@@ -199,19 +199,24 @@ struct alignas(16) FusedLds {
     int32_t tag[MERGE_H];       // hash tags; then group locations [0, ngroups) and pair weights [MERGE_P, 2 MERGE_P)
   } a;
   union {
-    SearchLds<KS> search;
+    ListLds<KS, SAVED> search;
     MergeWork<M, merge_t<KS>()> merge;
   } b;
 };
+// With the tile search's rows and lists, which saved lists do not use, their batch
+// had 50,352 bytes and three workgroups to a CU: m = 32 bf16, an order and lists
+// given, 262,144 lookups (2^24 rows, 64 clusters) 423 us, 341 now; 65,536 155 and 117;
+// 4,194,304 (10^8 rows) 8.48 ms now.
+static_assert(4 * sizeof(FusedLds<32, NB, true>) <= 160 * 1024, "four saved-list batches of m = 32 share a CU");
 static_assert(MERGE_H == 2 * MERGE_P, "group locations and pair weights share the tag array");
 
 // Waves per SIMD that the LDS of one batch allows (160 KB per CU, 4 SIMDs):
 // the register budget is held to it, so registers do not lower the occupancy
 // below what the LDS permits -- except for fp32 tables with m = 64, whose
 // 256-byte rows need more registers than four waves per SIMD leave.
-template <int DT, int M, int KS>
+template <int DT, int M, int KS, bool SAVED>
 constexpr int merge_waves_per_simd() {
-  const int w = (int)((160 * 1024) / sizeof(FusedLds<M, KS>)) * WAVES / 4;
+  const int w = (int)((160 * 1024) / sizeof(FusedLds<M, KS, SAVED>)) * WAVES / 4;
   return (DT == LRAM_F32 && M == 64 && w > 3) ? 3 : w;
 }
 
@@ -227,7 +232,7 @@ constexpr int merge_waves_per_simd() {
 // has little to merge: it scatters with per-lookup atomics instead.
 // SAVED: the forward's lists (NbrList saved) replace the search.
 template <int DT, int M, int TH, int KS = NB, bool SAVED = false>
-__global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS>())) k_backward_merged(const float* q,
+__global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS, SAVED>())) k_backward_merged(const float* q,
                                                              const float* __restrict__ z, Params P,
                                                              const void* __restrict__ table,
                                                              const float* __restrict__ gout,
@@ -235,7 +240,7 @@ __global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS>())) 
                                                              const uint32_t* __restrict__ skey,
                                                              const uint32_t* __restrict__ perm,
                                                              const uint32_t* __restrict__ gate, NbrList saved) {
-  __shared__ FusedLds<M, KS> S;
+  __shared__ FusedLds<M, KS, SAVED> S;
   if (!merge_chosen(*gate, P.L)) return;  // the batch is scattered by k_backward instead
   const int t = threadIdx.x, wave = (int)uniform(t / WAVE), lane = t % WAVE;
   const int64_t bbase = xcd_block() * (WAVES * P.lpw);  // consecutive batches share an L2
@@ -284,10 +289,10 @@ __global__ void __launch_bounds__(THREADS, (merge_waves_per_simd<DT, M, KS>())) 
     uint32_t my_l;
     auto lookup_of = [&](int i) { return (int64_t)(uint32_t)__builtin_amdgcn_readlane(my_l, 4 * i); };
     if constexpr (KS == NB) {
-      TileSearch<TH, 2> ts(P, S.b.search, wave, lane);
+      TileSearch<TH, SAVED ? 1 : 2, !SAVED> ts(P, S.b.search, wave, lane);
       if (nl > 0) {
         const bool have = load_tile<TH, true>(q, perm, base, nl, P, lane, in, my_l);
-        ts.template frames<!SAVED>(in, have, nl);
+        ts.frames(in, have, nl);
         if constexpr (SAVED) {
           for (int i = 0; i < nl; ++i) {
             const int64_t l = lookup_of(i);

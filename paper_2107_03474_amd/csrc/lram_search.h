@@ -511,11 +511,11 @@ __device__ __forceinline__ int threshold_k_hist(const uint32_t (&key)[NS], uint3
 // Lists other than the closest 32 keep the packed strict candidates in
 // registers; the closest 32 come here only where the tile search cannot decide
 // and take all of them from the tile search's LDS.
-template <int KS, int NBUF = (KS == NB ? 2 : 1), int WBUF = NBUF>
+template <int KS, int NBUF = (KS == NB ? 2 : 1), int WBUF = NBUF, bool SELECT = true>
 struct Search {
   Tables& S;
   WaveLds<KS, NBUF, WBUF>& W;
-  TileLds<KS>& T;
+  TileLds<KS == NB && SELECT>& T;
   int lane;
   uint32_t wbyte;
   static constexpr int NC_REG = KS == NB ? 1 : NS_STRICT;
@@ -533,7 +533,7 @@ struct Search {
 
   // (the kernel argument is read field by field: holding a reference to it
   // would force the argument block into private memory)
-  __device__ Search(const Params P, Tables& s, WaveLds<KS, NBUF, WBUF>& wv, TileLds<KS>& tl, int w, int l)
+  __device__ Search(const Params P, Tables& s, WaveLds<KS, NBUF, WBUF>& wv, TileLds<KS == NB && SELECT>& tl, int w, int l)
       : S(s), W(wv), T(tl), lane(l), wbyte(64u * (uint32_t)w) {
     if constexpr (NC_REG == NS_STRICT) {
 #pragma unroll
@@ -942,7 +942,7 @@ __device__ __forceinline__ uint32_t over_groups(uint32_t x, F f) {
 
 // Steps 1 to 3 for the frames of a tile: writes every accepted lookup's
 // candidate indices to idx and returns the accepted lookups' bits.
-__device__ __forceinline__ uint32_t tile_select(const Frame* fr, const TileLds<NB>& tile, uint16_t (*idx)[NB], int lane) {
+__device__ __forceinline__ uint32_t tile_select(const Frame* fr, const TileLds<true>& tile, uint16_t (*idx)[NB], int lane) {
   // (opaque: what follows from the lane is formed again for every tile; held
   // for the whole wave it costs the row loads their registers)
   const int ln = opaque(lane), n = ln & 15, g = ln >> 4;
@@ -1071,13 +1071,16 @@ __device__ __forceinline__ uint32_t tile_select(const Frame* fr, const TileLds<N
 }
 
 // Everything the kernels need of the search of the closest 32: a tile's
-// frames and selection, then pairs of its lookups.
-template <int TH, int WBUF>
+// frames and selection, then pairs of its lookups.  SELECT = false: the frames
+// only, for saved lists; without the tile's LDS four workgroups of the merged
+// scatter share a CU at m = 32 (see FusedLds).
+template <int TH, int WBUF, bool SELECT = true>
 struct TileSearch {
-  using SL = SearchLds<NB, 2, WBUF>;
+  static constexpr int NBUF = SELECT ? 2 : 1;
+  using SL = SearchLds<NB, NBUF, WBUF, SELECT>;
   SL& S;
-  WaveLds<NB, 2, WBUF>& W;
-  Search<NB, 2, WBUF> one;
+  WaveLds<NB, NBUF, WBUF>& W;
+  Search<NB, NBUF, WBUF, SELECT> one;
   QuadCtx<TH> Q;
   Frame* FR;
   int wave, lane;
@@ -1085,19 +1088,18 @@ struct TileSearch {
   uint32_t exist;     // bits of its lookups
   bool tiled;         // otherwise the general search takes every lookup
 
-  // every thread of the workgroup constructs it (a barrier), before any leaves
+  // every thread of the workgroup constructs it (a barrier if SELECT), before any leaves
   __device__ TileSearch(const Params P, SL& s, int w, int l)
       : S(s), W(s.wave[w]), one(P, s.tab, s.wave[w], s.tile, w, l), Q(P, l), FR(s.frames[w]), wave(w), lane(l),
         accepted(0), exist(0), tiled(P.tiled != 0) {
-    init_tile(s, tiled);
+    if constexpr (SELECT) init_tile(s, tiled);
   }
 
   // The lookup of this lane's quarter: position + lane / 4.
   __device__ __forceinline__ int quad() const { return Q.n; }
 
-  // Frames of the tile whose quarters are in (nt lookups of it exist).
-  // SELECT: also choose the candidates (saved lists need the frames only).
-  template <bool SELECT = true>
+  // Frames of the tile whose quarters are in (nt lookups of it exist), and with
+  // SELECT its candidates.
   __device__ __forceinline__ void frames(const QuadIn<TH>& in, bool have, int nt) {
     const uint2 sel = make_frames<TH>(in, have, Q, FR);
     wave_lds_sync();
