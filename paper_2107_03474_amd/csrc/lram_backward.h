@@ -217,7 +217,7 @@ __device__ __forceinline__ void theta_chain(const Frame* FR, const WL& W, int nt
 // ORD: visit the lookups in the order perm (as k_forward).
 // SAVED: the forward's lists (NbrList saved) replace the search.
 template <int DT, int M, bool EMIT, int TH, int KS = NB, bool ORD = false, bool SAVED = false>
-__global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == IN_THETA ? 3 : 4) k_backward(const float* q, const float* __restrict__ z, Params P,
+__global__ void __launch_bounds__(THREADS, (kernel_waves<DT, M, TH>())) k_backward(const float* q, const float* __restrict__ z, Params P,
                                                       const void* __restrict__ table,
                                                       const float* __restrict__ gout, float* __restrict__ gtab,
                                                       float* gq, uint32_t* __restrict__ pair_key,

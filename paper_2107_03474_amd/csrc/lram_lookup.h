@@ -240,6 +240,14 @@ __device__ __forceinline__ void fwd_consume(const WaveLds<NB, 2, 4>& W, int wb, 
   fwd_store<DT, M>(lane, l, acc, out, ok);
 }
 
+// Waves per SIMD that the forward and the backward are built for: 256-byte fp32
+// rows need more registers than four leave, and the activation layer's inline fp64
+// arguments (small batches only) more than three: held to three they spilled up
+// to 36 registers (m = 64 fp32, three / two, forward of 32 lookups 9.2 / 7.5 us, of 6,000
+// 17.7 / 14.7, backward 16.4 / 14.6, 65.2 / 63.2).
+template <int DT, int M, int TH>
+constexpr int kernel_waves() { return TH == IN_THETA ? 2 : (DT == LRAM_F32 && M == 64 ? 3 : 4); }
+
 // TH: the lookups' input; the activation layer's scale s is folded into the
 // weights by the search.  IN_STAGED: q is the output itself, lookup l's record
 // at the start of its row, read by the wave that writes the row afterwards.
@@ -248,7 +256,7 @@ __device__ __forceinline__ void fwd_consume(const WaveLds<NB, 2, 4>& W, int wb, 
 // in time and on the same XCD); outputs still go to the lookup's row.
 // SAVE: write every lookup's list for the backward (NbrList).
 template <int DT, int M, int TH, bool ORD = false, bool SAVE = false>
-__global__ void __launch_bounds__(THREADS, (DT == LRAM_F32 && M == 64) || TH == IN_THETA ? 3 : 4) k_forward(const float* q, Params P,
+__global__ void __launch_bounds__(THREADS, (kernel_waves<DT, M, TH>())) k_forward(const float* q, Params P,
                                                      const void* __restrict__ table, void* out,
                                                      const uint32_t* __restrict__ perm, NbrList save) {
   using G = FwdGeom<DT, M>;
