@@ -68,8 +68,13 @@ bool misaligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3) !=
 // inline / staged: 16,383 and 16,384 lookups 25.3 / 24.8 us).
 constexpr int64_t STAGE_MIN = 16384;
 
-// th: the activation layer, whose small batches form their coordinates inline.
-int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t* L, Params* P, bool th = false) {
+// How the lookups are spread over the waves of a kernel built for `waves` per SIMD.
+void spread(Params* P, int waves) {
+  P->tiled = tile_search(P->L, waves);
+  P->lpw = lookups_per_wave(P->L, waves);
+}
+
+int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t* L, Params* P) {
   if (B < 0 || H < 0 || !K) return LRAM_EINVAL;
   if (H != 0 && B > INT64_MAX / H) return LRAM_EINVAL;
   *L = B * H;
@@ -95,8 +100,7 @@ int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t
   P->L = *L;
   P->stage = 0;
   P->passes = 0;
-  P->tiled = tile_search(*L, th);
-  P->lpw = lookups_per_wave(*L, P->tiled);
+  spread(P, 4);
   return LRAM_OK;
 }
 
@@ -149,6 +153,7 @@ struct FwdLaunch {
   static int go(const float* q, const Params& Pq, const void* table, void* out, bool th, const uint32_t* perm,
                 NbrList save, hipStream_t s) {
     Params P = Pq;
+    spread(&P, th && P.L < STAGE_MIN ? kernel_waves<DT, M, IN_THETA>() : kernel_waves<DT, M, IN_QUERY>());
     const dim3 g(grid_for(P)), b(THREADS);
     constexpr int row = M * (DT == LRAM_F32 ? 4 : 2) / 4;  // floats of an output row
     if (th && P.L >= STAGE_MIN && !overlap(q, (size_t)P.L * 16, out, (size_t)P.L * row)) {
@@ -425,7 +430,10 @@ template <int DT, int M, int TH, int KS>
 void launch_atomic(const float* q, const float* z, const Params& Pq, const void* table, const float* g, float* gt, float* gq,
                    const uint32_t* gate, const uint32_t* perm, NbrList saved, hipStream_t s) {
   Params P = Pq;
-  if (KS != NB) P.lpw = lookups_per_wave(P.L, false);
+  if (KS == NB)
+    spread(&P, kernel_waves<DT, M, TH>());
+  else
+    P.lpw = lookups_per_wave_k(P.L);
   // behind the gate large batches launch half the workgroups: where the gate
   // sends the batch to the merge, each still costs its dispatch (32,768 of
   // them 18 us at 4,194,304 lookups)
@@ -467,9 +475,10 @@ int merged_pass(const float* q, const float* z, const Params& P, const void* tab
     if (int rc = build_order<TH>(q, P, o, s)) return rc;
   launch_atomic<DT, M, TH, KS>(q, z, P, table, g, gt, gq, o.shared, nullptr, saved, s);
   if (int rc = launched()) return rc;
-  // one batch of at most merge_t<KS>() lookups per workgroup
+  // one batch of at most merge_t<KS>() lookups per workgroup; three share a CU, a wave of each to a SIMD
   Params Pm = P;
-  Pm.lpw = P.lpw < merge_lpw<KS>() ? P.lpw : merge_lpw<KS>();
+  spread(&Pm, 3);
+  Pm.lpw = std::min<int32_t>(Pm.lpw, merge_lpw<KS>());
   const int64_t per_block = (int64_t)Pm.lpw * WAVES;
   const dim3 grid((unsigned)((P.L + per_block - 1) / per_block));
   const uint32_t* keys = o.sort.ka;
@@ -541,6 +550,7 @@ int sorted_pairs(const float* q, const Params& Pq, const void* table, const floa
                  const Radix<uint2>& r, bool th, NbrList saved, hipStream_t s) {
   Params P = Pq;
   P.passes = radix_passes(P.N);  // keys lie in [0, N]
+  spread(&P, th && P.L < STAGE_MIN ? kernel_waves<DT, M, IN_THETA>() : kernel_waves<DT, M, IN_QUERY>());
   const dim3 grid(grid_for(P)), b(THREADS);
   const uint32_t* const np = nullptr;
   int rc = LRAM_OK;
@@ -607,7 +617,10 @@ template <int DT, int M>
 struct FwdKLaunch {
   static int go(const float* q, const Params& Pq, const void* table, void* out, int width, hipStream_t s) {
     Params P = Pq;
-    if (width != NB) P.lpw = lookups_per_wave(P.L, false);
+    if (width == NB)
+      spread(&P, kernel_waves<DT, M, IN_QUERY>());
+    else
+      P.lpw = lookups_per_wave_k(P.L);
     const dim3 g(grid_for(P)), b(THREADS);
     switch (width) {
       case 16: hipLaunchKernelGGL((k_forward_k<DT, M, 16>), g, b, 0, s, q, P, table, out); break;
@@ -645,7 +658,7 @@ int forward_impl(const float* in, int64_t B, int64_t H, const int32_t K[8], cons
                  hipStream_t stream) {
   int64_t L;
   Params P;
-  int rc = check_common(in, B, H, K, &L, &P, th);
+  int rc = check_common(in, B, H, K, &L, &P);
   if (rc) return rc;
   rc = check_table(table, dtype, N, m, P, L);
   if (rc) return rc;
@@ -666,7 +679,7 @@ int backward_impl(const float* in, int64_t B, int64_t H, const int32_t K[8], con
                   hipStream_t stream) {
   int64_t L;
   Params P;
-  int rc = check_common(in, B, H, K, &L, &P, th);
+  int rc = check_common(in, B, H, K, &L, &P);
   if (rc) return rc;
   rc = check_table(table, dtype, N, m, P, L);
   if (rc) return rc;
@@ -887,7 +900,7 @@ int lram_access_histogram(const float* q, int64_t B, int64_t H, const int32_t K[
   if (!hist || misaligned4(hist)) return LRAM_EINVAL;
   for (int64_t l0 = 0; l0 < L; l0 += HIST_PIECE) {
     P.L = std::min(L - l0, HIST_PIECE);
-    P.tiled = tile_search(P.L, false);
+    P.tiled = tile_search(P.L, 4);
     P.lpw = hist_lookups_per_wave(P.L);
     const dim3 g(grid_for(P)), b(THREADS);
     if (hist_merged(P.L))
@@ -991,7 +1004,7 @@ int lram_neighbors_k(const float* q, int64_t B, int64_t H, const int32_t K[8], i
   if (rc) return rc;
   if (L == 0) return LRAM_OK;
   if (!slot || !w || misaligned4(slot) || misaligned4(w) || misaligned4(d2)) return LRAM_EINVAL;
-  if (width != NB) P.lpw = lookups_per_wave(L, false);
+  if (width != NB) P.lpw = lookups_per_wave_k(L);
   const dim3 g(grid_for(P)), b(THREADS);
   hipStream_t s = (hipStream_t)stream;
   switch (width) {

@@ -18,35 +18,35 @@ constexpr int TILE = 16;
 constexpr int64_t SIMDS = 256 * 4;
 constexpr int64_t LMAX = (int64_t(1) << 31) - 1;  // lookups per call
 
-// Whether the closest 32 of a batch are searched tile by tile, or one lookup per
-// wave by the general search: a tile's selection is a longer chain than one
-// lookup's scan, and two lookups on a wave scatter one after the other, so it pays
-// once a SIMD would have more than four waves (two behind the activation
-// layer's inline coordinates, whose kernels are built for two).  us, tiles with
-// two lookups per wave / general search with one (2^16 rows, m = 32 fp32): forward of
-// 300 lookups 9.8 / 6.9, of 2,048 9.7 / 7.3, of 4,096 10.4 / 9.0; backward 12.9 / 8.3, 14.3 /
-// 12.8, 19.9 / 19.6; flags 9.1 / 6.3, 9.0 / 6.7, 9.7 / 8.1.  From 4,097 on two lookups
-// share a wave either way: forward 10.1 / 12.7, backward 22.6 / 26.4.  Activation
-// layer, forward (2^18 rows, m = 64 fp32): 2,048 lookups 9.3 / 8.9, 3,072 11.9 / 13.9.
-constexpr bool tile_search(int64_t L, bool inline_theta) { return L > (inline_theta ? 2 : 4) * SIMDS; }
-
-// Lookups per wave.  A wave that searches tiles spends a tile's cost whatever
-// the tile holds (about 900 instructions; 120 more for each pair of lookups), so
-// small batches put two lookups on a wave, more once every SIMD has two
-// waves, up to a whole tile from 32,768 lookups on.  Forward, lookups per
-// wave 2 / 4 / 8 / 16 / 32 / 64: 16,384 lookups 28 / 21 / 19.9 / 22 / 37 / - us; 65,536 95 / 67 / 55 /
-// 51 / 57 / 87; 262,144 (2^20 rows, m = 64 fp32) - / 352 / 309 / 304 / 305 / 320.  The
-// general search (tile = false) costs the same for every lookup: one each until
-// every SIMD has four waves, then up to 64.  From 2^30 lookups on a wave takes 64
-// either way: 32 would make a grid of 2^32 work-items, which no launch accepts.
-constexpr int32_t lookups_per_wave(int64_t L, bool tile) {
-  if (!tile || L >= (int64_t(1) << 30)) {
-    const int64_t lpw = (L + 4 * SIMDS - 1) / (4 * SIMDS);
-    return (int32_t)(lpw < 1 ? 1 : (lpw > WAVE ? WAVE : lpw));
-  }
-  const int64_t lpw = ((L + 2 * SIMDS - 1) / (2 * SIMDS) + 1) / 2 * 2;
-  const int64_t top = L < (int64_t(1) << 19) ? TILE : 2 * TILE;
-  return (int32_t)(lpw < 2 ? 2 : (lpw > top ? top : lpw));
+// Lookups per wave of a kernel that is built for `waves` waves per SIMD: as few as
+// fill them.  A batch that leaves a wave at most two takes the general search,
+// one lookup after the other (tile_search false): a tile's selection is a longer
+// chain than the scans of two lookups.  Above, a wave searches tiles, and spends a
+// tile's cost whatever the tile holds (about 900 instructions; 120 more for each
+// pair of lookups), so it takes an even number, a whole tile at most below 524,288
+// lookups and two from there on.  us, tiles of 2 / tiles of 4 / general search with 1 (up to
+// 4,096) or 2 lookups per wave, m = 64 bf16, 2^24 rows: forward of 300 lookups 7.7 / - / 6.7, of 2,048
+// 9.9 / - / 7.6, of 5,000 12.2 / 12.0 / 10.4, of 8,192 14.5 / 13.3 / 12.1; backward with row atomics
+// 14.6 / - / 9.8, 25.5 / - / 22.9, 51.2 / 53.4 / 51.9, 66.3 / 66.2 / 67.4; flags of 300 (2^16 rows) 9.1 / - /
+// 6.3, of 8,192 13.2 / 11.7 / 11.5.  General search with four: 15.1, 69.9 and 13.6 at 8,192.
+// Three waves per SIMD (m = 64 fp32): forward of 6,000 13.0 / 13.4 / 11.1, of 7,000 15.9 / 12.8 / 15.9; two
+// (inline activation layer) of 2,048 9.3 / - / 8.9, of 3,072 11.9 / - / 13.9 with one lookup.
+// Tiles of 2 / 4 / 6 / 8 / 12 / 16, forward: 16,384 lookups 22.5 / 17.2 / 16.7 / 17.1 / 19.8 / 22.2; 24,576
+// 28.4 / 25.3 / 19.9 / 20.1 / 21.2 / 23.8; 32,768 35.9 / 28.0 / 29.1 / 23.3 / 24.5 / 24.7; 49,152 50.5 / 40.0 / 34.1 /
+// 35.6 / 31.4 / 32.1; backward: 12,000 109 / 104 / 106 / 110 / - / -; 32,768 277 / 277 / 288 / 275 / 281 / 284.  Forward of
+// 262,144 (2^20 rows, m = 64 fp32), 4 / 8 / 16 / 32 / 64 to a wave: 352 / 309 / 304 / 305 / 320.  From 2^30 lookups on
+// a wave takes 64: 32 would make a grid of 2^32 work-items, which no launch accepts.
+constexpr int64_t fill_waves(int64_t L, int waves) { return (L + waves * SIMDS - 1) / (waves * SIMDS); }
+constexpr bool tile_search(int64_t L, int waves) { return fill_waves(L, waves) > 2; }
+constexpr int32_t lookups_per_wave(int64_t L, int waves) {
+  const int64_t n = fill_waves(L, waves);
+  const int64_t top = L < (int64_t(1) << 19) ? TILE : (L < (int64_t(1) << 30) ? 2 * TILE : WAVE);
+  return (int32_t)(n < 1 ? 1 : (n <= 2 ? n : (n > top ? top : (n + 1) / 2 * 2)));
+}
+// Lists other than the closest 32, whose search costs the same for every lookup.
+constexpr int32_t lookups_per_wave_k(int64_t L) {
+  const int64_t n = fill_waves(L, 4);
+  return (int32_t)(n < 1 ? 1 : (n > WAVE ? WAVE : n));
 }
 
 // h mod K for K even, at least 2, and h in [-K - 3, K + 3] (as uint32_t: two's
@@ -73,9 +73,8 @@ constexpr int64_t blocks_for(int64_t L, int32_t lpw) {
 // they are added (measured beside k_access_hist), and the lookups per wave.
 constexpr bool hist_merged(int64_t L) { return L >= 16384; }
 constexpr int32_t hist_lookups_per_wave(int64_t L) {
-  if (!hist_merged(L)) return lookups_per_wave(L, tile_search(L, false));
-  const int32_t lpw = lookups_per_wave(L, false);
-  return L < 98304 ? (lpw < TILE / 2 ? lpw : TILE / 2) : TILE;
+  const int32_t lpw = lookups_per_wave(L, 4);
+  return !hist_merged(L) || lpw < TILE / 2 ? lpw : (L < 98304 ? TILE / 2 : TILE);
 }
 
 // Lookups per launch of the access histogram, whose waves take one tile each:

@@ -38,10 +38,11 @@ def test_lists(L, K):
     check_neighbors(mixed_queries(L, K, L), K)
 
 
-@pytest.mark.parametrize("L", [4095, 4096, 4097, 4099])
+@pytest.mark.parametrize("L", [3072, 3073, 4096, 4097, 6143, 6145, 8191, 8192, 8193])
 def test_line_between_searches(L):
-    """Either side of the size at which tiles replace the general search, one lookup per wave: lists bit-exact, and
-    the forward, the saved lists and the gradients of the same queries in a batch of the other kind."""
+    """Either side of the sizes at which a second lookup joins a wave and tiles replace the general search (4,096 and
+    8,192; 3,072 and 6,144 for m = 64 fp32): lists bit-exact, and the forward, the saved lists and the gradients of
+    the same queries in a batch of the other kind."""
     _say("tile line L=%d" % L)
     K = (4, 4, 6, 4, 4, 8, 4, 4)
     q_np = np.resize(mixed_queries(300, K, L), (L, 8))
@@ -51,14 +52,14 @@ def test_line_between_searches(L):
     table = torch.randn((int(np.prod(K)), 64), generator=g, device=DEV) * 0.02
     G = torch.randn((L, 64), generator=g, device=DEV)
     q = torch.from_numpy(q_np).to(DEV)
-    other = torch.cat([q, q[:4200 - 64]]) if L <= 4096 else q[:4096]
+    other = torch.cat([q, q, q]) if L <= 6144 else q[:4096]
     n = min(L, other.shape[0])
     nl, nl2 = lram.new_lists(q), lram.new_lists(other)
     out, out2 = lram.forward(q, table, K, lists=nl), lram.forward(other, table, K, lists=nl2)
     # the same 32 products in the searches' own orders: 32 additions, 32 2^-24 of the terms' sum, far below 1e-5
     assert _rel_rows(out[:n].cpu().numpy(), out2[:n].cpu().numpy()).max() <= 1e-5
     assert torch.equal(nl.slot[:n].sort(1)[0], nl2.slot[:n].sort(1)[0])
-    G2 = torch.cat([G, G])[:other.shape[0]]
+    G2 = torch.cat([G, G, G])[:other.shape[0]]
     for kw, kw2 in (({}, {}), ({"lists": nl}, {"lists": nl2})):
         gt, gq = lram.backward(q, table, K, G, mode="atomic", **kw)
         _, gq2 = lram.backward(other, table, K, G2, grad_table=False, mode="atomic", **kw2)
@@ -71,7 +72,7 @@ def test_line_between_searches(L):
 
 
 @pytest.mark.parametrize("m,dtype", [(32, torch.float32), (64, torch.float32), (64, torch.bfloat16)])
-@pytest.mark.parametrize("L", [2047, 2048, 2049])
+@pytest.mark.parametrize("L", [2047, 2048, 2049, 4095, 4097])
 def test_line_between_searches_activation_layer(L, m, dtype):
     """theta against the lookup on its own coordinates, scaled (one rounding each: 2^-23, 2^-8 in bf16)."""
     _say("tile line theta L=%d" % L)

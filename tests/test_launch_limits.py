@@ -21,11 +21,11 @@ int main() {
     for (int64_t d = -200; d <= 200; ++d) {
       const int64_t L = (int64_t(1) << s) + d;
       if (L < 1 || L > LMAX) continue;
-      for (bool tile : {false, true}) {
-        const int32_t lpw = lookups_per_wave(L, tile);
+      for (int waves = 1; waves <= 4; ++waves) {
+        const int32_t lpw = waves == 1 ? lookups_per_wave_k(L) : lookups_per_wave(L, waves);
         const int64_t blocks = blocks_for(L, lpw);
         if (lpw < 1 || lpw > WAVE || blocks * WAVES * lpw < L || blocks * THREADS >= items)
-          std::printf("L = %lld tile = %d: %d lookups per wave, %lld blocks\n", (long long)L, tile, lpw, (long long)blocks);
+          std::printf("L = %lld waves = %d: %d lookups per wave, %lld blocks\n", (long long)L, waves, lpw, (long long)blocks);
       }
       int64_t covered = 0;
       for (int64_t l0 = 0; l0 < L; l0 += HIST_PIECE) {
@@ -59,19 +59,22 @@ SMALL = r"""
 #include <cstdio>
 #include "lram_plain.h"
 int main() {
-  for (int th = 0; th < 2; ++th)
-    for (int64_t L = 1; L <= 5000; ++L) {
-      const bool tile = tile_search(L, th);
-      const int32_t lpw = lookups_per_wave(L, tile);
-      if (tile != (L > (th ? 2048 : 4096)) || (tile ? lpw < 2 : lpw != 1)) std::printf("%d: %lld %d %d\n", th, (long long)L, tile, lpw);
+  for (int waves = 2; waves <= 4; ++waves)
+    for (int64_t L = 1; L <= 200000; ++L) {
+      const int64_t room = waves * SIMDS;
+      const int32_t lpw = lookups_per_wave(L, waves);
+      const bool tile = tile_search(L, waves);
+      // one lookup each while there is a wave for each, then two, and tiles above: no more than an even number needs
+      bool ok = tile == (L > 2 * room) && (tile || lpw == (L > room ? 2 : 1));
+      if (tile) ok = lpw % 2 == 0 && lpw <= TILE && (lpw == 4 || (lpw - 2) * room < L) && (lpw == TILE || lpw * room >= L);
+      if (!ok) std::printf("%d waves: %lld %d %d\n", waves, (long long)L, tile, lpw);
     }
   return 0;
 }
 """
 
 
-def test_small_batches_take_one_lookup_per_wave(tmp_path):
-    """While a wave per lookup fits the SIMDs at the kernels' occupancy, no lookup waits for another's scatter."""
+def test_lookups_per_wave_fill_the_simds(tmp_path):
     assert run_host(tmp_path, SMALL) == ""
 
 
