@@ -436,8 +436,9 @@ void launch_atomic(const float* q, const float* z, const Params& Pq, const void*
     P.lpw = lookups_per_wave_k(P.L);
   // behind the gate large batches launch half the workgroups: where the gate
   // sends the batch to the merge, each still costs its dispatch (32,768 of
-  // them 18 us at 4,194,304 lookups)
-  if (gate && P.lpw >= 2 * TILE) P.lpw = WAVE;
+  // them 18 us at 4,194,304 lookups); smaller ones need the waves where it does not
+  // (131,072 uniform lookups with lists of 16: 384 us with half the waves, 338)
+  if (gate && P.L >= (int64_t(1) << 19)) P.lpw = WAVE;
   const dim3 grid(grid_for(P)), b(THREADS);
   uint32_t* const nk = nullptr;
   uint2* const nv = nullptr;
@@ -477,7 +478,10 @@ int merged_pass(const float* q, const float* z, const Params& P, const void* tab
   if (int rc = launched()) return rc;
   // one batch of at most merge_t<KS>() lookups per workgroup; three share a CU, a wave of each to a SIMD
   Params Pm = P;
-  spread(&Pm, 3);
+  if (KS == NB)
+    spread(&Pm, 3);
+  else
+    Pm.lpw = lookups_per_wave_k(P.L);
   Pm.lpw = std::min<int32_t>(Pm.lpw, merge_lpw<KS>());
   const int64_t per_block = (int64_t)Pm.lpw * WAVES;
   const dim3 grid((unsigned)((P.L + per_block - 1) / per_block));
