@@ -434,6 +434,11 @@ void launch_atomic(const float* q, const float* z, const Params& Pq, const void*
     spread(&P, kernel_waves<DT, M, TH>());
   else
     P.lpw = lookups_per_wave_k(P.L);
+  // in the lookup order neighbouring waves add to the same rows: long runs of
+  // it per wave keep those atomics apart (64 clusters on 2^24 rows, m = 32, 16 / 64 lookups
+  // per wave: 262,144 lookups 1,194 / 1,041 us, uniform queries 866 / 879; 1,048,576, 32 / 64:
+  // 4,889 / 4,361, 3,355 / 3,393)
+  if (perm && gt && P.L > WAVES * SIMDS * TILE) P.lpw = lookups_per_wave_k(P.L);
   // behind the gate large batches launch half the workgroups: where the gate
   // sends the batch to the merge, each still costs its dispatch (32,768 of
   // them 18 us at 4,194,304 lookups); smaller ones need the waves where it does not
