@@ -980,6 +980,8 @@ int lram_mark_touched(const float* q, int64_t B, int64_t H, const int32_t K[8], 
   if (rc) return rc;
   if (L == 0) return LRAM_OK;
   if (!touched) return LRAM_EINVAL;
+  // tiles without rows to wait for: two waves per SIMD hide them (20,000 lookups 12.6 us, four 13.8)
+  if (P.tiled) spread(&P, 2);
   hipLaunchKernelGGL(k_mark_touched, dim3(grid_for(P)), dim3(THREADS), 0, (hipStream_t)stream, q, P, touched);
   return launched();
 }
