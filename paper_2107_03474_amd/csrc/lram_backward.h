@@ -136,8 +136,9 @@ __device__ __forceinline__ void grad_query(Frame& F, WaveLds<KS, NBUF, WBUF>& W,
 #pragma unroll
       for (int k = 0; k < IC; ++k) {
         const uint32_t ab = __builtin_amdgcn_perm(n.hi, n.lo, lsel[k]);
-        // (padding entries carry no candidate: any table entry, times zero)
-        dq[k] = fma(a, (double)lds_f32(T.et, (real ? ab : 0u) + 256u * (e * IC + k)), dq[k]);
+        // (padding entries carry no candidate: an entry of the wave's own tables, built
+        // where count > 0 and so finite, times zero)
+        dq[k] = fma(a, (double)lds_f32(T.et, ab + 256u * (e * IC + k)), dq[k]);
       }
     }  // chunks of R rows
   }

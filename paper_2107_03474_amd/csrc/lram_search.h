@@ -752,7 +752,7 @@ struct Search {
           const float u2 = u * u;
           W.wgt[buf][e] = (u2 * u2) * F.s;  // exact for plain lookups (s = 1)
         } else {
-          n.lo = n.hi = 0;
+          n.lo = n.hi = wbyte * 0x01010101u;  // an entry of this wave's own tables (grad_query reads it, times zero)
           n.dbits = KEY_INF;
           n.slot = -1;
           W.wgt[buf][e] = 0.0f;
@@ -790,7 +790,7 @@ struct Search {
         n.slot = s;
         W.wgt[buf][lane] = nl.w[o];
       } else {
-        n.lo = n.hi = 0;
+        n.lo = n.hi = wbyte * 0x01010101u;  // (as in run)
         n.dbits = KEY_INF;
         n.slot = -1;
         W.wgt[buf][lane] = 0.0f;

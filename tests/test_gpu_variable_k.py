@@ -170,3 +170,40 @@ def test_merged_at_scale(k):
     rows = oracle.gather_rows(table.cpu().numpy(), nbs["slot"])
     err = _rel_rows(gq.cpu().numpy()[sample], oracle.grad_query(nbs, rows, Gn[sample]))
     assert err.max() <= 1e-5, err.max()
+
+
+@pytest.mark.parametrize("k", [16, 32, 64, 0])
+def test_padding_beside_a_wave_without_lists(k):
+    """Padded lists take nothing from the tables of another wave: with every first of four lookups (one wave of a
+    workgroup each) non-finite, no tables are built there, and the memory they would take holds what the histogram's
+    hash left, words that are NaN as fp32."""
+    _say("padding beside empty waves k=%d" % k)
+    K, L, m = (4,) * 8, 4096, 32
+    rng = np.random.default_rng(k)
+    q_np = (rng.random((L, 8)) * 4).astype(np.float32)
+    if k in (16, 32):
+        q_np = np.round(q_np) % 4        # lattice points and holes: lists shorter than k
+    q = torch.from_numpy(q_np.astype(np.float32)).to(DEV)
+    part = q.clone()
+    part[::4] = float("nan")
+    table = torch.from_numpy(rng.standard_normal((4 ** 8, m)).astype(np.float32)).to(DEV)
+    G = torch.from_numpy(rng.standard_normal((L, m)).astype(np.float32)).to(DEV)
+    hot = torch.full((1 << 17, 8), 1.3, device=DEV)
+    hist = torch.zeros(4 ** 8, device=DEV)
+
+    def dq(qs):
+        lists = None
+        if k == 32:                      # (the search itself pads with a candidate's own entry)
+            lists = lram.new_lists(qs)
+            lram.forward(qs, table, K, lists=lists)
+        gt = torch.zeros((4 ** 8, m), device=DEV)
+        lram.access_histogram(hot, K, hist)
+        if k == 32:
+            return lram.backward(qs, table, K, G, grad_table=gt, mode="atomic", lists=lists)[1]
+        return lram.backward(qs, table, K, G, grad_table=gt, mode="atomic", k=k)[1]
+
+    want = dq(q).clone()
+    want[::4] = 0.0
+    for _ in range(5):
+        got = dq(part)
+        assert torch.equal(got, want), int((~torch.isfinite(got)).any(1).sum())
