@@ -205,6 +205,14 @@ __device__ __forceinline__ void theta_chain(const Frame* FR, const WL& W, int nt
   wave_lds_sync();
 }
 
+// Waves per SIMD of the backward that emits pairs.  Rows of 64 columns spill three
+// registers at four (bf16, a whole backward by sorted runs, 2^18 rows, four / three: 262,144
+// lookups 722 / 711 us, 524,288 1,440 / 1,407); rows of 32 are as fast or faster at four
+// (540 / 549, 1,059 / 1,085), and so are those behind the staged activation layer, ten
+// spilled registers included (m = 64 bf16 760 / 778, 1,476 / 1,521).
+template <int DT, int M, int TH>
+constexpr int pair_waves() { return TH == IN_QUERY && M == 64 ? 3 : kernel_waves<DT, M, TH>(); }
+
 // The value gradient is either added straight into grad_table with fp32
 // atomics (EMIT = false), or emitted as (location, (lookup, w_j)) pairs for
 // the location sort (EMIT = true; padding gets the key N, which sorts last),
@@ -218,7 +226,7 @@ __device__ __forceinline__ void theta_chain(const Frame* FR, const WL& W, int nt
 // ORD: visit the lookups in the order perm (as k_forward).
 // SAVED: the forward's lists (NbrList saved) replace the search.
 template <int DT, int M, bool EMIT, int TH, int KS = NB, bool ORD = false, bool SAVED = false>
-__global__ void __launch_bounds__(THREADS, (kernel_waves<DT, M, TH>())) k_backward(const float* q, const float* __restrict__ z, Params P,
+__global__ void __launch_bounds__(THREADS, (EMIT ? pair_waves<DT, M, TH>() : kernel_waves<DT, M, TH>())) k_backward(const float* q, const float* __restrict__ z, Params P,
                                                       const void* __restrict__ table,
                                                       const float* __restrict__ gout, float* __restrict__ gtab,
                                                       float* gq, uint32_t* __restrict__ pair_key,

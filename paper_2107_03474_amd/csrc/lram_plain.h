@@ -50,17 +50,14 @@ constexpr int32_t lookups_per_wave_k(int64_t L) {
 }
 
 // h mod K for K even, at least 2, and h in [-K - 3, K + 3] (as uint32_t: two's
-// complement): a parity for K = 2; otherwise h + 2 K lies in [K - 3, 3 K + 3], never
-// negative, and three periods come off one by one, each by an unsigned minimum (a
-// step too far leaves the range).  The last minimum keeps any other h
-// below K, so that nothing can address outside the table.
+// complement): a parity for K = 2, otherwise up to two periods up or one down.  The
+// minimum keeps any other h below K, so that nothing can address outside the table.
 constexpr uint32_t torus_coord(uint32_t h, uint32_t K) {
-  auto least = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
-  uint32_t Y = h + 2u * K;
-  Y = least(Y, Y - K);
-  Y = least(Y, Y - K);
-  Y = least(Y, Y - K);
-  return K == 2u ? (h & 1u) : least(Y, K - 1u);
+  int32_t y = (int32_t)h;
+  y += y < 0 ? (int32_t)K : 0;
+  y += y < 0 ? (int32_t)K : 0;
+  y -= y >= (int32_t)K ? (int32_t)K : 0;
+  return K == 2u ? (h & 1u) : ((uint32_t)y < K - 1u ? (uint32_t)y : K - 1u);
 }
 
 // Workgroups that cover L lookups, lpw to a wave.
