@@ -236,7 +236,7 @@ int radix_passes(uint32_t N) {
 // not read).  One single-pass scatter per digit; the scratch is cleared and
 // every pass's digits are counted by then.
 template <typename V, bool IDENT, typename S>
-int radix_passes_run(const Radix<V>& r, int passes, hipStream_t s) {
+int radix_passes_run(const Radix<V>& r, int passes, hipStream_t s, Gate gate = NO_GATE) {
   uint32_t* kin = r.ka;
   uint32_t* kout = r.kb;
   V* vin = r.va;
@@ -247,11 +247,11 @@ int radix_passes_run(const Radix<V>& r, int passes, hipStream_t s) {
     if (IDENT && p == 0)
       hipLaunchKernelGGL((k_onesweep<V, IDENT, S>), dim3((unsigned)r.tiles), dim3(THREADS), 0, s,
                          (const uint32_t*)kin, (const V*)vin, r.n, p * RADIX_BITS, gc, st, r.hdr + SORT_FAIL, kout,
-                         vout);
+                         vout, gate);
     else
       hipLaunchKernelGGL((k_onesweep<V, false, S>), dim3((unsigned)r.tiles), dim3(THREADS), 0, s,
                          (const uint32_t*)kin, (const V*)vin, r.n, p * RADIX_BITS, gc, st, r.hdr + SORT_FAIL, kout,
-                         vout);
+                         vout, gate);
     if (int rc = launched()) return rc;
     std::swap(kin, kout);
     std::swap(vin, vout);
@@ -259,11 +259,15 @@ int radix_passes_run(const Radix<V>& r, int passes, hipStream_t s) {
   return LRAM_OK;
 }
 
-// Clears the scratch of a sort (digit counts and look-back states); the kernel
-// that forms the keys then counts their digits into hdr.
+// The scratch that a sort starts from cleared (digit counts and look-back
+// states): words of hdr; the kernel that forms the keys then counts their digits there.
+template <typename V>
+int64_t sort_words(const Radix<V>& r, int passes) {
+  return SORT_HDR_WORDS + (int64_t)passes * r.states * RADIX * (r.n < SORT_SMALL_STATES ? 1 : 2);
+}
 template <typename V>
 int clear_sort(const Radix<V>& r, int passes, hipStream_t s) {
-  const int64_t words = SORT_HDR_WORDS + (int64_t)passes * r.states * RADIX * (r.n < SORT_SMALL_STATES ? 1 : 2);
+  const int64_t words = sort_words(r, passes);
   const int64_t zb = (words + THREADS - 1) / THREADS;
   hipLaunchKernelGGL(k_zero_words, dim3((unsigned)(zb < 1024 ? zb : 1024)), dim3(THREADS), 0, s, r.hdr, words);
   return launched();
@@ -272,9 +276,9 @@ int clear_sort(const Radix<V>& r, int passes, hipStream_t s) {
 // The passes of a sort whose digits are counted (32-bit look-back states below
 // 2^30 elements).
 template <typename V, bool IDENT>
-int sort_counted(const Radix<V>& r, int passes, hipStream_t s) {
-  return r.n < SORT_SMALL_STATES ? radix_passes_run<V, IDENT, uint32_t>(r, passes, s)
-                                 : radix_passes_run<V, IDENT, uint64_t>(r, passes, s);
+int sort_counted(const Radix<V>& r, int passes, hipStream_t s, Gate gate = NO_GATE) {
+  return r.n < SORT_SMALL_STATES ? radix_passes_run<V, IDENT, uint32_t>(r, passes, s, gate)
+                                 : radix_passes_run<V, IDENT, uint64_t>(r, passes, s, gate);
 }
 
 // The lookup order of lram_order, which is also the merged scatter's
@@ -349,10 +353,12 @@ size_t sorted_layout(int64_t L, int32_t m, SortedWs* ws, char* base) {
   return c.off;
 }
 
-// Workspace of the merged scatter's sorted runs (see RUNS_MAX): the sort of the
-// 32 L (location, (lookup, w)) pairs.
+// Workspace of the merged scatter's sorted runs (see RUNS_MAX): k_runs_gate's word
+// where an order's header is (the batch merge that it may choose lays its order
+// over the rest), then the sort of the 32 L (location, (lookup, w)) pairs.
 size_t runs_layout(int64_t L, Radix<uint2>* r, char* base) {
   Carver c{base};
+  c.take(ORDER_KEYS_OFFSET);
   const int64_t n = L * NB;
   char* ka = c.take(n * 4);
   char* kb = c.take(n * 4);
@@ -376,14 +382,27 @@ size_t runs_layout(int64_t L, Radix<uint2>* r, char* base) {
 //           2^22 1,873 / 1,523, 1,423 / 1,313; 2^24 1,942 / 2,280, 1,414 / 1,730
 //   m = 32, 2^18 846 / 582, 682 / 570; 2^20 936 / 610, 730 / 604; 2^22 919 / 875, 733 / 782
 // so the line lies at two pairs per row (m = 64) and four (m = 32; its row
-// atomics cost half).  Lookups around very few centres (64) merge better by
-// batches (657 / 804 at 2^18 rows): the queries are not known here.
+// atomics cost half).
+// Lookups around few centres merge better by batches; k_runs_gate tells them on the
+// device, by the share of a sample whose closest points repeat.  Batch merge / sorted runs at
+// that share, 64, 256 and 1,024 centres of spread 0.3, and "zipf" (half uniform, half around
+// 4,096 centres of Zipf popularity), 2^18 rows (2^16 for m = 64 and 131,072):
+//   m = 64, 524,288 lookups  1,004 / 1,579 at .77, 1,197 / 1,616 at .54, 1,532 / 1,658 at .28, 2,209 / 1,633 at .25
+//           262,144          627 / 777 at .66, 735 / 805 at .41, 971 / 830 at .18, 1,258 / 819 at .21
+//           131,072          387 / 399 at .54, 464 / 398 at .29, 553 / 404 at .11, 611 / 400 at .18
+//   m = 32, 524,288          792 / 1,050 at .76, 824 / 1,067 at .54, 954 / 1,080 at .27, 1,169 / 1,073 at .26
+//           262,144          456 / 514 at .63, 491 / 534 at .39, 599 / 540 at .16, 697 / 536 at .20
+//           131,072          281 / 275 at .52, 324 / 280 at .27, 385 / 287 at .09, 424 / 285 at .17
+// Smaller batches gain little by it (64 centres of spread 0.05, m = 32 and 131,072 lookups 243 / 262,
+// m = 64 and 65,536 207 / 226; of 0.3 281 / 275 and 263 / 235) and the gate costs them more.
 // The runs need their workspace (801 bytes per lookup, 420 MB at RUNS_MAX); an
 // order-sized one, and batches outside [RUNS_MIN, RUNS_MAX], keep the batch merge.
 constexpr int64_t RUNS_MIN = 65536, RUNS_MAX = int64_t(1) << 19;
 bool runs_chosen(int64_t L, uint32_t N, int32_t m) {
   return L >= RUNS_MIN && L <= RUNS_MAX && L * NB >= (m == 64 ? 2 : 4) * (int64_t)N;
 }
+// k_runs_gate's bar in sixteenths (0: no gate).
+int runs_bar(int64_t L, int32_t m) { return L >= 262144 ? 5 : (L >= 131072 && m == 64 ? 8 : 0); }
 
 size_t merged_bytes(int64_t L) {
   const size_t order = order_layout(L, nullptr, nullptr);
@@ -392,27 +411,27 @@ size_t merged_bytes(int64_t L) {
 
 // Fills an order: closest-point keys, the stable sort (its result lands in
 // sort.ka / sort.va whatever the number of passes), and the merge gate's count.
+// gate: an order that the device's word calls for or not, its header cleared before.
 template <int TH>
-int build_order(const float* q, const Params& P, const OrderWs& o, hipStream_t s) {
+int build_order(const float* q, const Params& P, const OrderWs& o, hipStream_t s, Gate gate = NO_GATE) {
   Radix<uint32_t> r = o.sort;
-  if (radix_passes(P.N) & 1) {  // start from the other buffers so the result lands in ka / va
+  const int passes = gate.word ? 2 : radix_passes(P.N);
+  if (passes & 1) {  // start from the other buffers so the result lands in ka / va
     std::swap(r.ka, r.kb);
     std::swap(r.va, r.vb);
   }
   // clear the sort's header (digit counts, failure word, gate partials); the
   // key kernel counts the digits and clears the look-back states
-  const int passes = radix_passes(P.N);
-  const bool small = r.n < SORT_SMALL_STATES;
-  const int64_t state_words = (int64_t)passes * r.states * RADIX * (small ? 1 : 2);
-  hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((SORT_HDR_WORDS + THREADS - 1) / THREADS)), dim3(THREADS), 0, s,
-                     r.hdr, (int64_t)SORT_HDR_WORDS);
-  const int64_t kb = (P.L + THREADS - 1) / THREADS;
-  hipLaunchKernelGGL(k_cell_key<TH>, dim3((unsigned)(kb < 1024 ? kb : 1024)), dim3(THREADS), 0, s, q, P, r.ka, passes,
-                     r.hdr, reinterpret_cast<uint32_t*>(r.state), state_words);
+  const int64_t state_words = sort_words(r, passes) - SORT_HDR_WORDS;
+  if (!gate.word)
+    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((SORT_HDR_WORDS + THREADS - 1) / THREADS)), dim3(THREADS), 0, s,
+                       r.hdr, (int64_t)SORT_HDR_WORDS);
+  const int64_t kb = (P.L + THREADS - 1) / THREADS, kb_max = gate.word ? 512 : 1024;
+  hipLaunchKernelGGL(k_cell_key<TH>, dim3((unsigned)(kb < kb_max ? kb : kb_max)), dim3(THREADS), 0, s, q, P, r.ka, passes,
+                     r.hdr, reinterpret_cast<uint32_t*>(r.state), state_words, gate);
   if (int rc = launched()) return rc;
-  if (int rc = small ? radix_passes_run<uint32_t, true, uint32_t>(r, passes, s)
-                     : radix_passes_run<uint32_t, true, uint64_t>(r, passes, s))
-    return rc;
+  if (int rc = sort_counted<uint32_t, true>(r, passes, s, gate)) return rc;
+  if (gate.word) return LRAM_OK;  // (the merge is chosen already)
   // COUNT_UNROLL positions per thread: one round of loads
   const int64_t cb = (P.L + THREADS * COUNT_UNROLL - 1) / (THREADS * COUNT_UNROLL);
   hipLaunchKernelGGL(k_count_shared, dim3((unsigned)(cb < (1 << 20) ? cb : (1 << 20))), dim3(THREADS), 0, s,
@@ -466,6 +485,33 @@ void launch_atomic(const float* q, const float* z, const Params& Pq, const void*
   }
 }
 
+// The fused search and batch merge over an order, where the gate's word chooses it.
+template <int DT, int M, int TH, int KS>
+int launch_merged(const float* q, const float* z, const Params& P, const void* table, const float* g, float* gt,
+                  float* gq, const OrderWs& o, const uint32_t* gate, NbrList saved, hipStream_t s) {
+  // one batch of at most merge_t<KS>() lookups per workgroup; three share a CU, a wave of each to a SIMD
+  Params Pm = P;
+  if (KS == NB)
+    spread(&Pm, 3);
+  else
+    Pm.lpw = lookups_per_wave_k(P.L);
+  Pm.lpw = std::min<int32_t>(Pm.lpw, merge_lpw<KS>());
+  const int64_t per_block = (int64_t)Pm.lpw * WAVES;
+  const dim3 grid((unsigned)((P.L + per_block - 1) / per_block));
+  const uint32_t* keys = o.sort.ka;
+  const uint32_t* perm = o.sort.va;
+  if constexpr (TH == IN_QUERY && KS == NB) {
+    if (saved.on()) {
+      hipLaunchKernelGGL((k_backward_merged<DT, M, IN_QUERY, NB, true>), grid, dim3(THREADS), 0, s, q, z, Pm, table, g,
+                         gt, gq, keys, perm, gate, saved);
+      return launched();
+    }
+  }
+  hipLaunchKernelGGL((k_backward_merged<DT, M, TH, KS>), grid, dim3(THREADS), 0, s, q, z, Pm, table, g, gt, gq, keys,
+                     perm, gate, saved);
+  return launched();
+}
+
 // The merged scatter for lists of KS: the lookup order (unless the caller
 // passed one: have_order), then both the atomic kernel and the merged kernel --
 // the gate's count decides on the device which one works (thinly spread
@@ -481,27 +527,7 @@ int merged_pass(const float* q, const float* z, const Params& P, const void* tab
     if (int rc = build_order<TH>(q, P, o, s)) return rc;
   launch_atomic<DT, M, TH, KS>(q, z, P, table, g, gt, gq, o.shared, nullptr, saved, s);
   if (int rc = launched()) return rc;
-  // one batch of at most merge_t<KS>() lookups per workgroup; three share a CU, a wave of each to a SIMD
-  Params Pm = P;
-  if (KS == NB)
-    spread(&Pm, 3);
-  else
-    Pm.lpw = lookups_per_wave_k(P.L);
-  Pm.lpw = std::min<int32_t>(Pm.lpw, merge_lpw<KS>());
-  const int64_t per_block = (int64_t)Pm.lpw * WAVES;
-  const dim3 grid((unsigned)((P.L + per_block - 1) / per_block));
-  const uint32_t* keys = o.sort.ka;
-  const uint32_t* perm = o.sort.va;
-  if constexpr (TH == IN_QUERY && KS == NB) {
-    if (saved.on()) {
-      hipLaunchKernelGGL((k_backward_merged<DT, M, IN_QUERY, NB, true>), grid, dim3(THREADS), 0, s, q, z, Pm, table, g,
-                         gt, gq, keys, perm, (const uint32_t*)o.shared, saved);
-      return launched();
-    }
-  }
-  hipLaunchKernelGGL((k_backward_merged<DT, M, TH, KS>), grid, dim3(THREADS), 0, s, q, z, Pm, table, g, gt, gq, keys,
-                     perm, (const uint32_t*)o.shared, saved);
-  return launched();
+  return launch_merged<DT, M, TH, KS>(q, z, P, table, g, gt, gq, o, o.shared, saved, s);
 }
 
 // The activation layer's input of a backward pass: staged in grad_in's rows
@@ -553,48 +579,69 @@ struct BwdMergedLaunch {
 };
 
 // The pairs of a location sort: search and dq, the pairs with their digits
-// counted, then the sort's passes.
-template <int DT, int M>
-int sorted_pairs(const float* q, const Params& Pq, const void* table, const float* g, float* gt, float* gq,
-                 const Radix<uint2>& r, bool th, NbrList saved, hipStream_t s) {
+// counted (into scratch cleared before), then the sort's passes.
+// gate (nullable): nothing of it where the batch is merged instead.
+template <int DT, int M, int TH>
+int sorted_pairs(const float* q, const float* z, const Params& Pq, const void* table, const float* g, float* gt,
+                 float* gq, const Radix<uint2>& r, NbrList saved, const uint32_t* gate, hipStream_t s) {
   Params P = Pq;
   P.passes = radix_passes(P.N);  // keys lie in [0, N]
-  spread(&P, th && P.L < STAGE_MIN ? kernel_waves<DT, M, IN_THETA>() : kernel_waves<DT, M, IN_QUERY>());
+  spread(&P, pair_waves<DT, M, TH>());
   const dim3 grid(grid_for(P)), b(THREADS);
   const uint32_t* const np = nullptr;
-  int rc = LRAM_OK;
-  if (gt && (rc = clear_sort(r, P.passes, s))) return rc;
-  if (th) {
-    rc = with_theta_input(q, P, gq, s, [&](auto in, const float* at, const Params& Pt) {
-      hipLaunchKernelGGL((k_backward<DT, M, true, decltype(in)::value>), grid, b, 0, s, at, q, Pt, table, g, gt, gq,
-                         r.ka, r.va, np, np, saved, r.hdr);
-      return launched();
-    });
-  } else if (saved.on()) {
-    hipLaunchKernelGGL((k_backward<DT, M, true, IN_QUERY, NB, false, true>), grid, b, 0, s, q, q, P, table, g, gt, gq,
-                       r.ka, r.va, np, np, saved, r.hdr);
-    rc = launched();
-  } else {
-    hipLaunchKernelGGL((k_backward<DT, M, true, IN_QUERY>), grid, b, 0, s, q, q, P, table, g, gt, gq, r.ka, r.va, np,
-                       np, saved, r.hdr);
-    rc = launched();
-  }
-  if (rc || !gt) return rc;
-  return sort_counted<uint2, false>(r, P.passes, s);
+  auto* kernel = &k_backward<DT, M, true, TH>;
+  if constexpr (TH == IN_QUERY)
+    if (saved.on()) kernel = &k_backward<DT, M, true, IN_QUERY, NB, false, true>;
+  hipLaunchKernelGGL(kernel, grid, b, 0, s, q, z, P, table, g, gt, gq, r.ka, r.va, gate, np, saved, r.hdr);
+  if (int rc = launched()) return rc;
+  return gt ? sort_counted<uint2, false>(r, P.passes, s, Gate{gate, true}) : LRAM_OK;
 }
 
-// The merged scatter by sorted runs.
+// The merged scatter by sorted runs, or by batches where k_runs_gate says so: the
+// kernels of both are launched, and those not chosen return at once.  2^18 rows, m = 64,
+// 262,144 lookups, before / now: uniform 832 / 852 us, 64 centres of spread 0.3 774 / 638, of 0.05 722 / 509;
+// 524,288: 1,625 / 1,655, 1,566 / 1,071, 1,481 / 908; m = 32, 524,288: 1,076 / 1,102, 992 / 797, 969 / 712.
+// batch: the caller's order, or its layout over the workspace (have_order false).
+template <int DT, int M, int TH>
+int runs_pass(const float* q, const float* z, const Params& P, const void* table, const float* g, float* gt, float* gq,
+              const Radix<uint2>& r, uint32_t* gate, const OrderWs& batch, bool have_order, NbrList saved,
+              hipStream_t s) {
+  const int passes = radix_passes(P.N);
+  if (const int bar = runs_bar(P.L, M)) {
+    const int samples = (int)std::min<int64_t>(P.L / 64, GATE_SAMPLES);
+    // (the sample waits where the keys will be)
+    hipLaunchKernelGGL(k_runs_sample<TH>, dim3(512), dim3(THREADS), 0, s, q, P, samples, (int)(P.L / samples), r.ka, r.hdr,
+                       sort_words(r, passes), batch.sort.hdr, (int64_t)(have_order ? 0 : SORT_HDR_WORDS));
+    hipLaunchKernelGGL(k_runs_gate, dim3(1), dim3(GATE_THREADS), 0, s, (const uint32_t*)r.ka, samples, P.N, bar,
+                       (uint32_t)P.L, gate);
+    if (int rc = launched()) return rc;
+  } else {
+    gate = nullptr;
+    if (int rc = clear_sort(r, passes, s)) return rc;
+  }
+  if (int rc = sorted_pairs<DT, M, TH>(q, z, P, table, g, gt, gq, r, saved, gate, s)) return rc;
+  const bool odd = passes & 1;
+  const int64_t per_block = (int64_t)RUN_SPAN * WAVES;
+  hipLaunchKernelGGL((k_run_sum<M>), dim3((unsigned)((r.n + per_block - 1) / per_block)), dim3(THREADS), 0, s,
+                     (const uint32_t*)(odd ? r.kb : r.ka), (const uint2*)(odd ? r.vb : r.va), r.n, P.N, (uint32_t)P.L, g,
+                     gt, Gate{gate, true});
+  if (int rc = launched()) return rc;
+  if (!gate) return LRAM_OK;
+  if (!have_order)
+    if (int rc = build_order<TH>(q, P, batch, s, Gate{gate, false})) return rc;
+  return launch_merged<DT, M, TH, NB>(q, z, P, table, g, gt, gq, batch, gate, saved, s);
+}
+
 template <int DT, int M>
 struct BwdRunsLaunch {
   static int go(const float* q, const Params& P, const void* table, const float* g, float* gt, float* gq,
-                const Radix<uint2>& r, bool th, NbrList saved, hipStream_t s) {
-    if (int rc = sorted_pairs<DT, M>(q, P, table, g, gt, gq, r, th, saved, s)) return rc;
-    const bool odd = radix_passes(P.N) & 1;
-    const int64_t per_block = (int64_t)RUN_SPAN * WAVES;
-    hipLaunchKernelGGL((k_run_sum<M>), dim3((unsigned)((r.n + per_block - 1) / per_block)), dim3(THREADS), 0, s,
-                       (const uint32_t*)(odd ? r.kb : r.ka), (const uint2*)(odd ? r.vb : r.va), r.n, P.N, (uint32_t)P.L,
-                       g, gt);
-    return launched();
+                const Radix<uint2>& r, uint32_t* gate, const OrderWs& batch, bool have_order, bool th, NbrList saved,
+                hipStream_t s) {
+    if (th)
+      return with_theta_input(q, P, gq, s, [&](auto in, const float* at, const Params& Pt) {
+        return runs_pass<DT, M, decltype(in)::value>(at, q, Pt, table, g, gt, gq, r, gate, batch, have_order, saved, s);
+      });
+    return runs_pass<DT, M, IN_QUERY>(q, q, P, table, g, gt, gq, r, gate, batch, have_order, saved, s);
   }
 };
 
@@ -602,8 +649,16 @@ template <int DT, int M>
 struct BwdSortedLaunch {
   static int go(const float* q, const Params& P, const void* table, const float* g, float* gt, float* gq,
                 const SortedWs& ws, bool th, NbrList saved, hipStream_t s) {
-    if (int rc = sorted_pairs<DT, M>(q, P, table, g, gt, gq, ws.sort, th, saved, s)) return rc;
-    if (!gt) return LRAM_OK;
+    if (gt)
+      if (int rc = clear_sort(ws.sort, radix_passes(P.N), s)) return rc;
+    const int rc =
+        th ? with_theta_input(q, P, gq, s,
+                              [&](auto in, const float* at, const Params& Pt) {
+                                return sorted_pairs<DT, M, decltype(in)::value>(at, q, Pt, table, g, gt, gq, ws.sort,
+                                                                                saved, nullptr, s);
+                              })
+           : sorted_pairs<DT, M, IN_QUERY>(q, q, P, table, g, gt, gq, ws.sort, saved, nullptr, s);
+    if (rc || !gt) return rc;
     const bool odd = radix_passes(P.N) & 1;
     const uint32_t* keys = odd ? ws.sort.kb : ws.sort.ka;
     const uint2* vals = odd ? ws.sort.vb : ws.sort.va;
@@ -716,7 +771,8 @@ int backward_impl(const float* in, int64_t B, int64_t H, const int32_t K[8], con
         ws_bytes >= merged_bytes(L) && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0) {
       Radix<uint2> r{};
       runs_layout(L, &r, reinterpret_cast<char*>(workspace));
-      return dispatch<BwdRunsLaunch>(dtype, m, in, P, table, grad_out, grad_table, grad_in, r, th, saved, stream);
+      return dispatch<BwdRunsLaunch>(dtype, m, in, P, table, grad_out, grad_table, grad_in, r,
+                                     reinterpret_cast<uint32_t*>(workspace), o, order != nullptr, th, saved, stream);
     }
     return dispatch<BwdMergedLaunch>(dtype, m, in, P, table, grad_out, grad_table, grad_in, o, order != nullptr, th,
                                      width, saved, stream);

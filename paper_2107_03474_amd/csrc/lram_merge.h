@@ -47,9 +47,10 @@ template <int TH>
 __global__ void __launch_bounds__(THREADS) k_cell_key(const float* __restrict__ q, Params P,
                                                       uint32_t* __restrict__ key, int passes,
                                                       uint32_t* __restrict__ ghist, uint32_t* __restrict__ clear,
-                                                      int64_t nclear) {
+                                                      int64_t nclear, Gate gate) {
   __shared__ uint32_t h[WAVES][SORT_PASSES_MAX][RADIX];
   const int t = threadIdx.x, w = t / WAVE;
+  if (gate.closed()) return;
 #pragma unroll
   for (int k = 0; k < WAVES; ++k)
 #pragma unroll
@@ -67,7 +68,10 @@ __global__ void __launch_bounds__(THREADS) k_cell_key(const float* __restrict__ 
     if (l + THREADS < e) load_input<TH>(q + (l + THREADS) * in_stride<TH>(P), v);
     float qq[8], scale;
     query_from<TH>(cur, P, qq, scale);
-    const uint32_t loc = cell_location(qq, P);
+    uint32_t loc = cell_location(qq, P);
+    // an order for the library's own batch merge only brings like lookups together: the location's
+    // leading 16 bits, two passes
+    if (gate.word) loc >>= max(16 - (int)__clz(P.N), 0);
     key[l] = loc;
 #pragma unroll
     for (int p = 0; p < SORT_PASSES_MAX; ++p)
@@ -80,6 +84,79 @@ __global__ void __launch_bounds__(THREADS) k_cell_key(const float* __restrict__ 
     const uint32_t c = h[0][p][t] + h[1][p][t] + h[2][p][t] + h[3][p][t];
     if (p < passes && c) atomicAdd(&g[p * RADIX + t], c);
   }
+}
+
+// Whether a batch that may sort its pairs (runs_chosen) is merged batch by batch
+// instead.  Lookups around few centres share their closest points, and a batch of 64 in
+// their order then leaves few rows, each read once from LDS.  k_runs_sample takes the
+// closest points of n lookups, one in `stride` at a hashed place among them, so that heads
+// and other periods of the batch do not matter, and clears the sorts' counters a[0, na)
+// and b[0, nb); k_runs_gate (one workgroup) counts those that another of the sample
+// shares: at least bar / 16 of the finite ones send the batch to the merge (*gate =
+// L, which merge_chosen accepts; otherwise 0).
+constexpr int GATE_THREADS = 1024;
+constexpr int GATE_SAMPLES = 8192;  // at most: one lookup in 64
+constexpr int GATE_HBITS = 14;      // hash entries: at most half of them taken
+static_assert(2 * GATE_SAMPLES <= (1 << GATE_HBITS), "the gate's hash keeps empty entries");
+template <int TH>
+__global__ void __launch_bounds__(THREADS) k_runs_sample(const float* __restrict__ q, Params P, int n,
+                                                         int stride, uint32_t* __restrict__ key, uint32_t* __restrict__ a,
+                                                         int64_t na, uint32_t* __restrict__ b, int64_t nb) {
+  const int64_t first = (int64_t)blockIdx.x * THREADS + threadIdx.x, step = (int64_t)gridDim.x * THREADS;
+  for (int64_t i = first; i < n; i += step) {
+    const int64_t l = i * stride + __umulhi((uint32_t)i * 0x9E3779B1u, (uint32_t)stride);
+    float qq[8], scale;
+    load_query<TH>(q + l * in_stride<TH>(P), P, qq, scale);
+    key[i] = cell_location(qq, P);
+  }
+  for (int64_t i = first; i < na; i += step) a[i] = 0u;
+  for (int64_t i = first; i < nb; i += step) b[i] = 0u;
+}
+
+__global__ void __launch_bounds__(GATE_THREADS) k_runs_gate(const uint32_t* __restrict__ keys, int n, uint32_t N,
+                                                            int bar, uint32_t L, uint32_t* __restrict__ gate) {
+  __shared__ uint32_t tab[1 << GATE_HBITS];
+  __shared__ uint32_t twice[(1 << GATE_HBITS) / 32];
+  __shared__ int finite, single;
+  const int t = threadIdx.x;
+  constexpr int U = GATE_SAMPLES / GATE_THREADS;  // keys per thread at most
+  uint32_t k[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) k[u] = t + u * GATE_THREADS < n ? keys[t + u * GATE_THREADS] : N;
+  for (int i = t; i < (1 << GATE_HBITS); i += GATE_THREADS) tab[i] = 0xFFFFFFFFu;
+  for (int i = t; i < (1 << GATE_HBITS) / 32; i += GATE_THREADS) twice[i] = 0u;
+  if (t == 0) finite = single = 0;
+  __syncthreads();
+  int nf = 0, ns = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (k[u] >= N) continue;
+    ++nf;
+    uint32_t h = (k[u] * 0x9E3779B1u) >> (32 - GATE_HBITS);
+    while (true) {
+      const uint32_t old = atomicCAS(&tab[h], 0xFFFFFFFFu, k[u]);
+      if (old == 0xFFFFFFFFu) {
+        ++ns;
+        break;
+      }
+      if (old == k[u]) {
+        if (!((atomicOr(&twice[h / 32], 1u << (h % 32)) >> (h % 32)) & 1u)) --ns;
+        break;
+      }
+      h = (h + 1) & ((1 << GATE_HBITS) - 1);
+    }
+  }
+#pragma unroll
+  for (int mask = 1; mask < WAVE; mask <<= 1) {
+    nf += __shfl_xor(nf, mask);
+    ns += __shfl_xor(ns, mask);
+  }
+  if (t % WAVE == 0) {
+    atomicAdd(&finite, nf);
+    atomicAdd(&single, ns);
+  }
+  __syncthreads();
+  if (t == 0) *gate = 16 * (finite - single) >= bar * finite ? L : 0u;
 }
 
 // Activation layer coordinates as the lookups see them: q (8 fp32) and the

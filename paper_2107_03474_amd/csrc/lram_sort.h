@@ -65,6 +65,15 @@ constexpr int COUNT_STRIDE = 32;  // words between gate-count partials
 constexpr int SORT_HDR_WORDS = SORT_COUNT + COUNT_COPIES * COUNT_STRIDE;
 static_assert((SORT_COUNT * 4) % 128 == 0, "gate-count partials start on a line");
 
+// A kernel that works only where a word on the device is set (or clear, `inverse`);
+// always without a word.
+struct Gate {
+  const uint32_t* word;
+  bool inverse;
+  __device__ __forceinline__ bool closed() const { return word && (*word != 0u) == inverse; }
+};
+constexpr Gate NO_GATE{nullptr, false};
+
 __global__ void __launch_bounds__(THREADS) k_zero_words(uint32_t* __restrict__ p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x; i < n; i += (int64_t)gridDim.x * THREADS) p[i] = 0u;
 }
@@ -154,7 +163,8 @@ template <typename V, bool IDENT, typename S>
 __global__ void __launch_bounds__(THREADS, 4) k_onesweep(const uint32_t* __restrict__ kin, const V* __restrict__ vin,
                                                       int64_t n, int shift, const uint32_t* __restrict__ gcount,
                                                       S* __restrict__ state, uint32_t* __restrict__ fail,
-                                                      uint32_t* __restrict__ kout, V* __restrict__ vout) {
+                                                      uint32_t* __restrict__ kout, V* __restrict__ vout,
+                                                      Gate gate) {
   static_assert(!IDENT || sizeof(V) == 4, "identity payloads are lookup indices");
   using C = CountState<S>;
   // look-back step: 8-byte payloads keep twice the registers across it
@@ -165,6 +175,7 @@ __global__ void __launch_bounds__(THREADS, 4) k_onesweep(const uint32_t* __restr
   __shared__ uint32_t part[2][WAVES];
   __shared__ V stage[SORT_TILE];           // keys, then payloads, in digit order
   const int t = threadIdx.x, w = t / WAVE, lane = t % WAVE;
+  if (gate.closed()) return;
 #pragma unroll
   for (int k = 0; k < WAVES; ++k) wcnt[k][t] = 0;
   __syncthreads();
@@ -422,8 +433,10 @@ constexpr int RUN_BATCH = 16;   // gather instructions in flight per wave
 template <int M>
 __global__ void __launch_bounds__(THREADS) k_run_sum(const uint32_t* __restrict__ keys, const uint2* __restrict__ vals,
                                                      int64_t n, uint32_t N, uint32_t nl,
-                                                     const float* __restrict__ gout, float* __restrict__ gtab) {
+                                                     const float* __restrict__ gout, float* __restrict__ gtab,
+                                                     Gate gate) {
   constexpr int H = WAVE / M;
+  if (gate.closed()) return;
   const int lane = threadIdx.x % WAVE, col = lane % M, h = lane / M;
   const int64_t b = ((int64_t)blockIdx.x * WAVES + (int)uniform(threadIdx.x / WAVE)) * RUN_SPAN;
   if (b >= n) return;

@@ -120,3 +120,70 @@ def test_other_callers():
     tb, zb = lram.theta_backward(z, table, K, G, mode="merged")
     assert torch.equal(za, zb)
     assert ((ta.double() - tb.double()).norm(dim=1) <= 2e-5 * ta.double().norm(dim=1) + 1e-6 * ta.double().norm(dim=1).max()).all()
+
+
+def _around(centres, spread, L, K, g):
+    Kd = torch.tensor(K, device=DEV, dtype=torch.float64)
+    mu = torch.rand((centres, 8), generator=g, device=DEV, dtype=torch.float64) * Kd
+    q = mu[torch.randint(0, centres, (L,), generator=g, device=DEV)]
+    q = torch.remainder(q + spread * torch.randn((L, 8), generator=g, device=DEV, dtype=torch.float64), Kd).float()
+    return torch.where(q >= Kd.float(), torch.zeros_like(q), q).contiguous()
+
+
+@pytest.mark.parametrize("m,dtype", [(32, torch.float32), (64, torch.bfloat16)])
+@pytest.mark.parametrize("L,few", [(131072, True), (262144 + 3, True), (262144 + 3, False), (524288, True)])
+def test_few_centres(L, few, m, dtype):
+    """Lookups around few centres are merged batch by batch although their pairs may be sorted (the first word of the
+    workspace tells), others and smaller batches are not; every caller's form of either."""
+    gated = m == 64 or L >= 262144                         # otherwise nothing writes that word
+    _say("few centres L=%d %s m=%d" % (L, few, m))
+    K = (4, 4, 4, 4, 4, 4, 8, 8)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + m)
+    q = _around(16, 0.2, L, K, g) if few else torch.rand((L, 8), generator=g, device=DEV) * torch.tensor(K, device=DEV)
+    q[::3, 5] = float("inf")                               # (not counted on either side)
+    ws = torch.empty(lram.backward_workspace_bytes(L, 1, m, "merged"), dtype=torch.uint8, device=DEV)
+
+    def word():
+        return int(ws[:4].view(torch.int32).item())
+
+    def plain(*a):
+        ws.fill_(0xA5)
+        return lram.backward(*a, mode="merged", workspace=ws)
+
+    def ordered(q, table, K, G):
+        ws.fill_(0xA5)
+        return lram.backward(q, table, K, G, mode="merged", workspace=ws, order=lram.order(q, K))
+
+    def saved(q, table, K, G):
+        ws.fill_(0xA5)
+        nl = lram.new_lists(q)
+        lram.forward(q, table, K, lists=nl)
+        return lram.backward(q, table, K, G, mode="merged", workspace=ws, lists=nl)
+
+    for form in (plain, ordered, saved):
+        table, G = _compare(q, K, m, dtype, 1, form)
+        assert gated == (word() in (0, L)) and (not gated or word() == (L if few else 0)), form
+    z = torch.cat([torch.cos(q.double() * (2 * np.pi) / torch.tensor(K, device=DEV))[..., None],
+                   torch.sin(q.double() * (2 * np.pi) / torch.tensor(K, device=DEV))[..., None]], -1)
+    z = z.reshape(L, 16).float().nan_to_num(0.5).contiguous()
+    ta, za = lram.theta_backward(z, table, K, G, mode="atomic")
+    tb, zb = lram.theta_backward(z, table, K, G, mode="merged", workspace=ws)
+    assert not gated or word() == (L if few else 0)
+    assert torch.equal(za, zb)
+    err, size = (ta.double() - tb.double()).norm(dim=1), ta.double().norm(dim=1)
+    assert (err <= 2e-5 * size + 1e-6 * size.max()).all()
+
+
+def test_long_runs():
+    """One query below the sizes that the gate looks at: runs over many spans, no merge by batches."""
+    K, L, m = (4,) * 8, 70001, 32
+    q = torch.full((L, 8), 1.3, device=DEV) + torch.arange(8, device=DEV) * 0.11
+    ws = torch.empty(lram.backward_workspace_bytes(L, 1, m, "merged"), dtype=torch.uint8, device=DEV)
+    table = torch.randn((4 ** 8, m), device=DEV)
+    G = torch.rand((L, m), device=DEV) + 0.5               # one sign: sums of L terms, relative error below L 2^-24
+    gt, _ = lram.backward(q, table, K, G, mode="merged", workspace=ws)
+    slot, w, _ = lram.neighbors(q[:1], K)
+    ref = w[0].double()[:, None] * G.double().sum(0)[None]
+    got = gt[slot[0].long()].double()
+    assert ((got - ref).norm(dim=1) <= 1e-4 * ref.norm(dim=1)).all()
