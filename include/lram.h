@@ -78,7 +78,9 @@ typedef enum {
                               bit-reproducible from call to call */
   LRAM_SCATTER_MERGED = 2, /* tables small against the batch's pairs (65,536 to 524,288 lookups of k = 32, at
                               least 2 (m = 64) or 4 (m = 32) pairs per row, and the whole workspace given): sort
-                              the (slot, lookup) pairs, one atomic row per run of equal slots; otherwise
+                              the (slot, lookup) pairs, one atomic row per run of equal slots, unless a sample of
+                              a larger batch (from 131,072 lookups at m = 64, 262,144 at m = 32) shows on the
+                              device that its lookups gather around few points; otherwise
                               order lookups by their closest lattice point, merge equal slots within
                               each batch of consecutive lookups (64 for lists of up to 32, 32 for
                               longer ones), one atomic row per distinct slot;
@@ -195,8 +197,10 @@ int lram_scatter_mode_resolved(int64_t B, int64_t H, int mode, int* resolved);
  *   grad_q[l][i] = sum_j -2 u_j^3 (x_i - k_{j,i}) <grad_out[l], table[slot_j]>,
  *       u_j = 1 - s_j/8 (overwritten; nullable to skip it)
  * order/order_bytes: nullable; an order from lram_order for these queries.
- * The merged scatter then takes it instead of sorting (no workspace needed),
- * the atomic one visits the lookups in it, the sorted one ignores it.
+ * The merged scatter then takes it instead of ordering the lookups itself (no
+ * workspace needed; given a whole one apart from the order, a call that may sort
+ * its pairs writes there and uses the order only if it merges by batches after
+ * all), the atomic one visits the lookups in it, the sorted one ignores it.
  * nbr_slot/nbr_w/nbr_code: nullable (all three or none); the lists lram_forward
  * saved for these queries replace the neighbour search (each entry's distance
  * is recomputed from its code for dq).  Entries whose location is outside
@@ -338,7 +342,9 @@ int lram_backward_k(const float* q, int64_t B, int64_t H, const int32_t K[8], co
 int lram_theta_coords(const float* z, int64_t B, int64_t H, const int32_t K[8], float* q, float* s, void* stream);
 
 /* lram_theta_forward -- out[l] = theta(z_l) in the table dtype (fp32
- * accumulation, the scale folded into the 32 weights, one rounding). */
+ * accumulation, the scale folded into the 32 weights, one rounding).  From 16,384
+ * lookups on the rows of out hold the lookups' coordinates until they are
+ * written (not where out shares memory with z). */
 int lram_theta_forward(const float* z, int64_t B, int64_t H, const int32_t K[8], const void* table, int dtype,
                        int64_t N, int32_t m, void* out, void* stream);
 
@@ -348,7 +354,8 @@ int lram_theta_forward(const float* z, int64_t B, int64_t H, const int32_t K[8],
  *   grad_table[s] += sum over (l, j) with slot_j(l) = s of scale_l w_j grad_out[l]
  *       (accumulated; same modes, workspace and rules as lram_backward, whose
  *        lram_backward_workspace_bytes applies unchanged)
- *   grad_z[l] [16] fp32 (overwritten; nullable): with r_i = |z_i|, c_i = K_i/2pi,
+ *   grad_z[l] [16] fp32 (overwritten; nullable; from 16,384 lookups on it holds the
+ *       lookups' coordinates in between): with r_i = |z_i|, c_i = K_i/2pi,
  *       dL/ds = sum_j w_j <G, v_j>, dL/dq = s dq (dq as in lram_backward),
  *       dL/dRe z_i = dL/ds s^2 Re z_i / r_i^3 - dL/dq_i c_i Im z_i / r_i^2,
  *       dL/dIm z_i = dL/ds s^2 Im z_i / r_i^3 + dL/dq_i c_i Re z_i / r_i^2.

@@ -395,8 +395,10 @@ size_t runs_layout(int64_t L, Radix<uint2>* r, char* base) {
 //           131,072          281 / 275 at .52, 324 / 280 at .27, 385 / 287 at .09, 424 / 285 at .17
 // Smaller batches gain little by it (64 centres of spread 0.05, m = 32 and 131,072 lookups 243 / 262,
 // m = 64 and 65,536 207 / 226; of 0.3 281 / 275 and 263 / 235) and the gate costs them more.
-// The runs need their workspace (801 bytes per lookup, 420 MB at RUNS_MAX); an
-// order-sized one, and batches outside [RUNS_MIN, RUNS_MAX], keep the batch merge.
+// The runs need their workspace (801 bytes per lookup, 420 MB at RUNS_MAX, which
+// is all that RUNS_MAX bounds: the gain per lookup still grows there); an order-sized
+// one, and batches outside [RUNS_MIN, RUNS_MAX], keep the batch merge.  Below RUNS_MIN
+// only a caller who asks for the merged scatter would come here (AUTO_MERGE_MIN).
 constexpr int64_t RUNS_MIN = 65536, RUNS_MAX = int64_t(1) << 19;
 bool runs_chosen(int64_t L, uint32_t N, int32_t m) {
   return L >= RUNS_MIN && L <= RUNS_MAX && L * NB >= (m == 64 ? 2 : 4) * (int64_t)N;
