@@ -43,9 +43,9 @@ def _merged(q, table, K, G):
 @pytest.mark.parametrize("L,K", [
     (65535, (4, 4, 4, 4, 4, 4, 4, 4)),     # below RUNS_MIN: the batch merge
     (65536, (4, 4, 4, 4, 4, 4, 4, 4)),
-    (65537, (4, 4, 6, 4, 6, 4, 4, 8)),     # ragged, an uneven torus, two to four pairs per row
+    (65537, (4, 4, 6, 4, 6, 4, 4, 8)),     # ragged, an uneven torus, 294,912 rows
     (131072 + 5, (2, 2, 4, 2, 2, 4, 2, 2)),  # 1,024 rows, both lifts of a side of 2, long runs
-    (131072, (8, 8, 8, 8, 4, 4, 8, 4)),    # 2^22 rows / 2^22 pairs: the batch merge on this side of the line
+    (131072, (8, 8, 8, 8, 4, 4, 8, 4)),    # 2^21 rows, two pairs per row: sorted runs for m = 64, the batch merge for m = 32
 ])
 def test_runs(L, K, m, dtype):
     _say("runs L=%d K=%s m=%d %s" % (L, K, m, dtype))
@@ -187,3 +187,54 @@ def test_long_runs():
     ref = w[0].double()[:, None] * G.double().sum(0)[None]
     got = gt[slot[0].long()].double()
     assert ((got - ref).norm(dim=1) <= 1e-4 * ref.norm(dim=1)).all()
+
+
+def _path(ws):
+    """What the merged scatter did with a workspace that was 0xA5: "batch" -- an order of its own, whose header ends in
+    a failure word of 0; "untouched"; "runs" -- sorted pairs, or the gate's choice between them and a batch merge, which
+    writes the first word at most."""
+    if int(ws[4:8].view(torch.int32).item()) == 0:
+        return "batch"
+    return "runs" if bool((ws[256:1024] != 0xA5).any()) else "untouched"
+
+
+@pytest.mark.parametrize("m", [32, 64])
+@pytest.mark.parametrize("L,K", [
+    (65535, (4,) * 8),                     # the smallest batch that sorts, and one below
+    (65536, (4,) * 8),
+    (524288, (4,) * 8),                    # the largest, and one above
+    (524289, (4,) * 8),
+    (65536, (4, 4, 4, 4, 4, 8, 8, 8)),     # 2^19 rows, four pairs per row; one lookup less is below m = 32's line
+    (131071, (4, 4, 4, 4, 8, 8, 8, 8)),
+    (131072, (4, 4, 4, 4, 8, 8, 8, 8)),
+    (100003, (4, 4, 4, 4, 8, 8, 8, 8)),    # between two and four
+    (131071, (8, 8, 8, 8, 4, 4, 8, 4)),    # just below two
+])
+def test_line(L, K, m):
+    """The rule's line (sizes, pairs per row) and every caller's form on both sides of it: with and without an order,
+    lists and a query gradient."""
+    N = int(np.prod(K))
+    sorts = 65536 <= L <= 524288 and 32 * L >= (2 if m == 64 else 4) * N
+    _say("line L=%d K=%s m=%d: %s" % (L, K, m, "runs" if sorts else "batch"))
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    q = torch.rand((L, 8), generator=g, device=DEV) * torch.tensor(K, device=DEV)
+    order = lram.order(q, K)
+    ws = torch.empty(max(lram.backward_workspace_bytes(L, 1, m, "merged"), lram.order_layout(L, 1)[0]),
+                     dtype=torch.uint8, device=DEV)
+
+    def call(q, table, K, G, **kw):
+        ws.fill_(0xA5)
+        return lram.backward(q, table, K, G, mode="merged", workspace=ws, **kw)
+
+    table, G = _compare(q, K, m, torch.float32, 1, call)
+    assert _path(ws) == ("runs" if sorts else "batch")
+    _compare(q, K, m, torch.float32, 1, lambda *a: call(*a, order=order))
+    assert _path(ws) == ("runs" if sorts else "untouched")
+    nl = lram.new_lists(q)
+    lram.forward(q, table, K, lists=nl)
+    _compare(q, K, m, torch.float32, 1, lambda *a: call(*a, lists=nl, order=order))
+    assert _path(ws) == ("runs" if sorts else "untouched")
+    _compare(q, K, m, torch.float32, 1,
+             lambda *a: (call(*a, want_grad_q=False)[0], lram.backward(*a, mode="atomic")[1]))
+    assert _path(ws) == ("runs" if sorts else "batch")
