@@ -69,9 +69,10 @@ bool misaligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3) !=
 constexpr int64_t STAGE_MIN = 16384;
 
 // How the lookups are spread over the waves of a kernel built for `waves` per SIMD.
-void spread(Params* P, int waves) {
+constexpr int64_t ANY_ROUNDS = INT64_MAX;
+void spread(Params* P, int waves, int64_t max_rounds = 2) {
   P->tiled = tile_search(P->L, waves);
-  P->lpw = lookups_per_wave(P->L, waves);
+  P->lpw = lookups_per_wave(P->L, waves, max_rounds);
 }
 
 int check_common(const float* q, int64_t B, int64_t H, const int32_t* K, int64_t* L, Params* P) {
@@ -452,7 +453,7 @@ void launch_atomic(const float* q, const float* z, const Params& Pq, const void*
                    const uint32_t* gate, const uint32_t* perm, NbrList saved, hipStream_t s) {
   Params P = Pq;
   if (KS == NB)
-    spread(&P, kernel_waves<DT, M, TH>());
+    spread(&P, kernel_waves<DT, M, TH>(), ANY_ROUNDS);
   else
     P.lpw = lookups_per_wave_k(P.L);
   // in the lookup order neighbouring waves add to the same rows: long runs of
@@ -494,7 +495,7 @@ int launch_merged(const float* q, const float* z, const Params& P, const void* t
   // one batch of at most merge_t<KS>() lookups per workgroup; three share a CU, a wave of each to a SIMD
   Params Pm = P;
   if (KS == NB)
-    spread(&Pm, 3);
+    spread(&Pm, 3, 1);
   else
     Pm.lpw = lookups_per_wave_k(P.L);
   Pm.lpw = std::min<int32_t>(Pm.lpw, merge_lpw<KS>());
@@ -588,7 +589,7 @@ int sorted_pairs(const float* q, const float* z, const Params& Pq, const void* t
                  float* gq, const Radix<uint2>& r, NbrList saved, const uint32_t* gate, hipStream_t s) {
   Params P = Pq;
   P.passes = radix_passes(P.N);  // keys lie in [0, N]
-  spread(&P, pair_waves<DT, M, TH>());
+  spread(&P, pair_waves<DT, M, TH>(), ANY_ROUNDS);
   const dim3 grid(grid_for(P)), b(THREADS);
   const uint32_t* const np = nullptr;
   auto* kernel = &k_backward<DT, M, true, TH>;

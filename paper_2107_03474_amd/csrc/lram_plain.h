@@ -34,19 +34,28 @@ constexpr int64_t LMAX = (int64_t(1) << 31) - 1;  // lookups per call
 // Tiles of 2 / 4 / 6 / 8 / 12 / 16, forward: 16,384 lookups 22.5 / 17.2 / 16.7 / 17.1 / 19.8 / 22.2; 24,576
 // 28.4 / 25.3 / 19.9 / 20.1 / 21.2 / 23.8; 32,768 35.9 / 28.0 / 29.1 / 23.3 / 24.5 / 24.7; 49,152 50.5 / 40.0 / 34.1 /
 // 35.6 / 31.4 / 32.1; backward: 12,000 109 / 104 / 106 / 110 / - / -; 32,768 277 / 277 / 288 / 275 / 281 / 284.  Forward of
-// 262,144 (2^20 rows, m = 64 fp32), 4 / 8 / 16 / 32 / 64 to a wave: 352 / 309 / 304 / 305 / 320.  From 2^30 lookups on
+// 262,144 (2^20 rows, m = 64 fp32), 4 / 8 / 16 / 32 / 64 to a wave: 352 / 309 / 304 / 305 / 320.  Batches below
+// 524,288 that need a few rounds of waves (max_rounds at most: 2, any number where row atomics hide the
+// tiles' cost, none where a batch is merged) spread evenly over them; whole tiles leave the last
+// round nearly empty: 70,000 lookups, whole tiles / evenly, forward (2^24 rows, m = 32 bf16) 61.1 / 51.6,
+// backward with row atomics (2^20, m = 64 bf16) 511 / 464.  From 2^30 lookups on
 // a wave takes 64: 32 would make a grid of 2^32 work-items, which no launch accepts.
 constexpr int64_t fill_waves(int64_t L, int waves) { return (L + waves * SIMDS - 1) / (waves * SIMDS); }
 constexpr bool tile_search(int64_t L, int waves) { return fill_waves(L, waves) > 2; }
-constexpr int32_t lookups_per_wave(int64_t L, int waves) {
+constexpr int32_t lookups_per_wave(int64_t L, int waves, int64_t max_rounds) {
   const int64_t n = fill_waves(L, waves);
-  const int64_t top = L < (int64_t(1) << 19) ? TILE : (L < (int64_t(1) << 30) ? 2 * TILE : WAVE);
-  return (int32_t)(n < 1 ? 1 : (n <= 2 ? n : (n > top ? top : (n + 1) / 2 * 2)));
+  if (n <= 2) return (int32_t)(n < 1 ? 1 : n);
+  if (L < (int64_t(1) << 19)) {
+    const int64_t rounds = (n + TILE - 1) / TILE;
+    return rounds > max_rounds ? TILE : (int32_t)(((n + rounds - 1) / rounds + 1) / 2 * 2);
+  }
+  return L < (int64_t(1) << 30) ? 2 * TILE : WAVE;
 }
-// Lists other than the closest 32, whose search costs the same for every lookup.
+// Lists other than the closest 32, whose search costs the same for every lookup (64 at most, and
+// evenly over the rounds of waves).
 constexpr int32_t lookups_per_wave_k(int64_t L) {
-  const int64_t n = fill_waves(L, 4);
-  return (int32_t)(n < 1 ? 1 : (n > WAVE ? WAVE : n));
+  const int64_t n = fill_waves(L, 4), rounds = (n + WAVE - 1) / WAVE;
+  return (int32_t)(n < 1 ? 1 : (n + rounds - 1) / rounds);
 }
 
 // h mod K for K even, at least 2, and h in [-K - 3, K + 3] (as uint32_t: two's
@@ -70,8 +79,8 @@ constexpr int64_t blocks_for(int64_t L, int32_t lpw) {
 // they are added (measured beside k_access_hist), and the lookups per wave.
 constexpr bool hist_merged(int64_t L) { return L >= 16384; }
 constexpr int32_t hist_lookups_per_wave(int64_t L) {
-  const int32_t lpw = lookups_per_wave(L, 4);
-  return !hist_merged(L) || lpw < TILE / 2 ? lpw : (L < 98304 ? TILE / 2 : TILE);
+  const int32_t lpw = lookups_per_wave(L, 4, INT64_MAX);
+  return !hist_merged(L) || lpw < TILE / 2 ? lpw : (L < 98304 ? TILE / 2 : (lpw < TILE ? lpw : TILE));
 }
 
 // Lookups per launch of the access histogram, whose waves take one tile each:

@@ -21,8 +21,8 @@ int main() {
     for (int64_t d = -200; d <= 200; ++d) {
       const int64_t L = (int64_t(1) << s) + d;
       if (L < 1 || L > LMAX) continue;
-      for (int waves = 1; waves <= 4; ++waves) {
-        const int32_t lpw = waves == 1 ? lookups_per_wave_k(L) : lookups_per_wave(L, waves);
+      for (int waves = 1; waves <= 4; ++waves) for (int64_t rounds : {int64_t(1), int64_t(2), INT64_MAX}) {
+        const int32_t lpw = waves == 1 ? lookups_per_wave_k(L) : lookups_per_wave(L, waves, rounds);
         const int64_t blocks = blocks_for(L, lpw);
         if (lpw < 1 || lpw > WAVE || blocks * WAVES * lpw < L || blocks * THREADS >= items)
           std::printf("L = %lld waves = %d: %d lookups per wave, %lld blocks\n", (long long)L, waves, lpw, (long long)blocks);
@@ -57,16 +57,25 @@ def test_every_accepted_batch_launches(tmp_path):
 
 SMALL = r"""
 #include <cstdio>
+#include <initializer_list>
 #include "lram_plain.h"
 int main() {
   for (int waves = 2; waves <= 4; ++waves)
     for (int64_t L = 1; L <= 200000; ++L) {
       const int64_t room = waves * SIMDS;
-      const int32_t lpw = lookups_per_wave(L, waves);
+      const int32_t lpw = lookups_per_wave(L, waves, 1);
       const bool tile = tile_search(L, waves);
       // one lookup each while there is a wave for each, then two, and tiles above: no more than an even number needs
       bool ok = tile == (L > 2 * room) && (tile || lpw == (L > room ? 2 : 1));
       if (tile) ok = lpw % 2 == 0 && lpw <= TILE && (lpw == 4 || (lpw - 2) * room < L) && (lpw == TILE || lpw * room >= L);
+      // evenly over as many rounds as whole tiles need: no more rounds, and no more lookups than they take
+      for (int64_t most : {int64_t(2), INT64_MAX}) {
+        const int64_t rounds = (L + TILE * room - 1) / (TILE * room);
+        const int32_t even = lookups_per_wave(L, waves, most);
+        ok = ok && (rounds == 1 || rounds > most ? even == lpw
+                                                 : even % 2 == 0 && even <= TILE && even * room * rounds >= L &&
+                                                       (even - 2) * room * rounds < L);
+      }
       if (!ok) std::printf("%d waves: %lld %d %d\n", waves, (long long)L, tile, lpw);
     }
   return 0;
