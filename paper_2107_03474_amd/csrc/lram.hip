@@ -404,8 +404,12 @@ constexpr int64_t RUNS_MIN = 65536, RUNS_MAX = int64_t(1) << 19;
 bool runs_chosen(int64_t L, uint32_t N, int32_t m) {
   return L >= RUNS_MIN && L <= RUNS_MAX && L * NB >= (m == 64 ? 2 : 4) * (int64_t)N;
 }
-// k_runs_gate's bar in sixteenths (0: no gate).
-int runs_bar(int64_t L, int32_t m) { return L >= 262144 ? 5 : (L >= 131072 && m == 64 ? 8 : 0); }
+// k_runs_gate's bar in sixteenths (0: no gate).  A caller's order saves the batch merge
+// its own sort (64 centres of spread 0.3, 2^20 rows, an order given, sorted runs / now: 140,000 lookups, m = 32
+// bf16 298 / 250 us, with saved lists 317 / 252; 70,000, m = 64 bf16 252 / 226).
+int runs_bar(int64_t L, int32_t m, bool order) {
+  return order || L >= 262144 ? 5 : (L >= 131072 && m == 64 ? 8 : 0);
+}
 
 size_t merged_bytes(int64_t L) {
   const size_t order = order_layout(L, nullptr, nullptr);
@@ -610,7 +614,7 @@ int runs_pass(const float* q, const float* z, const Params& P, const void* table
               const Radix<uint2>& r, uint32_t* gate, const OrderWs& batch, bool have_order, NbrList saved,
               hipStream_t s) {
   const int passes = radix_passes(P.N);
-  if (const int bar = runs_bar(P.L, M)) {
+  if (const int bar = runs_bar(P.L, M, have_order)) {
     const int samples = (int)std::min<int64_t>(P.L / 64, GATE_SAMPLES);
     // (the sample waits where the keys will be)
     hipLaunchKernelGGL(k_runs_sample<TH>, dim3(512), dim3(THREADS), 0, s, q, P, samples, (int)(P.L / samples), r.ka, r.hdr,

@@ -131,11 +131,11 @@ def _around(centres, spread, L, K, g):
 
 
 @pytest.mark.parametrize("m,dtype", [(32, torch.float32), (64, torch.bfloat16)])
-@pytest.mark.parametrize("L,few", [(131072, True), (262144 + 3, True), (262144 + 3, False), (524288, True)])
+@pytest.mark.parametrize("L,few", [(65536, True), (131072, True), (262144 + 3, True), (262144 + 3, False), (524288, True)])
 def test_few_centres(L, few, m, dtype):
     """Lookups around few centres are merged batch by batch although their pairs may be sorted (the first word of the
     workspace tells), others and smaller batches are not; every caller's form of either."""
-    gated = m == 64 or L >= 262144                         # otherwise nothing writes that word
+    gated = L >= (131072 if m == 64 else 262144)                         # otherwise nothing writes that word
     _say("few centres L=%d %s m=%d" % (L, few, m))
     K = (4, 4, 4, 4, 4, 4, 8, 8)
     g = torch.Generator(device=DEV)
@@ -161,7 +161,9 @@ def test_few_centres(L, few, m, dtype):
         lram.forward(q, table, K, lists=nl)
         return lram.backward(q, table, K, G, mode="merged", workspace=ws, lists=nl)
 
-    for form in (plain, ordered, saved):
+    _compare(q, K, m, dtype, 1, ordered)                   # (an order brings the gate with it at any size)
+    assert word() == (L if few else 0)
+    for form in (plain, saved):
         table, G = _compare(q, K, m, dtype, 1, form)
         assert gated == (word() in (0, L)) and (not gated or word() == (L if few else 0)), form
     z = torch.cat([torch.cos(q.double() * (2 * np.pi) / torch.tensor(K, device=DEV))[..., None],
