@@ -208,8 +208,8 @@ __device__ __forceinline__ void theta_chain(const Frame* FR, const WL& W, int nt
 // Waves per SIMD of the backward that emits pairs.  Rows of 64 columns spill three
 // registers at four (bf16, a whole backward by sorted runs, 2^18 rows, four / three: 262,144
 // lookups 722 / 711 us, 524,288 1,440 / 1,407); rows of 32 are as fast or faster at four
-// (540 / 549, 1,059 / 1,085), and so are those behind the staged activation layer, ten
-// spilled registers included (m = 64 bf16 760 / 778, 1,476 / 1,521).
+// (540 / 549, 1,059 / 1,085; three spilled), and so are those behind the staged activation
+// layer, nine spilled registers included (m = 64 bf16 760 / 778, 1,476 / 1,521).
 template <int DT, int M, int TH>
 constexpr int pair_waves() { return TH == IN_QUERY && M == 64 ? 3 : kernel_waves<DT, M, TH>(); }
 

@@ -191,6 +191,39 @@ def test_long_runs():
     assert ((got - ref).norm(dim=1) <= 1e-4 * ref.norm(dim=1)).all()
 
 
+def test_gate_in_a_graph():
+    """A captured backward chooses anew at every replay: uniform, clustered and again uniform queries in its buffer,
+    with eager work between the replays."""
+    K, L, m = (4, 4, 4, 4, 4, 4, 8, 8), 131072, 64
+    g = torch.Generator(device=DEV)
+    g.manual_seed(8)
+    N = int(np.prod(K))
+    batches = [torch.rand((L, 8), generator=g, device=DEV) * torch.tensor(K, device=DEV), _around(16, 0.2, L, K, g)]
+    table = torch.randn((N, m), generator=g, device=DEV) * 0.02
+    G = torch.randn((L, m), generator=g, device=DEV)
+    ws = torch.empty(lram.backward_workspace_bytes(L, 1, m, "merged"), dtype=torch.uint8, device=DEV)
+    q, gt, gq = batches[0].clone(), torch.zeros((N, m), device=DEV), torch.empty((L, 8), device=DEV)
+
+    def step():
+        lram.backward(q, table, K, G, grad_table=gt, grad_q=gq, mode="merged", workspace=ws)
+
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for which in (0, 1, 0, 1):
+        q.copy_(batches[which])
+        gt.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(ws[:4].view(torch.int32).item()) == (L if which else 0)
+        want, wq = lram.backward(q, table, K, G, mode="atomic")
+        assert torch.equal(gq, wq)
+        err, size = (gt.double() - want.double()).norm(dim=1), want.double().norm(dim=1)
+        assert (err <= 2e-5 * size + 1e-6 * size.max()).all()
+
+
 def _path(ws):
     """What the merged scatter did with a workspace that was 0xA5: "batch" -- an order of its own, whose header ends in
     a failure word of 0; "untouched"; "runs" -- sorted pairs, or the gate's choice between them and a batch merge, which
